@@ -97,6 +97,12 @@ int64_t batch_slot_elems(const cc_plan *p, int s) {
   return sl.name == "t1" ? int64_t(p->o) * p->v : int64_t(p->o) * p->o * p->v * p->v;
 }
 
+// the split-K factor a grouped launch of this step uses (FP64 real systems
+// have one of their own)
+int &split_of(const cc_batch *B, Step &st) {
+  return B->prec == PREC_F64 && !B->cplx ? st.split64 : st.gemm.split;
+}
+
 // (Re)build the device tables of every grouped step from the plans' current
 // per-call state (amplitude pointers, shift, denominator mode).
 void build_tables(cc_batch *B) {
@@ -174,7 +180,7 @@ void build_tables(cc_batch *B) {
           if (work > best) {
             best = work;
             if (B->prec == PREC_F64)
-              g.tile = st.tile >= 0 ? st.tile : gemm_f64_pick(st.gemm.M, st.gemm.N, st.gemm.K, g.akc, g.bkc);
+              g.tile = std::max(st.tile, 0);
             else
               g.tile = st.tile_lp[B->prec] >= 0 && gemm_lowp_tile_grouped(B->prec, st.tile_lp[B->prec])
                            ? st.tile_lp[B->prec]
@@ -188,6 +194,7 @@ void build_tables(cc_batch *B) {
           const Step &st = p->iter[k];
           GemmGroupEntry e{};
           e.d = st.gemm;
+          e.d.split = split_of(B, p->iter[k]);
           e.d.A = ptr_of(p, st.a);
           e.d.B = ptr_of(p, st.b);
           e.d.C = ptr_of(p, st.c);
@@ -381,7 +388,7 @@ void run_gstep(cc_batch *B, size_t k, hipStream_t s) {
         d.C = ptr_of(p, st.c);
         d.ws = st.b2 >= 0 ? ptr_of(p, st.b2) : nullptr;
         if (cplx) gemm_c128(d, s, st.tile_z);
-        else if (B->prec == PREC_F64) gemm_f64(d, s, st.tile);
+        else if (B->prec == PREC_F64) gemm_f64(gemm_f64_desc(st, d), s, st.tile);
         else gemm_lowp(d, B->prec, s, st.tile_lp[B->prec]);
       } else if (st.kind == Step::PERMUTE) {
         launch_perm(make_perm_entry(st.perm, ptr_of(p, st.a), ptr_of(p, st.c)), cplx, s);
@@ -447,7 +454,7 @@ void batch_group_splits(cc_batch *B) {
   B->own_split.assign(B->plans[0]->iter.size(), {});
   for (size_t k = 0; k < B->plans[0]->iter.size(); ++k) {
     if (B->plans[0]->iter[k].kind != Step::GEMM) continue;
-    for (cc_plan *p : B->plans) B->own_split[k].push_back(p->iter[k].gemm.split);
+    for (cc_plan *p : B->plans) B->own_split[k].push_back(split_of(B, p->iter[k]));
     int64_t tiles = 0;
     for (cc_plan *p : B->plans) {
       const GemmDesc &d = p->iter[k].gemm;
@@ -455,8 +462,8 @@ void batch_group_splits(cc_batch *B) {
     }
     const int64_t split = tiles >= 2048 ? 1 : (2048 + tiles - 1) / std::max<int64_t>(tiles, 1);
     for (cc_plan *p : B->plans) {
-      GemmDesc &d = p->iter[k].gemm;
-      d.split = int(std::max<int64_t>(1, std::min<int64_t>({split, int64_t(d.split), std::max<int64_t>(1, d.K / 256)})));
+      int &own = split_of(B, p->iter[k]);
+      own = int(std::max<int64_t>(1, std::min<int64_t>({split, int64_t(own), std::max<int64_t>(1, p->iter[k].gemm.K / 256)})));
     }
   }
 }
@@ -528,11 +535,11 @@ void batch_autotune(cc_batch *B, int reps) {
         std::vector<int> cur;
         bool differs = false;
         for (size_t b = 0; b < B->plans.size(); ++b) {
-          cur.push_back(B->plans[b]->iter[k].gemm.split);
+          cur.push_back(split_of(B, B->plans[b]->iter[k]));
           differs = differs || cur[b] != B->own_split[k][b];
         }
         if (differs) {
-          for (size_t b = 0; b < B->plans.size(); ++b) B->plans[b]->iter[k].gemm.split = B->own_split[k][b];
+          for (size_t b = 0; b < B->plans.size(); ++b) split_of(B, B->plans[b]->iter[k]) = B->own_split[k][b];
           build_tables(B);
           run_gstep(B, k, s);
           CC_HIP_CHECK(hipEventRecord(e0, s));
@@ -542,7 +549,7 @@ void batch_autotune(cc_batch *B, int reps) {
           float ms = 0.f;
           CC_HIP_CHECK(hipEventElapsedTime(&ms, e0, e1));
           if (ms >= best_ms)
-            for (size_t b = 0; b < B->plans.size(); ++b) B->plans[b]->iter[k].gemm.split = cur[b];
+            for (size_t b = 0; b < B->plans.size(); ++b) split_of(B, B->plans[b]->iter[k]) = cur[b];
         }
       }
     }

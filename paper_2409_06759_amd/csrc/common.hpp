@@ -68,6 +68,7 @@ struct GemmDesc {
   int split = 1;               // split-K factor; > 1 needs ws of split*M*N elements
   void *ws = nullptr;
   int64_t ws_elems = 0;        // capacity of ws in elements (the tail cut checks it)
+  int refine = 1;              // 0: split is final (chosen together with the tile)
   // reduced precision with converted operands ("shadows"): A and B point to
   // FP32 (F32) or to bf16 hi planes whose lo planes follow at +a_plane /
   // +b_plane elements (BF16X3), indexed exactly like the FP64 tensors
@@ -141,7 +142,15 @@ int gemm_c128_num_tiles();
 const char *gemm_c128_tile_name(int id);
 int gemm_f64_num_tiles();
 const char *gemm_f64_tile_name(int id);
-int gemm_f64_pick(int64_t M, int64_t N, int64_t K, bool a_kc, bool b_kc);
+// Tile and split-K factor of an FP64 GEMM from a model of its time; partial
+// sums of at most ws_elems elements (0: no split).  lds_direct: the operands
+// suit the LDS-direct kernels (K-contiguous, even K and row lengths).
+struct F64Choice {
+  int tile, split;
+};
+F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems);
+// the split-K factor re-chosen for a forced tile (gemm_split_refine)
+int gemm_f64_refined_split(const GemmDesc &d, int tile_id, int64_t ws_elems);
 int gemm_split_pick(int64_t M, int64_t N, int64_t K, int tile_id);
 int gemm_lowp_pick(int prec, int64_t M, int64_t N);
 void gemm_lowp_tile_shape(int prec, int tile_id, int *bm, int *bn);

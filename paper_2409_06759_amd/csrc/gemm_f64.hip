@@ -17,8 +17,8 @@
 //   registers) while the current one is multiplied.  Operands may be
 //   K-contiguous or M/N-contiguous; the LDS layout follows the global one so
 //   both the HBM reads and the LDS fragment reads stay unit-stride.
-// * The LDS-direct configuration (256x128x16) takes K-contiguous operands
-//   with global_load_lds_dwordx4 into three LDS stages (see its kernel).
+// * The LDS-direct configurations take K-contiguous operands with
+//   global_load_lds_dwordx4 into three LDS stages (see their kernel).
 // * Workgroup ids are remapped so that the M tiles sharing one N tile are
 //   dispatched to the same XCD (shared L2 for the B panel).
 // * A launch whose last round of resident workgroups would be at most half
@@ -57,9 +57,8 @@ struct Cfg {
 // One workgroup's share of a GEMM: logical tile L0 in [0, tiles * split).
 template <int BM, int BN, int BK, int WM, int WN, bool AKC, bool BKC>
 __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM, int64_t tilesN,
-                                              int64_t L0) {
+                                              int64_t L0, double *smem) {
   using C = Cfg<BM, BN, BK, WM, WN, AKC, BKC>;
-  __shared__ __attribute__((aligned(16))) double smem[2 * (C::A_ELEMS + C::B_ELEMS)];
   // buffer b of A at smem + b*A_ELEMS, of B at smem + 2*A_ELEMS + b*B_ELEMS
 
   const int64_t tiles = tilesM * tilesN;
@@ -80,25 +79,24 @@ __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM,
   B += kb * d.sbk;
 
   // Global -> register staging in 16-byte vectors (two doubles along the
-  // unit-stride dimension) when the strides and base allow it; otherwise the
-  // same vectors are assembled element by element.  Out-of-range elements are 0.
+  // unit-stride dimension; global loads need only 8-byte alignment), the last
+  // element of an odd row on its own.  Out-of-range elements are 0.
   constexpr int AR = AKC ? BM : BK, AC = AKC ? BK : BM, BR = BKC ? BN : BK, BC = BKC ? BK : BN;
   constexpr int ANV = AR * AC / 2, BNV = BR * BC / 2;
   constexpr int AVT = (ANV + C::NT - 1) / C::NT, BVT = (BNV + C::NT - 1) / C::NT;
   typedef double d2 __attribute__((ext_vector_type(2)));
+  typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
   d2 ra[AVT], rb[BVT];
-  const bool vec_a = ((AKC ? d.sam : d.sak) % 2 == 0) && ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
-  const bool vec_b = ((BKC ? d.sbn : d.sbk) % 2 == 0) && ((reinterpret_cast<uintptr_t>(B) & 15) == 0);
 
-  auto vload = [&](const double *base, int64_t rstride, int64_t r_lim, int64_t c_lim, int64_t r0, int64_t c0,
-                   bool vec_ok, int v, int ncolv) -> d2 {
+  auto vload = [&](const double *base, int64_t rstride, int64_t r_lim, int64_t c_lim, int64_t r0, int64_t c0, int v,
+                   int ncolv) -> d2 {
     const int rr = v / ncolv, cc = (v % ncolv) * 2;
     const int64_t gr = r0 + rr, gc = c0 + cc;
     const double *src = base + gr * rstride + gc;
-    if (vec_ok && gr < r_lim && gc + 2 <= c_lim) return *reinterpret_cast<const d2 *>(src);
+    if (gr < r_lim && gc + 2 <= c_lim) return *reinterpret_cast<const d2u *>(src);
     d2 t;
     t.x = (gr < r_lim && gc < c_lim) ? src[0] : 0.0;
-    t.y = (gr < r_lim && gc + 1 < c_lim) ? src[1] : 0.0;
+    t.y = 0.0;
     return t;
   };
   auto gload = [&](int64_t k0) {
@@ -106,13 +104,13 @@ __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM,
     for (int i = 0; i < AVT; ++i) {
       const int v = tid + i * C::NT;
       if (ANV % C::NT == 0 || v < ANV)
-        ra[i] = AKC ? vload(A, d.sam, M, K, m0, k0, vec_a, v, AC / 2) : vload(A, d.sak, K, M, k0, m0, vec_a, v, AC / 2);
+        ra[i] = AKC ? vload(A, d.sam, M, K, m0, k0, v, AC / 2) : vload(A, d.sak, K, M, k0, m0, v, AC / 2);
     }
 #pragma unroll
     for (int i = 0; i < BVT; ++i) {
       const int v = tid + i * C::NT;
       if (BNV % C::NT == 0 || v < BNV)
-        rb[i] = BKC ? vload(B, d.sbn, N, K, n0, k0, vec_b, v, BC / 2) : vload(B, d.sbk, K, N, k0, n0, vec_b, v, BC / 2);
+        rb[i] = BKC ? vload(B, d.sbn, N, K, n0, k0, v, BC / 2) : vload(B, d.sbk, K, N, k0, n0, v, BC / 2);
     }
   };
   auto sstore = [&](int buf) {
@@ -208,8 +206,10 @@ __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM,
 template <int BM, int BN, int BK, int WM, int WN, bool AKC, bool BKC, int TAG>
 __global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_kernel(GemmDesc d, int64_t tilesM,
                                                                   int64_t tilesN) {
+  using C = Cfg<BM, BN, BK, WM, WN, AKC, BKC>;
+  __shared__ __attribute__((aligned(16))) double smem[2 * (C::A_ELEMS + C::B_ELEMS)];
   const int64_t total = tilesM * tilesN * d.split;
-  gemm_f64_body<BM, BN, BK, WM, WN, AKC, BKC>(d, tilesM, tilesN, xcd_remap(blockIdx.x, total));
+  gemm_f64_body<BM, BN, BK, WM, WN, AKC, BKC>(d, tilesM, tilesN, xcd_remap(blockIdx.x, total), smem);
 }
 
 // Grouped launch: one workgroup range per system; system b owns logical
@@ -217,15 +217,18 @@ __global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_kernel(GemmDesc d, int
 template <int BM, int BN, int BK, int WM, int WN, bool AKC, bool BKC>
 __global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_grouped(const GemmGroupEntry *__restrict__ e,
                                                                    const int64_t *__restrict__ off, int n) {
+  using C = Cfg<BM, BN, BK, WM, WN, AKC, BKC>;
+  __shared__ __attribute__((aligned(16))) double smem[2 * (C::A_ELEMS + C::B_ELEMS)];
   const int b = group_find(off, n, blockIdx.x);
   const GemmGroupEntry &g = e[b];
-  gemm_f64_body<BM, BN, BK, WM, WN, AKC, BKC>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b]);
+  gemm_f64_body<BM, BN, BK, WM, WN, AKC, BKC>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b], smem);
 }
 
-// ---- 256x128x16 with LDS-direct loads ---------------------------------------
-// K a multiple of 16, both operands K-contiguous with 16-byte aligned rows
-// (the particle-particle ladder's layout); rows past M or N load the last
-// valid row instead, which only reaches outputs that are never stored.  Each lane's 16
+// ---- LDS-direct configurations (K chunk 16) ---------------------------------
+// Both operands K-contiguous with 16-byte aligned rows and an even K (the
+// particle-particle ladder's layout); rows past M or N load the last valid
+// row instead, which only reaches outputs that are never stored, and k pairs
+// past K load zeros from a zero pair in device memory.  Each lane's 16
 // bytes go straight from HBM/L2 into LDS (global_load_lds_dwordx4): no
 // staging registers, three LDS stages, two chunks of K in flight.  A 16-row
 // block of a stage is two halves of 64 slots of 16 bytes; slot L of half h
@@ -233,23 +236,35 @@ __global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_grouped(const GemmGrou
 // k values it feeds the f64 MFMA (k = 4q + s, as in the staged kernel) as
 // two 16-byte reads, each contiguous across the wave (no bank conflicts).  The
 // products and their order are those of the staged kernel of the same tile,
-// so results are bitwise the same.  Waits: "vmcnt <= 6" after the six loads
+// so results are bitwise the same.  Waits: "vmcnt <= LOADS" after the loads
 // of chunk kt+1 means chunk kt has landed (in-order completion), the barrier
 // behind it makes that so for every wave, and "lgkmcnt == 0" before it
 // means every wave has finished reading the stage the next loads overwrite.
-namespace dma64 {
-constexpr int BM = 256, BN = 128, BK = 16, WM = 4, WN = 2, NT = WM * WN * kWave;
-constexpr int FM = BM / WM / 16, FN = BN / WN / 16;
-constexpr int A_EL = BM * BK, B_EL = BN * BK, STAGE = A_EL + B_EL;  // doubles
-constexpr int NSTAGE = 3;
-constexpr int LOADS = (2 * (BM / 16) + 2 * (BN / 16)) / (WM * WN);  // per wave and chunk
-static_assert(LOADS == 6, "the explicit waits count six loads per chunk");
-}  // namespace dma64
+__device__ __attribute__((aligned(16))) const double kZeroPair[2] = {0.0, 0.0};
 
-__device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t tilesM, int64_t tilesN, int64_t L0) {
-  using namespace dma64;
-  __shared__ __attribute__((aligned(16))) double S[NSTAGE * STAGE];
+template <int BM, int BN, int WM, int WN, int NST>
+struct Dma64 {
+  static constexpr int BK = 16, NT = WM * WN * kWave;
+  static constexpr int FM = BM / WM / 16, FN = BN / WN / 16;
+  static constexpr int A_EL = BM * BK, STAGE = (BM + BN) * BK;  // doubles
+  static constexpr int NSTAGE = NST, ELEMS = NSTAGE * STAGE;
+  static constexpr int LOADS = 2 * (BM / 16 + BN / 16) / (WM * WN);  // 1 KiB loads per wave and chunk
+  static_assert(2 * (BM / 16 + BN / 16) % (WM * WN) == 0, "whole loads per wave");
+  static_assert(BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "tile/wave mismatch");
+};
 
+// the shapes and layouts the LDS-direct kernels handle
+__host__ __device__ __forceinline__ bool f64_dma_ok(const GemmDesc &d) {
+  return d.sak == 1 && d.sbk == 1 && d.K > 0 && d.K % 2 == 0 && d.sam % 2 == 0 && d.sbn % 2 == 0 &&
+         (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 && (reinterpret_cast<uintptr_t>(d.B) & 15) == 0;
+}
+
+template <int BM, int BN, int WM, int WN, int NST>
+__device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t tilesM, int64_t tilesN, int64_t L0,
+                                                  double *S) {
+  using C = Dma64<BM, BN, WM, WN, NST>;
+  constexpr int BK = C::BK, FM = C::FM, FN = C::FN, A_EL = C::A_EL, STAGE = C::STAGE, NSTAGE = C::NSTAGE,
+                LOADS = C::LOADS;
   const int64_t tiles = tilesM * tilesN;
   const int64_t ks = L0 / tiles, L = L0 % tiles;
   const int64_t m0 = (L % tilesM) * BM, n0 = (L / tilesM) * BN;
@@ -260,29 +275,35 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
   const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
-  const int64_t nk = K / BK;
+  const int64_t nk = (K + BK - 1) / BK;
 
-  // this wave's loads: A blocks 2w and 2w+1, B block w, each as two halves;
-  // lane l of half h loads row (l & 15), k = 4 (l >> 4) + 2h + {0, 1}
+  // this wave's loads: LOADS of the stage's half blocks (16 rows x 8 k),
+  // numbered with the A blocks first; lane l of half h loads row (l & 15),
+  // k = 4 (l >> 4) + 2h + {0, 1}
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(S));
   const double *src[LOADS];
   uint32_t dst[LOADS];
+  int kof[LOADS];
   const double *Ag = static_cast<const double *>(d.A) + kb;
   const double *Bg = static_cast<const double *>(d.B) + kb;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int blk = 2 * wave + (u >> 1), h = u & 1;
-    src[u] = Ag + std::min<int64_t>(m0 + blk * 16 + r, M - 1) * d.sam + 4 * q + 2 * h;
+  for (int u = 0; u < LOADS; ++u) {
+    const int x = wave * LOADS + u, blk = x >> 1, h = x & 1;
+    kof[u] = 4 * q + 2 * h;
+    src[u] = (blk < BM / 16 ? Ag + std::min<int64_t>(m0 + blk * 16 + r, M - 1) * d.sam
+                            : Bg + std::min<int64_t>(n0 + (blk - BM / 16) * 16 + r, N - 1) * d.sbn) +
+             kof[u];
     dst[u] = __builtin_amdgcn_readfirstlane(lds0 + 8u * uint32_t(blk * 256 + h * 128));
   }
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    src[4 + u] = Bg + std::min<int64_t>(n0 + wave * 16 + r, N - 1) * d.sbn + 4 * q + 2 * u;
-    dst[4 + u] = __builtin_amdgcn_readfirstlane(lds0 + 8u * uint32_t(A_EL + wave * 256 + u * 128));
-  }
   auto issue = [&](int stage, int64_t k0) {
+    if (k0 + BK <= K) {
 #pragma unroll
-    for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
+      for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
+    } else {  // the last, partial chunk: zeros past K
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u)
+        lds_load16(k0 + kof[u] < K ? src[u] + k0 : kZeroPair, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
+    }
   };
 
   d4 acc[FM][FN];
@@ -291,13 +312,14 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
 #pragma unroll
     for (int j = 0; j < FN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 
+  static_assert(NST == 2 || NST == 3, "the explicit waits are written for one or two chunks in flight");
   if (nk > 0) issue(0, 0);
-  if (nk > 1) issue(1, BK);
-  int cur = 0, nxt = 2;
+  if (NST == 3 && nk > 1) issue(1, BK);
+  int cur = 0, nxt = NST - 1;
   for (int64_t kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + 2 < nk) issue(nxt, (kt + 2) * BK);
+    if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
     const double *St = S + cur * STAGE;
     // the k pair of steps 0-1 of every fragment is read first; the pair of
     // steps 2-3 is read behind the MFMAs of step 0, so it overlaps them (at
@@ -361,16 +383,26 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
     }
 }
 
-template <int TAG>
-__global__ __launch_bounds__(dma64::NT) void gemm_f64_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
-  gemm_f64_dma_body(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split));
+template <int BM, int BN, int WM, int WN, int NST, int TAG>
+__global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
+  __shared__ __attribute__((aligned(16))) double S[Dma64<BM, BN, WM, WN, NST>::ELEMS];
+  gemm_f64_dma_body<BM, BN, WM, WN, NST>(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split), S);
 }
 
-// the shapes and layouts the LDS-direct kernel handles
-bool f64_dma_ok(const GemmDesc &d) {
-  return d.sak == 1 && d.sbk == 1 && d.K % dma64::BK == 0 &&
-         d.sam % 2 == 0 && d.sbn % 2 == 0 && (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 &&
-         (reinterpret_cast<uintptr_t>(d.B) & 15) == 0;
+// Grouped launch: the systems whose operands the LDS-direct loads cannot
+// take (odd K or row length) run the staged body of the same tile.
+template <int BM, int BN, int WM, int WN, int NST>
+__global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_dma_grouped(const GemmGroupEntry *__restrict__ e,
+                                                                      const int64_t *__restrict__ off, int n) {
+  using St = Cfg<BM, BN, 16, WM, WN, true, true>;
+  constexpr int SN = 2 * (St::A_ELEMS + St::B_ELEMS), DN = Dma64<BM, BN, WM, WN, NST>::ELEMS;
+  __shared__ __attribute__((aligned(16))) double S[SN > DN ? SN : DN];
+  const int b = group_find(off, n, blockIdx.x);
+  const GemmGroupEntry &g = e[b];
+  if (f64_dma_ok(g.d))
+    gemm_f64_dma_body<BM, BN, WM, WN, NST>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b], S);
+  else
+    gemm_f64_body<BM, BN, 16, WM, WN, true, true>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b], S);
 }
 
 struct TileInfo {
@@ -423,21 +455,41 @@ void launch_cfg(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
      &occupancy_cfg<BM, BN, BK, WM, WN, true, false>, &occupancy_cfg<BM, BN, BK, WM, WN, true, true>} \
   }
 
-template <int TAG>
+template <int BM, int BN, int WM, int WN, int NST, int TAG>
 void launch_f64_dma(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
   if (f64_dma_ok(d))
-    hipLaunchKernelGGL((gemm_f64_dma_kernel<TAG>), dim3(tm * tn * d.split), dim3(dma64::NT), 0, s, d, tm, tn);
+    hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, NST, TAG>), dim3(tm * tn * d.split), dim3(WM * WN * kWave), 0,
+                       s, d, tm, tn);
   else
-    launch_cfg<256, 128, 16, 4, 2, true, true, TAG>(d, tm, tn, s);
+    launch_cfg<BM, BN, 16, WM, WN, true, true, TAG>(d, tm, tn, s);
 }
+template <int BM, int BN, int WM, int WN, int NST>
 int occ_f64_dma() {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f64_dma_kernel<0>, dma64::NT, 0) != hipSuccess) {
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f64_dma_kernel<BM, BN, WM, WN, NST, 0>, WM * WN * kWave, 0) !=
+      hipSuccess) {
     (void)hipGetLastError();
     return 0;
   }
   return nb;
 }
+template <int BM, int BN, int WM, int WN, int NST>
+void launch_grp_dma(const GemmGroupEntry *e, const int64_t *off, int n, int64_t blocks, hipStream_t s) {
+  hipLaunchKernelGGL((gemm_f64_dma_grouped<BM, BN, WM, WN, NST>), dim3(blocks), dim3(WM * WN * kWave), 0, s, e, off, n);
+}
+
+// LDS-direct where the operands allow, else the staged kernel of the tile
+#define CC_TILE_DMA(BM, BN, WM, WN, NST, NAME)                                                                              \
+  TileInfo {                                                                                                     \
+    #BM "x" #BN "x16_w" #WM "x" #WN NAME, BM, BN, 16, WM *WN * kWave, {                                        \
+      &launch_cfg<BM, BN, 16, WM, WN, false, false>, &launch_cfg<BM, BN, 16, WM, WN, false, true>,               \
+          &launch_cfg<BM, BN, 16, WM, WN, true, false>, &launch_f64_dma<BM, BN, WM, WN, NST, 0>                       \
+    }, &launch_f64_dma<BM, BN, WM, WN, NST, 1>, &launch_f64_dma<BM, BN, WM, WN, NST, 2>,                                   \
+    {&launch_grp<BM, BN, 16, WM, WN, false, false>, &launch_grp<BM, BN, 16, WM, WN, false, true>,                \
+     &launch_grp<BM, BN, 16, WM, WN, true, false>, &launch_grp_dma<BM, BN, WM, WN, NST>},                             \
+    {&occupancy_cfg<BM, BN, 16, WM, WN, false, false>, &occupancy_cfg<BM, BN, 16, WM, WN, false, true>,          \
+     &occupancy_cfg<BM, BN, 16, WM, WN, true, false>, &occ_f64_dma<BM, BN, WM, WN, NST>}                              \
+  }
 
 const TileInfo kTiles[] = {
     CC_TILE(128, 128, 16, 2, 2),
@@ -456,20 +508,9 @@ const TileInfo kTiles[] = {
     CC_TILE(64, 128, 16, 2, 4),
     CC_TILE(128, 128, 16, 4, 4),
     CC_TILE(256, 64, 16, 8, 2),
-    // 256x128x16 with LDS-direct loads where the shape allows, else staged
-    TileInfo{"256x128x16_w4x2_lds",
-             256,
-             128,
-             16,
-             4 * 2 * kWave,
-             {&launch_cfg<256, 128, 16, 4, 2, false, false>, &launch_cfg<256, 128, 16, 4, 2, false, true>,
-              &launch_cfg<256, 128, 16, 4, 2, true, false>, &launch_f64_dma<0>},
-             &launch_f64_dma<1>,
-             &launch_f64_dma<2>,
-             {&launch_grp<256, 128, 16, 4, 2, false, false>, &launch_grp<256, 128, 16, 4, 2, false, true>,
-              &launch_grp<256, 128, 16, 4, 2, true, false>, &launch_grp<256, 128, 16, 4, 2, true, true>},
-             {&occupancy_cfg<256, 128, 16, 4, 2, false, false>, &occupancy_cfg<256, 128, 16, 4, 2, false, true>,
-              &occupancy_cfg<256, 128, 16, 4, 2, true, false>, &occ_f64_dma}},
+    CC_TILE_DMA(256, 128, 4, 2, 3, "_lds"),
+    CC_TILE_DMA(64, 128, 2, 4, 2, "_lds2"),
+    CC_TILE_DMA(32, 32, 2, 2, 3, "_lds"),
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -577,28 +618,79 @@ int64_t gemm_tail_ws_bound(int64_t M, int64_t N, int64_t K) {
 
 int64_t gemm_f64_tail_ws(const GemmDesc &d, int tile_id) {
   if (d.M <= 0 || d.N <= 0 || d.K <= 0) return 0;
-  if (tile_id < 0 || tile_id >= kNumTiles) tile_id = gemm_f64_pick(d.M, d.N, d.K, d.sak == 1, d.sbk == 1);
+  if (tile_id < 0 || tile_id >= kNumTiles) tile_id = gemm_f64_choose(d.M, d.N, d.K, f64_dma_ok(d), 0).tile;
   return f64_cut(d, tile_id).ws_elems;
 }
 
 int gemm_f64_num_tiles() { return kNumTiles; }
 const char *gemm_f64_tile_name(int id) { return (id >= 0 && id < kNumTiles) ? kTiles[id].name : "?"; }
 
-// Static choice: the tile that minimises (rounds of resident workgroups) x
-// (tile work), counting padding; the autotuner refines this by timing.
-int gemm_f64_pick(int64_t M, int64_t N, int64_t K, bool, bool) {
-  (void)K;
-  const double cus = 256.0;
-  int best = 0;
-  double best_cost = 1e300;
-  for (int t = 0; t < kNumTiles; ++t) {
-    const TileInfo &ti = kTiles[t];
-    if (ti.BK != 16) continue;
-    const double tiles = double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN);
-    const double rounds = std::ceil(tiles / cus);
-    // a tile's time ~ its MFMA work; small tiles pay a fixed per-tile overhead
-    const double cost = rounds * (double(ti.BM) * ti.BN + 4096.0);
-    if (cost < best_cost) { best_cost = cost; best = t; }
+// ---- static choice of tile and split-K factor --------------------------------
+// Time of one launch (and its split-K reduction), in microseconds, from a
+// model whose constants were fitted to 15,000 timings on the MI355X: every
+// configuration and a grid of split-K factors on the 404 GEMM shapes of the
+// CCSD, packed CCSD and CCSDT lists at o = 4..32, v = 20..160.  A compute unit
+// runs min(resident, w) of its w workgroups at a time; a K chunk of those takes
+// their MFMA cycles over the tile's efficiency, or the latency of one chunk
+// when there are too few of them to hide it.  That time competes with the
+// operands' and outputs' HBM traffic and with the tiles' operand traffic from
+// the L2s; the shorter of the two is partly hidden.  Over those shapes the
+// choice is 2.5% (geometric mean) slower than the fastest configuration; the
+// rule it replaced (rounds of 256 workgroups x tile area, staged tiles first)
+// was 37% slower, on launches over 50 us: ladder 1024 x 25600 x 25600
+// 28.3 -> 20.0 ms, 2000^3 394 -> 295 us, 160000 x 400 x 400 1.97 -> 1.28 ms,
+// 10 x 6400000 x 10 0.61 -> 0.46 ms.  The autotuner refines it by timing.
+struct F64Model {
+  int tile;       // kTiles index
+  int resident;   // workgroups per CU
+  double eff[2];  // share of the MFMA rate: M/N-contiguous or odd operands; LDS-direct ones
+};
+constexpr F64Model kF64Models[] = {
+    {3, 6, {0.78, 0.32}},                       // 32x32 staged: launches bound by memory
+    {11, 2, {0.74, 0.0}},                       // 128x128 staged
+    {16, 1, {0.0, 0.92}},                       // 256x128 LDS-direct
+    {kNumTiles - 2, 3, {0.74, 0.92}},           // 64x128 LDS-direct, two stages
+    {kNumTiles - 1, 6, {0.0, 0.57}},            // 32x32 LDS-direct (staged: the first line)
+};
+// per operand form: cycles of one chunk alone, cycles per workgroup set
+// (fixed; per 1,024 outputs), HBM TB/s, microseconds and TB/s of the split-K
+// partial sums, L2 TB/s, share of the shorter time that is not hidden
+constexpr double kF64Const[2][8] = {{1044, 159, 454, 5.24, 2.9, 7.6, 10.0, 0.54},
+                                    {702, 359, 417, 5.9, 2.3, 3.4, 26.5, 0.14}};
+
+double f64_model_us(const F64Model &m, int form, int64_t M, int64_t N, int64_t K, int64_t split) {
+  const TileInfo &ti = kTiles[m.tile];
+  const double *c = kF64Const[form];
+  const int64_t n = (((K + split - 1) / split) + 15) / 16;  // chunks per workgroup
+  const double area = double(ti.BM) * ti.BN;
+  const double wgs = double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN) * double(split);
+  const double w = std::ceil(wgs / 256.0), conc = std::min(w, double(m.resident));
+  const double chunk = std::max(conc * area / 4.0 / m.eff[form], c[0]);  // 128 flop per cycle and CU
+  const double mfma = (w / conc) * (double(n) * chunk + c[1] + c[2] * area / 1024.0 * conc) / 2400.0;
+  const double l2 = wgs * double(ti.BM + ti.BN) * double(n) * 128.0 / c[6] * 1e-6;
+  const double mem = (double(M) * K + double(N) * K + (split == 1 ? 2.0 * double(M) * N : 0.0)) * 8.0 / c[3] * 1e-6;
+  const double work = std::max(mfma, l2);
+  const double red = split > 1 ? c[4] + 16.0 * double(split) * double(M) * N / c[5] * 1e-6 : 0.0;
+  return 3.0 + std::max(work, mem) + c[7] * std::min(work, mem) + red;
+}
+
+F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems) {
+  static constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
+  const int form = lds_direct ? 1 : 0;
+  F64Choice best{3, 1};
+  double best_us = 1e300;
+  for (const F64Model &m : kF64Models) {
+    if (m.eff[form] <= 0.0) continue;
+    const TileInfo &ti = kTiles[m.tile];
+    const int64_t tiles = ((M + ti.BM - 1) / ti.BM) * ((N + ti.BN - 1) / ti.BN);
+    for (int s : kSplits) {
+      if (s > 1 && (int64_t(s) * 64 > K || tiles * s > 4096 || int64_t(s) * M * N > ws_elems)) break;
+      const double us = f64_model_us(m, form, M, N, K, s);
+      if (us < best_us) {
+        best_us = us;
+        best = F64Choice{m.tile, s};
+      }
+    }
   }
   return best;
 }
@@ -629,7 +721,14 @@ void gemm_f64_tile_shape(int tile_id, int *bm, int *bn) {
   *bn = kTiles[tile_id].BN;
 }
 
-void gemm_f64(const GemmDesc &d, hipStream_t s, int tile_id) {
+int gemm_f64_refined_split(const GemmDesc &d, int tile_id, int64_t ws_elems) {
+  const TileInfo &ti = kTiles[tile_id];
+  return gemm_split_refine(d.M, d.N, d.K, ti.BM, ti.BN, ti.BK,
+                           tile_slots(tile_id, (d.sak == 1 ? 2 : 0) + (d.sbk == 1 ? 1 : 0)), d.split, ws_elems);
+}
+
+void gemm_f64(const GemmDesc &d0, hipStream_t s, int tile_id) {
+  GemmDesc d = d0;
   if (d.M <= 0 || d.N <= 0) return;
   const bool akc = (d.sak == 1), bkc = (d.sbk == 1);
   CC_REQUIRE(akc || d.sam == 1, -1, "gemm: A needs a unit stride in m or k");
@@ -646,10 +745,20 @@ void gemm_f64(const GemmDesc &d, hipStream_t s, int tile_id) {
     permute_f64(p, d.C, d.C, s);
     return;
   }
-  if (tile_id < 0 || tile_id >= kNumTiles) tile_id = gemm_f64_pick(d.M, d.N, d.K, akc, bkc);
+  CC_REQUIRE(d.split >= 1, -1, "gemm: split must be >= 1");
+  if (tile_id < 0 || tile_id >= kNumTiles) {
+    // the library's choice, of the split-K factor too where the caller
+    // allowed one (within the workspace it gave)
+    const F64Choice ch = gemm_f64_choose(
+        d.M, d.N, d.K, f64_dma_ok(d),
+        d.split > 1 && d.ws ? (d.ws_elems > 0 ? d.ws_elems : d.split * d.M * d.N) : 0);
+    tile_id = ch.tile;
+    d.split = ch.split;
+  } else if (d.ws && d.split > 1 && d.ws_elems > 0 && d.refine) {
+    d.split = gemm_f64_refined_split(d, tile_id, d.ws_elems);
+  }
   const TileInfo &ti = kTiles[tile_id];
   const int64_t tm = (d.M + ti.BM - 1) / ti.BM, tn = (d.N + ti.BN - 1) / ti.BN;
-  CC_REQUIRE(d.split >= 1, -1, "gemm: split must be >= 1");
   CC_REQUIRE(d.split == 1 || d.ws != nullptr, -1, "gemm: split-K needs a workspace");
   CC_REQUIRE(d.split == 1 || d.ws_elems == 0 || d.ws_elems >= d.split * d.M * d.N, -1,
              "gemm: split-K workspace too small");
@@ -668,13 +777,6 @@ void gemm_f64(const GemmDesc &d, hipStream_t s, int tile_id) {
       gemm_run_cut(d, tc, sizeof(double), sizeof(double), one);
       return;
     }
-  }
-  if (d.ws && d.split > 1 && d.ws_elems > 0) {
-    GemmDesc g = d;
-    g.split = gemm_split_refine(d.M, d.N, d.K, ti.BM, ti.BN, ti.BK,
-                                tile_slots(tile_id, (akc ? 2 : 0) + (bkc ? 1 : 0)), d.split, d.ws_elems);
-    one(g);
-    return;
   }
   one(d);
 }

@@ -131,7 +131,8 @@ struct Planner {
   // Split-K partial sums, or room for the K-split tail of a launch whose last
   // round of workgroups would be mostly empty (real GEMMs only).
   void reserve_ws(Step &g, int64_t M, int64_t N, int64_t K) {
-    const int64_t split = g.gemm.split > 1 ? int64_t(g.gemm.split) * M * N : 0;
+    const int64_t smax = p->cplx ? g.gemm.split : std::max(g.gemm.split, g.split64);
+    const int64_t split = smax > 1 ? smax * M * N : 0;
     // complex: room for the tail of the realified M x 2N x 2K reduced-precision
     // GEMM, in complex elements
     const int64_t tail = p->cplx ? (gemm_tail_ws_bound(M, 2 * N, 2 * K) + 1) / 2 : gemm_tail_ws_bound(M, N, K);
@@ -143,6 +144,18 @@ struct Planner {
       splitws_elems = std::max<int64_t>(splitws_elems, std::max(split, tail));
       g.b2 = splitws;
     }
+  }
+
+  // Split-K factors, and for real systems the FP64 tile with its own factor
+  // (partial sums of at most 2^24 elements, as gemm_split_pick's).
+  void choose_split(Step &g) {
+    const GemmDesc &d = g.gemm;
+    g.gemm.split = gemm_split_pick(d.M, d.N, d.K, -1);
+    if (p->cplx) return;
+    const bool direct = d.sak == 1 && d.sbk == 1 && d.K % 2 == 0 && d.sam % 2 == 0 && d.sbn % 2 == 0;
+    const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, direct, int64_t(1) << 24);
+    g.tile = ch.tile;
+    g.split64 = ch.split;
   }
 
   int slot(const std::string &name) {
@@ -373,9 +386,8 @@ struct Planner {
     g.flops = (p->cplx ? 8.0 : 2.0) * double(M) * double(N) * double(Kd);
     g.tag = op.tag;
     g.gemm.ladder = std::string(op.tag) == "ladder" ? 1 : 0;
-    g.gemm.split = gemm_split_pick(M, N, Kd, -1);
+    choose_split(g);
     reserve_ws(g, M, N, Kd);
-    g.tile = p->cplx ? -1 : gemm_f64_pick(M, N, Kd, xkc, ykc);
     if (best.cm) {
       g.c = c;
       g.gemm.alpha = op.alpha;
@@ -495,9 +507,8 @@ struct Planner {
     g.gemm.ladder = std::string(tag) == "ladder" ? 1 : 0;
     g.flops = (p->cplx ? 8.0 : 2.0) * double(M) * double(N) * double(Kalg);
     g.tag = tag;
-    g.gemm.split = gemm_split_pick(M, N, K, -1);
+    choose_split(g);
     reserve_ws(g, M, N, K);
-    g.tile = p->cplx ? -1 : gemm_f64_pick(M, N, K, akc, bkc);
     p->flops_per_iter += g.flops;
     if (g.gemm.ladder) p->ladder_flops += g.flops;
     return g;
@@ -843,6 +854,8 @@ void use_blocked(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s, bool co
   d.lp_in = 2;
 }
 
+void run_f64(const GemmDesc &d, const Step &st, hipStream_t s) { gemm_f64(gemm_f64_desc(st, d), s, st.tile); }
+
 void run_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
   if (p->cplx && (p->cur_prec == PREC_F64 || !st.lowp_ok)) gemm_c128(d, s, st.tile_z);
   else if (p->cplx) {
@@ -850,7 +863,7 @@ void run_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
     if (blocked_for(p, st, tile)) use_blocked(p, d, st, s, true);
     else use_shadows_c(p, d, st, s, true);
     gemm_lowp(d, p->cur_prec, s, tile);
-  } else if (p->cur_prec == PREC_F64 || !st.lowp_ok) gemm_f64(d, s, st.tile);
+  } else if (p->cur_prec == PREC_F64 || !st.lowp_ok) run_f64(d, st, s);
   else {
     const int tile = st.tile_lp[p->cur_prec];
     if (blocked_for(p, st, tile)) use_blocked(p, d, st, s, true);
@@ -873,7 +886,7 @@ void run_delta_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
   // products of two varying operands are corrected in split bf16 only: two
   // FP32 products take as long as the FP64 one
   if (r.var == 2 && p->delta_prec != PREC_BF16X3) {
-    gemm_f64(d, s, st.tile);
+    run_f64(d, st, s);
     return;
   }
   CC_REQUIRE(r.ref_op && r.ref_out && r.dshadow, CC_EINTERNAL, "reference buffers not prepared");
@@ -895,7 +908,7 @@ void run_delta_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
       g.C = r.ref_out;
       g.ldc = d.N;
       g.beta = 0.0;
-      gemm_f64(g, s, st.tile);
+      run_f64(g, st, s);
       add_product(C, d.ldc, d.beta, r.ref_out, d.M, d.N, s);
       return;
     }
@@ -923,7 +936,7 @@ void run_delta_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
     g.ldc = d.N;
     g.beta = 0.0;
     if (p->cplx) gemm_c128(g, s, st.tile_z);
-    else gemm_f64(g, s, st.tile);
+    else run_f64(g, st, s);
     add_product(C, w * d.ldc, d.beta, r.ref_out, d.M, w * d.N, s);
     return;
   }
@@ -1079,6 +1092,13 @@ void plan_prepare(cc_plan *p) {
         CC_HIP_CHECK(hipMalloc(&d.dblk, size_t(blocked_plane(d.n_op / g.K, g.K)) * 4));
     }
   }
+}
+
+GemmDesc gemm_f64_desc(const Step &st, const GemmDesc &d) {
+  GemmDesc g = d;
+  g.split = st.split64;
+  g.refine = 0;
+  return g;
 }
 
 TauEntry tau_entry(cc_plan *p) {
@@ -1493,7 +1513,17 @@ void plan_autotune(cc_plan *p, int reps) {
       auto it = cache.find(key);
       // cached value: the tile, plus kBlockedChoice when it runs on the blocked copies
       constexpr int kBlockedChoice = 1000;
+      // an FP64 tile other than the library's choice runs with the factor
+      // refined from the general one
+      auto f64_split = [&](int t) {
+        if (t == st->tile) return st->split64;
+        GemmDesc g = st->gemm;
+        const int64_t cap = st->b2 >= 0 ? p->slots[st->b2].elems : 0;
+        if (g.split > 1 && cap > 0) g.split = gemm_f64_refined_split(g, t, cap);
+        return g.split;
+      };
       if (it != cache.end()) {
+        if (!cz && prec == PREC_F64) st->split64 = f64_split(it->second % kBlockedChoice);
         slot = it->second % kBlockedChoice;
         if (blk) st->blk_use = it->second >= kBlockedChoice ? 1 : 0;
         continue;
@@ -1512,8 +1542,12 @@ void plan_autotune(cc_plan *p, int reps) {
       float best_ms = 1e30f;
       auto launch = [&](int t, int b) {
         if (cz) gemm_c128(d, s, t);
-        else if (prec == PREC_F64) gemm_f64(d, s, t);
-        else gemm_lowp(b ? db : d, prec, s, t);
+        else if (prec == PREC_F64) {
+          GemmDesc g = d;
+          g.split = f64_split(t);
+          g.refine = 0;
+          gemm_f64(g, s, t);
+        } else gemm_lowp(b ? db : d, prec, s, t);
       };
       // every configuration on the row-major copies, and the LDS-direct
       // ones also on the blocked copies
@@ -1532,6 +1566,7 @@ void plan_autotune(cc_plan *p, int reps) {
             best_blk = b;
           }
         }
+      if (!cz && prec == PREC_F64) st->split64 = f64_split(best);
       slot = best;
       if (blk) st->blk_use = best_blk;
       const int value = best + (best_blk ? kBlockedChoice : 0);
@@ -1605,7 +1640,7 @@ std::string plan_describe(const cc_plan *p) {
              << " M=" << st.gemm.M << " N=" << st.gemm.N << " K=" << st.gemm.K << " sam=" << st.gemm.sam
              << " sak=" << st.gemm.sak << " sbn=" << st.gemm.sbn << " sbk=" << st.gemm.sbk
              << " ldc=" << st.gemm.ldc << " alpha=" << st.gemm.alpha << " beta=" << st.gemm.beta
-             << " split=" << st.gemm.split
+             << " split=" << (p->cplx || (p->cur_prec != PREC_F64 && st.lowp_ok) ? st.gemm.split : st.split64)
              << " tile=" << (st.tile >= 0 ? gemm_f64_tile_name(st.tile) : "auto") << "\n";
           break;
         case Step::OUTER:

@@ -65,6 +65,7 @@ struct Step {
   GemmDesc gemm{};
   OuterArgs outer{};
   int tile = -1;        // FP64 tile
+  int split64 = 1;      // its split-K factor, chosen with it (gemm.split: the reduced precisions')
   int tile_lp[3] = {-1, -1, -1};  // per reduced precision (index = cc_prec)
   int tile_z = -1;      // complex128 tile
   int delta = -1;       // index into cc_plan::deltas (GEMM linear in the amplitudes)
@@ -195,6 +196,7 @@ void plan_run_energy(cc_plan *p);    // tau + energy only
 std::string plan_describe(const cc_plan *p);
 void plan_autotune(cc_plan *p, int reps);
 std::string plan_profile_table(const cc_plan *p);
+GemmDesc gemm_f64_desc(const Step &st, const GemmDesc &d);  // d with the step's FP64 split-K factor
 TauEntry tau_entry(cc_plan *p);
 T3Entry t3_entry(cc_plan *p);
 AsmEntry asm_entry(cc_plan *p);
