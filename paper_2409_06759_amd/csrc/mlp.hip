@@ -9,6 +9,7 @@
 // three dense layers are MFMA GEMMs (FP64, or FP32 MFMA with FP32
 // accumulation); the elementwise parts below are FP64.
 #include <cmath>
+#include <cstring>
 #include <string>
 #include <vector>
 
@@ -200,11 +201,16 @@ __global__ __launch_bounds__(256) void fill_kernel(double *p, double v, int64_t 
   for (int64_t e = blockIdx.x * int64_t(256) + threadIdx.x; e < n; e += int64_t(gridDim.x) * 256) p[e] = v;
 }
 
-// loss = sum of partials / c, written to out[idx] (fixed order)
-__global__ void loss_sum_kernel(const double *lpart, int nb, int64_t c, double *out, int64_t idx) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
+// loss = sum of the nb <= 4096 partials / c, in order, written to out[idx]
+// (staged in LDS first: one thread adding from device memory took 15 us)
+__global__ __launch_bounds__(256) void loss_sum_kernel(const double *__restrict__ lpart, int nb, int64_t c,
+                                                       double *__restrict__ out, int64_t idx) {
+  __shared__ double sh[4096];
+  for (int k = threadIdx.x; k < nb; k += 256) sh[k] = lpart[k];
+  __syncthreads();
+  if (threadIdx.x == 0) {
     double s = 0.0;
-    for (int k = 0; k < nb; ++k) s += lpart[k];
+    for (int k = 0; k < nb; ++k) s += sh[k];
     out[idx] = s / double(c);
   }
 }
@@ -355,6 +361,312 @@ void forward_fused(const double *P, const double *z, int64_t n, double *f, hipSt
   CC_HIP_CHECK(hipGetLastError());
 }
 
+// ---- fused FP32 training passes ---------------------------------------------
+// One minibatch of c samples is R = 2c rows (the + branch, then the - branch).
+// The dense layers take FP32 operands on v_mfma_f32_16x16x4_f32 with FP32
+// sums, bias, ReLU and the output layer's gradient in FP64 from those sums:
+// every product, its place in its sum and every rounding is that of the
+// layer-by-layer GEMMs (dense() below), so the results are theirs bit for bit.
+// What is gone are the FP64 activations in device memory, written and read
+// once per layer and elementwise pass (13 passes of 134 MB per minibatch of
+// 65536, 970 us): the forward pass writes the second hidden layer once, in FP32
+// and with its ReLU mask in the sign of zero, and the backward pass forms
+// everything else from it and z in registers and LDS (both bound by MFMA).
+// Minibatch of 65536: 970 -> 211 us (forward 70, backward 113: 61 and 76 TFLOP/s
+// of the work that has to be done, the FP32 MFMA peak being 157).
+//   MFMA 16x16x4 operands: lane l = 16 q + r supplies A[row r][k q] and
+//   B[k q][col r] and holds D[4 q + t][r], t = 0..3 ("D form").  Step s of a
+//   16-long chunk of k uses k = 4 q + s.  So a D-form block of 16 rows is,
+//   value for value, the operand of a sum over those rows.
+// Eight waves; wave w owns hidden units 16 w .. 16 w + 15.  Rows go by in
+// blocks of 64.
+constexpr int TW = 8, TROWS = 64;
+constexpr int RM_LD = HID + 4;    // row-major LDS rows: 16-byte reads spread over the banks
+constexpr int TR_LD = TROWS + 4;  // the same for unit-major rows
+
+__device__ __forceinline__ int64_t mb_source(const int64_t *order, int64_t r0, int64_t c, int64_t row) {
+  const int64_t u = r0 + (row < c ? row : row - c);
+  return order ? order[u] : u;
+}
+
+// (1, z0, z1, z2) of a row in FP32; zeros past the last row
+__device__ __forceinline__ f4v mb_row(const double *z, const int64_t *order, int64_t r0, int64_t c, int64_t row) {
+  if (row >= 2 * c) return f4v{0.f, 0.f, 0.f, 0.f};
+  const double *p = z + 3 * mb_source(order, r0, c, row);
+  const float z0 = float(p[0]);
+  return f4v{1.f, row < c ? z0 : -z0, float(p[1]), float(p[2])};
+}
+
+// FP64 bias and ReLU of an FP32 sum, rounded to FP32; -0 where the unit is off
+__device__ __forceinline__ float bias_relu_f32(float acc, double bias) {
+  const double x = double(acc) + bias;
+  return x > 0.0 ? float(x) : -0.f;
+}
+__device__ __forceinline__ bool unit_on(float h) { return __float_as_uint(h) != 0x80000000u; }
+
+// H1 of this wave's 16 units for the rows zl holds, D form per 16-row block
+__device__ __forceinline__ void layer1(const f4v *zl, const float (&w1)[3], double b1, int q, int r, f4v (&h)[4]) {
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    const f4v zr = zl[16 * b + r];
+    f4v acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(q == 0 ? zr[1 + s] : 0.f, q == 0 ? w1[s] : 0.f, acc, 0, 0, 0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) h[b][t] = bias_relu_f32(acc[t], b1);
+  }
+}
+
+__global__ __launch_bounds__(TW * 64, 4) void mlp_train_forward_kernel(const double *__restrict__ P,
+                                                                    const double *__restrict__ z,
+                                                                    const int64_t *__restrict__ order, int64_t r0,
+                                                                    int64_t c, float *__restrict__ H2f,
+                                                                    double *__restrict__ g) {
+  __shared__ __attribute__((aligned(16))) float sH1[TROWS * RM_LD], sH2[TROWS * RM_LD];
+  __shared__ f4v zl[TROWS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, r = lane & 15;
+  const int64_t R = 2 * c;
+  const int u = 16 * w + r;  // this lane's unit in D form
+  float w1[3];
+#pragma unroll
+  for (int s = 0; s < 3; ++s) w1[s] = float(P[OFF_W1 + 3 * u + s]);
+  const double b1 = P[OFF_B1 + u], b2 = P[OFF_B2 + u];
+  f4v w2[8], w3[8];  // B operands: W2[unit][16 kc + 4 q + s], W3 in column 0
+#pragma unroll
+  for (int kc = 0; kc < 8; ++kc)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      w2[kc][s] = float(P[OFF_W2 + u * HID + 16 * kc + 4 * q + s]);
+      w3[kc][s] = r == 0 ? float(P[OFF_W3 + 16 * kc + 4 * q + s]) : 0.f;
+    }
+  for (int64_t row0 = int64_t(blockIdx.x) * TROWS; row0 < R; row0 += int64_t(gridDim.x) * TROWS) {
+    if (w == 0) zl[lane] = mb_row(z, order, r0, c, row0 + lane);
+    __syncthreads();
+    f4v h[4];
+    layer1(zl, w1, b1, q, r, h);
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) sH1[(16 * b + 4 * q + t) * RM_LD + u] = h[b][t];
+    __syncthreads();
+    f4v acc[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[b] = f4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < 8; ++kc) {
+      f4v a[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b) a[b] = *reinterpret_cast<const f4v *>(&sH1[(16 * b + r) * RM_LD + 16 * kc + 4 * q]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b][s], w2[kc][s], acc[b], 0, 0, 0);
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) sH2[(16 * b + 4 * q + t) * RM_LD + u] = bias_relu_f32(acc[b][t], b2);
+    __syncthreads();
+    // the whole block in 16-byte stores, and g = H2 W3 by one wave per 16 rows
+    for (int e = tid; e < TROWS * HID / 4; e += TW * 64) {
+      const int row = e / (HID / 4), col = (e % (HID / 4)) * 4;
+      if (row0 + row < R)
+        *reinterpret_cast<f4v *>(H2f + (row0 + row) * HID + col) =
+            *reinterpret_cast<const f4v *>(&sH2[row * RM_LD + col]);
+    }
+    if (w < 4) {
+      f4v gs{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kc = 0; kc < 8; ++kc) {
+        const f4v a = *reinterpret_cast<const f4v *>(&sH2[(16 * w + r) * RM_LD + 16 * kc + 4 * q]);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) gs = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], w3[kc][s], gs, 0, 0, 0);
+      }
+      if (r == 0)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const int64_t row = row0 + 16 * w + 4 * q + t;
+          if (row < R) g[row] = double(gs[t]);
+        }
+    }
+    // the next block's zl and sH1 writes come behind its first barrier; sH2 is
+    // written behind its second
+  }
+}
+
+struct GradSplits {
+  int64_t kw, kv;  // rows per slice: dW2, sums over rows with a vector
+  int nw, nv;      // slices of each kind
+};
+
+// Partial sums of the gradients.  Workgroup s sums rows [s kw, (s + 1) kw) of
+// dW2 into slice s of ws_w2; the sums over rows with a vector (biases, W1,
+// W3) go out every kv rows (kw a multiple of kv), slice by slice.
+struct GradSlices {
+  double *w2, *w1, *b1, *b2, *w3, *b3;  // [split][...]
+  int64_t kw, kv;
+  int nw, nv;  // slices of each kind
+};
+
+__global__ __launch_bounds__(TW * 64) void mlp_train_backward_kernel(const double *__restrict__ P,
+                                                                     const double *__restrict__ z,
+                                                                     const int64_t *__restrict__ order, int64_t r0,
+                                                                     int64_t c, const float *__restrict__ H2f,
+                                                                     const double *__restrict__ dg, GradSlices G) {
+  // two buffers each: the next block is formed while slower waves still read
+  __shared__ __attribute__((aligned(16))) float sH1[2][HID * TR_LD];    // [unit][row]
+  __shared__ __attribute__((aligned(16))) float sD2[2][TROWS * RM_LD];  // dA2 [row][unit]
+  __shared__ f4v zl[3][TROWS];
+  __shared__ double dgl[3][TROWS];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, r = lane & 15;
+  const int64_t R = 2 * c;
+  const int u = 16 * w + r;
+  float w1[3];
+#pragma unroll
+  for (int s = 0; s < 3; ++s) w1[s] = float(P[OFF_W1 + 3 * u + s]);
+  const double b1 = P[OFF_B1 + u], w3 = P[OFF_W3 + u];
+  f4v w2t[8];  // B operand of dA1: W2[16 kc + 4 q + s][unit]
+#pragma unroll
+  for (int kc = 0; kc < 8; ++kc)
+#pragma unroll
+    for (int s = 0; s < 4; ++s) w2t[kc][s] = float(P[OFF_W2 + (16 * kc + 4 * q + s) * HID + u]);
+
+  const int64_t begin = int64_t(blockIdx.x) * G.kw, end = begin + G.kw;
+  auto load_rows = [&](int64_t row0, f4v &zr, double &d) {
+    const int64_t row = row0 + lane;
+    const bool in = row < end && row < R;
+    zr = in ? mb_row(z, order, r0, c, row) : f4v{0.f, 0.f, 0.f, 0.f};
+    d = in ? dg[row] : 0.0;
+  };
+  auto load_h2 = [&](int64_t row0, f4v (&h)[4]) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int64_t row = row0 + 16 * b + 4 * q + t;
+        h[b][t] = row < end && row < R ? H2f[row * HID + u] : -0.f;
+      }
+  };
+  const f4v zero4{0.f, 0.f, 0.f, 0.f};
+  f4v accw[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) accw[i] = zero4;
+  f4v accv1 = zero4, accv2 = zero4, accv3 = zero4, accv0 = zero4;
+  int slice = int(begin / G.kv);
+  int64_t left = G.kv;  // rows until the vector sums go out
+
+  f4v zn;
+  double dn = 0.0;
+  if (w == 0) {
+    load_rows(begin, zn, dn);
+    zl[0][lane] = zn;
+    dgl[0][lane] = dn;
+    load_rows(begin + TROWS, zn, dn);
+  }
+  f4v h2n[4];
+  load_h2(begin, h2n);
+  __syncthreads();
+  int it = 0;
+  for (int64_t row0 = begin; row0 < end; row0 += TROWS, ++it) {
+    const int buf = it & 1, zb = it % 3;
+    // -- form H1 and dA2 of the wave's units
+    if (w == 0) {  // the next block's rows (read behind the barrier below)
+      zl[(it + 1) % 3][lane] = zn;
+      dgl[(it + 1) % 3][lane] = dn;
+    }
+    f4v h1[4], h2[4], d2[4];
+    layer1(zl[zb], w1, b1, q, r, h1);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      *reinterpret_cast<f4v *>(&sH1[buf][u * TR_LD + 16 * b + 4 * q]) = h1[b];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        h2[b][t] = h2n[b][t];
+        const double dgr = dgl[zb][16 * b + 4 * q + t];
+        d2[b][t] = unit_on(h2[b][t]) ? float(dgr * w3) : 0.f;
+        sD2[buf][(16 * b + 4 * q + t) * RM_LD + u] = d2[b][t];
+      }
+    }
+    __syncthreads();
+    if (row0 + TROWS < end) load_h2(row0 + TROWS, h2n);
+    if (w == 0) load_rows(row0 + 2 * TROWS, zn, dn);
+    // -- dA1 = dA2 W2, units of this wave
+    f4v d1[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) d1[b] = zero4;
+#pragma unroll
+    for (int kc = 0; kc < 8; ++kc) {
+      f4v a[4];
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        a[b] = *reinterpret_cast<const f4v *>(&sD2[buf][(16 * b + r) * RM_LD + 16 * kc + 4 * q]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          d1[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[b][s], w2t[kc][s], d1[b], 0, 0, 0);
+    }
+    // -- sums over the rows, block by block
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if (row0 + 16 * b >= end) break;
+      f4v hb[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        hb[i] = *reinterpret_cast<const f4v *>(&sH1[buf][(16 * i + r) * TR_LD + 16 * b + 4 * q]);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          accw[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d2[b][s], hb[i][s], accw[i], 0, 0, 0);
+        // A rows 0..3: 1, z0, z1, z2 (bias and W1), 1 (b2), dg (W3, b3)
+        const int row = 16 * b + 4 * q + s;
+        const f4v zr = zl[zb][row];
+        const float one = zr[0];
+        const float av = r == 0 ? one : r == 1 ? zr[1] : r == 2 ? zr[2] : r == 3 ? zr[3] : 0.f;
+        const float ad = r == 0 ? float(dgl[zb][row]) : 0.f;
+        const float dd = unit_on(h1[b][s]) ? d1[b][s] : 0.f;
+        accv1 = __builtin_amdgcn_mfma_f32_16x16x4f32(av, dd, accv1, 0, 0, 0);
+        accv2 = __builtin_amdgcn_mfma_f32_16x16x4f32(r == 0 ? one : 0.f, d2[b][s], accv2, 0, 0, 0);
+        accv3 = __builtin_amdgcn_mfma_f32_16x16x4f32(ad, h2[b][s], accv3, 0, 0, 0);
+        if (w == 0) accv0 = __builtin_amdgcn_mfma_f32_16x16x4f32(ad, r == 0 ? one : 0.f, accv0, 0, 0, 0);
+      }
+      left -= 16;
+      if (left == 0) {
+        if (q == 0 && slice < G.nv) {
+          const int64_t v = int64_t(slice) * HID + u;
+          G.b1[v] = double(accv1[0]);
+          G.w1[3 * v] = double(accv1[1]);
+          G.w1[3 * v + 1] = double(accv1[2]);
+          G.w1[3 * v + 2] = double(accv1[3]);
+          G.b2[v] = double(accv2[0]);
+          G.w3[v] = double(accv3[0]);
+          if (w == 0 && r == 0) G.b3[slice] = double(accv0[0]);
+        }
+        accv0 = accv1 = accv2 = accv3 = zero4;
+        ++slice;
+        left = G.kv;
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      G.w2[(int64_t(blockIdx.x) * HID + 16 * w + 4 * q + t) * HID + 16 * i + r] = double(accw[i][t]);
+  // vector slices that lie wholly past the workgroups' rows
+  if (blockIdx.x == gridDim.x - 1)
+    for (int sl = int(int64_t(G.nw) * (G.kw / G.kv)); sl < G.nv; ++sl)
+      if (w == 0) {
+        for (int e = lane; e < HID; e += 64) G.b1[int64_t(sl) * HID + e] = G.b2[int64_t(sl) * HID + e] =
+            G.w3[int64_t(sl) * HID + e] = 0.0;
+        for (int e = lane; e < 3 * HID; e += 64) G.w1[int64_t(sl) * 3 * HID + e] = 0.0;
+        if (lane == 0) G.b3[sl] = 0.0;
+      }
+}
+
 // Dense layer helper: C[M][N] = alpha * A' B'^T + beta C (GemmDesc conventions)
 void dense(int prec, int64_t M, int64_t N, int64_t K, const double *A, int64_t sam, int64_t sak, const double *B,
            int64_t sbn, int64_t sbk, double *C, double beta, double *ws, int64_t ws_elems, hipStream_t s) {
@@ -372,36 +684,130 @@ void dense(int prec, int64_t M, int64_t N, int64_t K, const double *A, int64_t s
   else gemm_lowp(d, prec, s, -1);
 }
 
+// Slices of the fused backward pass: those of the layer-by-layer gradient
+// GEMMs (their split-K factors, whole 16-row chunks), so that the partial sums
+// are the same.  The sums over rows with a vector go out several times per
+// dW2 slice; minibatches whose slice lengths do not fit each other that way
+// (2c above 65,536 and no multiple of it) run layer by layer.
+constexpr int64_t WS_ELEMS = 256 * int64_t(HID) * HID;
+bool fused_slices(int64_t R, GradSplits *g) {
+  auto pick = [R](int64_t M, int64_t N, int *split, int64_t *kc) {
+    *split = int(std::min<int64_t>(gemm_split_pick(M, N, R, -1), WS_ELEMS / (M * N)));
+    *kc = ((R + *split - 1) / *split + 15) / 16 * 16;
+  };
+  int64_t k1 = 0, k3 = 0;
+  int s1 = 0, s3 = 0;
+  pick(HID, HID, &g->nw, &g->kw);
+  pick(1, HID, &g->nv, &g->kv);  // b1, b2, W3
+  pick(HID, 3, &s1, &k1);        // W1
+  pick(1, 1, &s3, &k3);          // b3
+  return s1 == g->nv && s3 == g->nv && k1 == g->kv && k3 == g->kv && g->kw % g->kv == 0;
+}
+
 struct MlpWork {
   int64_t cap = 0;  // rows per chunk (samples)
   double *z2 = nullptr, *H1 = nullptr, *H2 = nullptr, *dH = nullptr, *g = nullptr, *dg = nullptr,
-         *grad = nullptr, *ones = nullptr, *lpart = nullptr, *ws = nullptr;
+         *grad = nullptr, *ones = nullptr, *lpart = nullptr, *ws = nullptr, *wsv = nullptr;
+  float *H2f = nullptr;
+  void *red = nullptr;  // grouped reductions of the fused pass: entries and offsets for up to two R
+  int64_t red_R[2] = {0, 0}, red_blocks[2] = {0, 0};
+  std::vector<unsigned char> red_host[2];
   int64_t ws_elems = 0;
+  static constexpr int64_t kMaxVec = 1024;  // vector slices (the largest split-K factor)
+  static void A(void **p, int64_t bytes) {
+    if (*p) return;
+    if (hipMalloc(p, std::max<int64_t>(bytes, 16)) != hipSuccess) {
+      (void)hipGetLastError();
+      *p = nullptr;
+      throw CCError(CC_ENOMEM, "MLP workspace allocation failed");
+    }
+  }
+  static void A(double **p, int64_t n) { A(reinterpret_cast<void **>(p), n * int64_t(sizeof(double))); }
   void alloc(int64_t c) {
     cap = c;
-    auto A = [](double **p, int64_t n) {
-      if (hipMalloc(p, sizeof(double) * std::max<int64_t>(n, 1)) != hipSuccess) {
-        (void)hipGetLastError();
-        throw CCError(CC_ENOMEM, "MLP workspace allocation failed");
-      }
-    };
-    A(&z2, 2 * c * 3);
-    A(&H1, 2 * c * HID);
-    A(&H2, 2 * c * HID);
-    A(&dH, 2 * c * HID);
     A(&g, 2 * c);
     A(&dg, 2 * c);
     A(&grad, NPAR);
-    A(&ones, 2 * c);
     A(&lpart, 4096);
-    ws_elems = 256 * int64_t(HID) * HID;
+    ws_elems = WS_ELEMS;
     A(&ws, ws_elems);
   }
+  void layers(hipStream_t s) {  // FP64 activations of the layer-by-layer passes
+    if (ones) return;
+    A(&z2, 2 * cap * 3);
+    A(&H1, 2 * cap * HID);
+    A(&H2, 2 * cap * HID);
+    A(&dH, 2 * cap * HID);
+    A(&ones, 2 * cap);
+    hipLaunchKernelGGL(fill_kernel, dim3(grid_of(2 * cap)), dim3(256), 0, s, ones, 1.0, 2 * cap);
+  }
+  void fused() {
+    A(reinterpret_cast<void **>(&H2f), 2 * cap * HID * int64_t(sizeof(float)));
+    A(&wsv, kMaxVec * (6 * HID + 1));
+    A(&red, 2 * kRedBytes);
+  }
+  static constexpr int kRed = 6;
+  static constexpr int64_t kRedBytes = 1024;
   ~MlpWork() {
-    for (double *p : {z2, H1, H2, dH, g, dg, grad, ones, lpart, ws})
+    for (double *p : {z2, H1, H2, dH, g, dg, grad, ones, lpart, ws, wsv})
       if (p) (void)hipFree(p);
+    if (H2f) (void)hipFree(H2f);
+    if (red) (void)hipFree(red);
   }
 };
+
+// Fused FP32 forward and backward of one minibatch; its gradient into w.grad.
+void fused_chunk(const double *P, const double *z, const double *y, const int64_t *order, int64_t r0, int64_t c,
+                 const GradSplits &sp, MlpWork &w, double *loss_out, int64_t loss_idx, hipStream_t s) {
+  const int64_t R = 2 * c;
+  w.fused();
+  GradSlices G{};
+  G.w2 = w.ws;
+  G.b1 = w.wsv;
+  G.b2 = G.b1 + MlpWork::kMaxVec * HID;
+  G.w3 = G.b2 + MlpWork::kMaxVec * HID;
+  G.w1 = G.w3 + MlpWork::kMaxVec * HID;
+  G.b3 = G.w1 + MlpWork::kMaxVec * 3 * HID;
+  G.kw = sp.kw;
+  G.kv = sp.kv;
+  G.nw = sp.nw;
+  G.nv = sp.nv;
+  // the six reductions as one grouped launch (tables kept for the full and
+  // the last minibatch)
+  int set = w.red_R[0] == R ? 0 : w.red_R[1] == R ? 1 : w.red_R[0] == 0 ? 0 : 1;
+  if (w.red_R[set] != R) {
+    const SplitkEntry es[MlpWork::kRed] = {
+        make_splitk_entry(G.w2, sp.nw, HID, HID, w.grad + OFF_W2, HID, 1.0, 0.0),
+        make_splitk_entry(G.w1, sp.nv, HID, 3, w.grad + OFF_W1, 3, 1.0, 0.0),
+        make_splitk_entry(G.b1, sp.nv, 1, HID, w.grad + OFF_B1, HID, 1.0, 0.0),
+        make_splitk_entry(G.b2, sp.nv, 1, HID, w.grad + OFF_B2, HID, 1.0, 0.0),
+        make_splitk_entry(G.w3, sp.nv, 1, HID, w.grad + OFF_W3, HID, 1.0, 0.0),
+        make_splitk_entry(G.b3, sp.nv, 1, 1, w.grad + OFF_B3, 1, 1.0, 0.0)};
+    int64_t off[MlpWork::kRed + 1] = {0};
+    for (int k = 0; k < MlpWork::kRed; ++k) off[k + 1] = off[k] + es[k].units;
+    static_assert(sizeof(es) + sizeof(off) <= MlpWork::kRedBytes, "reduction tables");
+    if (w.red_R[set] != 0) CC_HIP_CHECK(hipStreamSynchronize(s));  // an older table may still be read
+    w.red_host[set].resize(MlpWork::kRedBytes);
+    std::memcpy(w.red_host[set].data(), es, sizeof(es));
+    std::memcpy(w.red_host[set].data() + sizeof(es), off, sizeof(off));
+    CC_HIP_CHECK(hipMemcpyAsync(static_cast<char *>(w.red) + set * MlpWork::kRedBytes, w.red_host[set].data(),
+                                MlpWork::kRedBytes, hipMemcpyHostToDevice, s));
+    w.red_R[set] = R;
+    w.red_blocks[set] = off[MlpWork::kRed];
+  }
+  const int64_t nblk = (R + TROWS - 1) / TROWS;
+  hipLaunchKernelGGL(mlp_train_forward_kernel, dim3(std::min<int64_t>(nblk, 512)), dim3(TW * 64), 0, s, P, z, order,
+                     r0, c, w.H2f, w.g);
+  const int nb = int(grid_of(c));
+  hipLaunchKernelGGL(head_kernel, dim3(nb), dim3(256), 0, s, w.g, c, y, order, r0, (double *)nullptr, w.dg, w.lpart);
+  if (loss_out) hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, s, w.lpart, nb, c, loss_out, loss_idx);
+  hipLaunchKernelGGL(mlp_train_backward_kernel, dim3(sp.nw), dim3(TW * 64), 0, s, P, z, order, r0, c, w.H2f, w.dg, G);
+  CC_HIP_CHECK(hipGetLastError());
+  const char *tab = static_cast<const char *>(w.red) + set * MlpWork::kRedBytes;
+  launch_splitk_grouped(reinterpret_cast<const SplitkEntry *>(tab),
+                        reinterpret_cast<const int64_t *>(tab + MlpWork::kRed * sizeof(SplitkEntry)), MlpWork::kRed,
+                        w.red_blocks[set], false, s);
+}
 
 // Forward of rows [r0, r0+c): leaves H1, H2, g in the workspace.
 void forward_chunk(int prec, const double *P, const double *z, const int64_t *order, int64_t r0, int64_t c,
@@ -420,11 +826,17 @@ void forward_chunk(int prec, const double *P, const double *z, const int64_t *or
 void backward_chunk(int prec, const double *P, const double *z, const double *y, const int64_t *order, int64_t r0,
                     int64_t c, MlpWork &w, double *loss_out, int64_t loss_idx, hipStream_t s) {
   const int64_t R = 2 * c;
+  GradSplits sp;
+  if (prec == PREC_F32 && fused_slices(R, &sp)) {
+    fused_chunk(P, z, y, order, r0, c, sp, w, loss_out, loss_idx, s);
+    return;
+  }
+  w.layers(s);
   forward_chunk(prec, P, z, order, r0, c, w, s);
   const int nb = int(grid_of(c));
   hipLaunchKernelGGL(head_kernel, dim3(nb), dim3(256), 0, s, w.g, c, y, order, r0, (double *)nullptr, w.dg,
                      w.lpart);
-  if (loss_out) hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(64), 0, s, w.lpart, nb, c, loss_out, loss_idx);
+  if (loss_out) hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, s, w.lpart, nb, c, loss_out, loss_idx);
   double *G = w.grad;
   // W3 (1 x 128) = dg^T H2 ; b3 = sum dg
   dense(prec, 1, HID, R, w.dg, R, 1, w.H2, 1, HID, G + OFF_W3, 0.0, w.ws, w.ws_elems, s);
@@ -573,6 +985,7 @@ int cc_mlp_forward(cc_ctx *ctx, int prec, const double *params, const double *z,
     ccmi::MlpWork w;
     const int64_t cap = std::min<int64_t>(n, 1 << 18);
     w.alloc(cap);
+    w.layers(ctx->stream);
     for (int64_t r0 = 0; r0 < n; r0 += cap) {
       const int64_t c = std::min(cap, n - r0);
       ccmi::forward_chunk(prec, params, z, nullptr, r0, c, w, ctx->stream);
@@ -595,7 +1008,6 @@ int cc_mlp_loss_grad(cc_ctx *ctx, int prec, const double *params, const double *
     ccmi::MlpWork w;
     w.alloc(n);
     hipStream_t s = ctx->stream;
-    hipLaunchKernelGGL(ccmi::fill_kernel, dim3(ccmi::grid_of(2 * n)), dim3(256), 0, s, w.ones, 1.0, 2 * n);
     double *dl = nullptr;
     CC_HIP_CHECK(hipMalloc(&dl, sizeof(double)));
     ccmi::backward_chunk(prec, params, z, y, nullptr, 0, n, w, dl, 0, s);
@@ -622,7 +1034,6 @@ int cc_mlp_train(cc_ctx *ctx, int prec, double *params, double *adam_m, double *
     const int64_t c = std::min(batch, n);
     ccmi::MlpWork w;
     w.alloc(c);
-    hipLaunchKernelGGL(ccmi::fill_kernel, dim3(ccmi::grid_of(2 * c)), dim3(256), 0, s, w.ones, 1.0, 2 * c);
     const int64_t steps_per_epoch = (n + c - 1) / c;
     double *dl = nullptr;
     CC_HIP_CHECK(hipMalloc(&dl, sizeof(double) * steps_per_epoch));
