@@ -87,6 +87,7 @@ void convert_shadow(int prec, const double *src, int64_t n, void *dst, hipStream
 int64_t blocked_plane(int64_t R, int64_t K);
 void convert_blocked(const double *src, const double *ref, int64_t R, int64_t K, void *dst, hipStream_t s);
 bool gemm_lowp_tile_blocked(int prec, int tile_id);  // its LDS-direct kernel reads blocked copies
+bool gemm_b3_auto_blocked(int64_t M, int64_t N);  // the library's own choice for M x N outputs reads them
 // dst = reduced-precision (a - ref), same layout as convert_shadow.
 void convert_delta(int prec, const double *a, const double *ref, int64_t n, void *dst, hipStream_t s);
 void copy_f64(double *dst, const double *src, int64_t n, hipStream_t s);

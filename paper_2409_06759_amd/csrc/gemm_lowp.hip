@@ -387,6 +387,8 @@ __global__ __launch_bounds__(WM *WN *kWave) void gemm_lowp_kernel(GemmDesc d, in
 // chunk visible to every wave.  The same barrier, behind "lgkmcnt == 0",
 // guarantees that every wave has finished reading the stage the next loads
 // overwrite.  Nothing else in the kernel uses M0.
+__device__ __attribute__((aligned(16))) const uint32_t kZero16[4] = {0, 0, 0, 0};
+
 namespace dma {
 constexpr int BM = 256, BN = 128, BK = 32, WM = 4, WN = 2, NT = WM * WN * kWave;
 constexpr int FM = BM / WM / 16, FN = BN / WN / 16;
@@ -397,9 +399,14 @@ constexpr int LOADS = (2 * (BM / 16) + 2 * (BN / 16)) / (WM * WN);  // per wave 
 static_assert(LOADS == 6, "the explicit waits count six loads per chunk");
 }  // namespace dma
 
+template <int BM, int BN, int WM, int WN, int NST>
 __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tilesM, int64_t tilesN, int64_t L0) {
-  using namespace dma;
-  __shared__ __attribute__((aligned(16))) unsigned short S[NSTAGE * STAGE];
+  constexpr int BK = 32, FM = BM / WM / 16, FN = BN / WN / 16;
+  constexpr int A_EL = BM * BK, B_EL = BN * BK, STAGE = 2 * A_EL + 2 * B_EL;  // [A hi | A lo | B hi | B lo]
+  constexpr int LOADS = 2 * (BM / 16 + BN / 16) / (WM * WN);                  // per wave and chunk
+  static_assert(2 * (BM / 16 + BN / 16) % (WM * WN) == 0, "whole loads per wave");
+  static_assert(NST == 2 || NST == 3, "the explicit waits are written for one or two chunks in flight");
+  __shared__ __attribute__((aligned(16))) unsigned short S[NST * STAGE];
 
   const int64_t tiles = tilesM * tilesN;
   const int64_t ks = L0 / tiles, L = L0 % tiles;
@@ -411,11 +418,11 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
   const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
-  const int64_t nk = K / BK;
+  const int64_t nk = (K + BK - 1) / BK;
 
-  // this wave's loads: A blocks 2w and 2w+1, B block w, hi and lo planes of
-  // each; LDS addresses are byte offsets in the shared aperture (its low 32
-  // bits), made wave-uniform for M0
+  // this wave's loads: LOADS of the stage's 16-row blocks, numbered hi and lo
+  // plane by block, A before B; LDS addresses are byte offsets in the shared
+  // aperture (its low 32 bits), made wave-uniform for M0
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(S));
   const unsigned short *src[LOADS];
   uint32_t dst[LOADS];
@@ -430,19 +437,23 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
                     : g + std::min<int64_t>(r0 + r, lim - 1) * stride + q * 8;
   };
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int blk = 2 * wave + (u >> 1), pl = u & 1;
-    src[u] = row_src(Ag + pl * d.a_plane, m0 + blk * 16, M, d.sam);
-    dst[u] = __builtin_amdgcn_readfirstlane(lds0 + 2u * uint32_t(pl * A_EL + blk * 512));
-  }
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    src[4 + u] = row_src(Bg + u * d.b_plane, n0 + wave * 16, N, d.sbn);
-    dst[4 + u] = __builtin_amdgcn_readfirstlane(lds0 + 2u * uint32_t(2 * A_EL + u * B_EL + wave * 512));
+  for (int u = 0; u < LOADS; ++u) {
+    const int x = wave * LOADS + u, blk = x >> 1, pl = x & 1, bb = blk - BM / 16;
+    src[u] = bb < 0 ? row_src(Ag + pl * d.a_plane, m0 + blk * 16, M, d.sam)
+                    : row_src(Bg + pl * d.b_plane, n0 + bb * 16, N, d.sbn);
+    dst[u] = __builtin_amdgcn_readfirstlane(
+        lds0 + 2u * uint32_t(bb < 0 ? pl * A_EL + blk * 512 : 2 * A_EL + pl * B_EL + bb * 512));
   }
   auto issue = [&](int stage, int64_t k0) {
+    if (k0 + BK <= K) {
 #pragma unroll
-    for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0 * kx, dst[u] + uint32_t(stage) * uint32_t(2 * STAGE));
+      for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0 * kx, dst[u] + uint32_t(stage) * uint32_t(2 * STAGE));
+    } else {  // the last, partial chunk (row-major copies): zeros past K
+      const bool in = k0 + q * 8 < K;
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u)
+        lds_load16(in ? static_cast<const void *>(src[u] + k0) : kZero16, dst[u] + uint32_t(stage) * uint32_t(2 * STAGE));
+    }
   };
 
   f4 acc[FM][FN];
@@ -452,12 +463,12 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
     for (int j = 0; j < FN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
   if (nk > 0) issue(0, 0);
-  if (nk > 1) issue(1, BK);
-  int cur = 0, nxt = 2;
+  if (NST == 3 && nk > 1) issue(1, BK);
+  int cur = 0, nxt = NST - 1;
   for (int64_t kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + 2 < nk) issue(nxt, (kt + 2) * BK);
+    if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
     const unsigned short *St = S + cur * STAGE;
     bf8 fah[FM], fal[FM], fbh[FN], fbl[FN];
 #pragma unroll
@@ -484,8 +495,8 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fah[i], fbh[j], acc[i][j], 0, 0, 0);
       }
     __builtin_amdgcn_s_setprio(0);
-    cur = cur == NSTAGE - 1 ? 0 : cur + 1;
-    nxt = nxt == NSTAGE - 1 ? 0 : nxt + 1;
+    cur = cur == NST - 1 ? 0 : cur + 1;
+    nxt = nxt == NST - 1 ? 0 : nxt + 1;
   }
 
   // epilogue (as the staged kernel): accumulator t of lane l is C[4 (l >> 4) + t][l & 15]
@@ -662,9 +673,9 @@ __device__ __forceinline__ void gemm_b3_dmap_body(const GemmDesc &d, int64_t til
     }
 }
 
-template <int TAG>
-__global__ __launch_bounds__(dma::NT) void gemm_b3_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
-  gemm_b3_dma_body(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split));
+template <int BM, int BN, int WM, int WN, int NST, int TAG>
+__global__ __launch_bounds__(WM *WN *kWave) void gemm_b3_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
+  gemm_b3_dma_body<BM, BN, WM, WN, NST>(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split));
 }
 
 template <int TAG>
@@ -799,11 +810,14 @@ __global__ __launch_bounds__(dmw::NT) void gemm_b3_dmw_kernel(GemmDesc d, int64_
 // step s of each 16-wide k half, so a 16-row block of a k half is 64 slots
 // of 16 bytes, slot L = row (L & 15), k = 4 (L >> 4) .. +3.  A chunk of 32 k
 // is two such halves: 16 + 16 A loads and 8 + 8 B loads, six per wave.
+template <int BM, int BN, int WM, int WN, int NST>
 __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t tilesM, int64_t tilesN, int64_t L0) {
-  using namespace dma;
+  constexpr int BK = 32, FM = BM / WM / 16, FN = BN / WN / 16;
   constexpr int FA_EL = BM * BK, FB_EL = BN * BK, FSTAGE = FA_EL + FB_EL;  // floats: [A | B]
-  static_assert(FSTAGE * 4 == STAGE * 2, "same stage size as the split-bf16 kernel");
-  __shared__ __attribute__((aligned(16))) float S[NSTAGE * FSTAGE];
+  constexpr int LOADS = 2 * (BM / 16 + BN / 16) / (WM * WN);               // per wave and chunk
+  static_assert(2 * (BM / 16 + BN / 16) % (WM * WN) == 0, "whole loads per wave");
+  static_assert(NST == 2 || NST == 3, "the explicit waits are written for one or two chunks in flight");
+  __shared__ __attribute__((aligned(16))) float S[NST * FSTAGE];
 
   const int64_t tiles = tilesM * tilesN;
   const int64_t ks = L0 / tiles, L = L0 % tiles;
@@ -815,29 +829,36 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
   const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
-  const int64_t nk = K / BK;
+  const int64_t nk = (K + BK - 1) / BK;
 
-  // loads: (block, k half) pairs; A: blocks 2w, 2w+1 x halves 0, 1; B: block w x halves 0, 1.
-  // A block b, half h sits at floats (h * (BM / 16) + b) * 256 of the stage.
+  // loads: (block, k half) pairs, A before B; A block b, half h sits at
+  // floats (h * (BM / 16) + b) * 256 of the stage
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(S));
   const float *src[LOADS];
   uint32_t dst[LOADS];
   const float *Ag = static_cast<const float *>(d.A) + kb;
   const float *Bg = static_cast<const float *>(d.B) + kb;
 #pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int blk = 2 * wave + (u >> 1), h = u & 1;
-    src[u] = Ag + std::min<int64_t>(m0 + blk * 16 + r, M - 1) * d.sam + 16 * h + 4 * q;
-    dst[u] = __builtin_amdgcn_readfirstlane(lds0 + 4u * uint32_t((h * (BM / 16) + blk) * 256));
-  }
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    src[4 + u] = Bg + std::min<int64_t>(n0 + wave * 16 + r, N - 1) * d.sbn + 16 * u + 4 * q;
-    dst[4 + u] = __builtin_amdgcn_readfirstlane(lds0 + 4u * uint32_t(FA_EL + (u * (BN / 16) + wave) * 256));
+  for (int u = 0; u < LOADS; ++u) {
+    const int x = wave * LOADS + u, blk = x >> 1, h = x & 1, bb = blk - BM / 16;
+    src[u] = (bb < 0 ? Ag + std::min<int64_t>(m0 + blk * 16 + r, M - 1) * d.sam
+                     : Bg + std::min<int64_t>(n0 + bb * 16 + r, N - 1) * d.sbn) +
+             16 * h + 4 * q;
+    dst[u] = __builtin_amdgcn_readfirstlane(
+        lds0 + 4u * uint32_t(bb < 0 ? (h * (BM / 16) + blk) * 256 : FA_EL + (h * (BN / 16) + bb) * 256));
   }
   auto issue = [&](int stage, int64_t k0) {
+    if (k0 + BK <= K) {
 #pragma unroll
-    for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(4 * FSTAGE));
+      for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(4 * FSTAGE));
+    } else {  // the last, partial chunk: zeros past K
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u) {
+        const int h = (wave * LOADS + u) & 1;
+        lds_load16(k0 + 16 * h + 4 * q < K ? static_cast<const void *>(src[u] + k0) : kZero16,
+                   dst[u] + uint32_t(stage) * uint32_t(4 * FSTAGE));
+      }
+    }
   };
 
   f4 acc[FM][FN];
@@ -847,12 +868,12 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
     for (int j = 0; j < FN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
   if (nk > 0) issue(0, 0);
-  if (nk > 1) issue(1, BK);
-  int cur = 0, nxt = 2;
+  if (NST == 3 && nk > 1) issue(1, BK);
+  int cur = 0, nxt = NST - 1;
   for (int64_t kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + 2 < nk) issue(nxt, (kt + 2) * BK);
+    if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
     const float *St = S + cur * FSTAGE;
     // the second k half is read behind the first half's first MFMA step
     f4 fa[2][FM], fb[2][FN];
@@ -881,8 +902,8 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
     for (int s = 1; s < 4; ++s) mfma_step(0, s);
 #pragma unroll
     for (int s = 0; s < 4; ++s) mfma_step(1, s);
-    cur = cur == NSTAGE - 1 ? 0 : cur + 1;
-    nxt = nxt == NSTAGE - 1 ? 0 : nxt + 1;
+    cur = cur == NST - 1 ? 0 : cur + 1;
+    nxt = nxt == NST - 1 ? 0 : nxt + 1;
   }
 
   double *__restrict__ Cp = static_cast<double *>(d.C);
@@ -911,23 +932,25 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
     }
 }
 
-template <int TAG>
-__global__ __launch_bounds__(dma::NT) void gemm_f32_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
-  gemm_f32_dma_body(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split));
+template <int BM, int BN, int WM, int WN, int NST, int TAG>
+__global__ __launch_bounds__(WM *WN *kWave) void gemm_f32_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
+  gemm_f32_dma_body<BM, BN, WM, WN, NST>(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split));
 }
 
+// the shapes and layouts the LDS-direct kernels handle: K-contiguous copies
+// with 16-byte aligned rows of whole 16-byte groups (the last, partial chunk of
+// K loads zeros past K); blocked copies hold whole chunks
 bool f32_dma_ok(const GemmDesc &d) {
-  return d.lp_in && d.sak == 1 && d.sbk == 1 && d.K % dma::BK == 0 &&
-         d.sam % 4 == 0 && d.sbn % 4 == 0 && (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 &&
-         (reinterpret_cast<uintptr_t>(d.B) & 15) == 0;
-}
-
-// the shapes and layouts the LDS-direct kernel handles
-bool b3_dma_ok(const GemmDesc &d) {
-  return d.lp_in && d.sak == 1 && d.sbk == 1 && d.K % dma::BK == 0 &&
-         d.sam % 8 == 0 && d.sbn % 8 == 0 && d.a_plane % 8 == 0 && d.b_plane % 8 == 0 &&
+  return d.lp_in == 1 && d.sak == 1 && d.sbk == 1 && d.K % 4 == 0 && d.sam % 4 == 0 && d.sbn % 4 == 0 &&
          (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 && (reinterpret_cast<uintptr_t>(d.B) & 15) == 0;
 }
+bool b3_dma_ok(const GemmDesc &d) {
+  return d.lp_in && d.sak == 1 && d.sbk == 1 && d.K % (d.lp_in == 2 ? 32 : 8) == 0 && d.sam % 8 == 0 &&
+         d.sbn % 8 == 0 && d.a_plane % 8 == 0 && d.b_plane % 8 == 0 &&
+         (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 && (reinterpret_cast<uintptr_t>(d.B) & 15) == 0;
+}
+// the pipelined 256x128 and the 256x256 kernels: whole chunks only
+bool b3_whole_ok(const GemmDesc &d) { return b3_dma_ok(d) && d.K % dma::BK == 0; }
 
 // Grouped launch over many systems: system b owns logical tiles
 // [off[b], off[b+1]).  FP64 operands converted while staging, or (LPIN)
@@ -999,23 +1022,37 @@ int occ_l() {
         {CC_LOCC(MODE, BM, BN, BK, WM, WN, false, PF), CC_LOCC(MODE, BM, BN, BK, WM, WN, true, PF)},             \
         false, &launch_lg<MODE, BM, BN, BK, WM, WN, true, true, true>                                           \
   }
-template <int TAG>
+template <int BM, int BN, int WM, int WN, int NST, int TAG>
 void launch_b3_dma(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
   if (b3_dma_ok(d))
-    hipLaunchKernelGGL((gemm_b3_dma_kernel<TAG>), dim3(tm * tn * d.split), dim3(dma::NT), 0, s, d, tm, tn);
+    hipLaunchKernelGGL((gemm_b3_dma_kernel<BM, BN, WM, WN, NST, TAG>), dim3(tm * tn * d.split), dim3(WM * WN * kWave),
+                       0, s, d, tm, tn);
   else
-    launch_l<PREC_BF16X3, 256, 128, 32, 4, 2, true, true, 1, TAG>(d, tm, tn, s);
+    launch_l<PREC_BF16X3, BM, BN, 32, WM, WN, true, true, 1, TAG>(d, tm, tn, s);
 }
-template <int TAG>
+template <int BM, int BN, int WM, int WN, int NST, int TAG>
 void launch_f32_dma(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
   if (f32_dma_ok(d))
-    hipLaunchKernelGGL((gemm_f32_dma_kernel<TAG>), dim3(tm * tn * d.split), dim3(dma::NT), 0, s, d, tm, tn);
+    hipLaunchKernelGGL((gemm_f32_dma_kernel<BM, BN, WM, WN, NST, TAG>), dim3(tm * tn * d.split), dim3(WM * WN * kWave),
+                       0, s, d, tm, tn);
   else
-    launch_l<PREC_F32, 256, 128, 32, 4, 2, true, true, 1, TAG>(d, tm, tn, s);
+    launch_l<PREC_F32, BM, BN, 32, WM, WN, true, true, 1, TAG>(d, tm, tn, s);
 }
+template <int BM, int BN, int WM, int WN, int NST>
 int occ_f32_dma() {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_dma_kernel<0>, dma::NT, 0) != hipSuccess) {
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f32_dma_kernel<BM, BN, WM, WN, NST, 0>, WM * WN * kWave,
+                                                   0) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return nb;
+}
+template <int BM, int BN, int WM, int WN, int NST>
+int occ_b3_dma() {
+  int nb = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_b3_dma_kernel<BM, BN, WM, WN, NST, 0>, WM * WN * kWave,
+                                                   0) != hipSuccess) {
     (void)hipGetLastError();
     return 0;
   }
@@ -1023,7 +1060,7 @@ int occ_f32_dma() {
 }
 template <int TAG>
 void launch_b3_dmap(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
-  if (b3_dma_ok(d))
+  if (b3_whole_ok(d))
     hipLaunchKernelGGL((gemm_b3_dmap_kernel<TAG>), dim3(tm * tn * d.split), dim3(dma::NT), 0, s, d, tm, tn);
   else
     launch_l<PREC_BF16X3, 256, 128, 32, 4, 2, true, true, 1, TAG>(d, tm, tn, s);
@@ -1036,17 +1073,9 @@ int occ_b3_dmap() {
   }
   return nb;
 }
-int occ_b3_dma() {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_b3_dma_kernel<0>, dma::NT, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    return 0;
-  }
-  return nb;
-}
 template <int TAG>
 void launch_b3_dmw(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
-  if (b3_dma_ok(d))
+  if (b3_whole_ok(d))
     hipLaunchKernelGGL((gemm_b3_dmw_kernel<TAG>), dim3(tm * tn * d.split), dim3(dmw::NT), 0, s, d, tm, tn);
   else  // shapes it does not take: the staged 256x128 kernel over its own tiles
     launch_l<PREC_BF16X3, 256, 128, 32, 4, 2, true, true, 1, TAG>(d, (d.M + 255) / 256, (d.N + 127) / 128, s);
@@ -1063,28 +1092,29 @@ int occ_b3_dmw() {
   }
   return nb;
 }
+// LDS-direct where the operands allow, else the staged kernel of the tile
+#define CC_LTILE_DMA(MODE, LAUNCH, OCC, BM, BN, WM, WN, NST, NAME, BLOCKED)                                         \
+  LTile {                                                                                                          \
+    #BM "x" #BN "x32_w" #WM "x" #WN NAME, BM, BN, 32,                                                              \
+        {&launch_l<MODE, BM, BN, 32, WM, WN, false, false, 1>, &launch_l<MODE, BM, BN, 32, WM, WN, false, true, 1>, \
+         &launch_l<MODE, BM, BN, 32, WM, WN, true, false, 1>, &LAUNCH<BM, BN, WM, WN, NST, 0>},                    \
+        &LAUNCH<BM, BN, WM, WN, NST, 1>, &LAUNCH<BM, BN, WM, WN, NST, 2>,                                          \
+        {&launch_lg<MODE, BM, BN, 32, WM, WN, false, false>, &launch_lg<MODE, BM, BN, 32, WM, WN, false, true>,    \
+         &launch_lg<MODE, BM, BN, 32, WM, WN, true, false>, &launch_lg<MODE, BM, BN, 32, WM, WN, true, true>},     \
+        {CC_LOCC(MODE, BM, BN, 32, WM, WN, false, 1), &occ_l<MODE, BM, BN, 32, WM, WN, false, false, true, 1>,     \
+         &occ_l<MODE, BM, BN, 32, WM, WN, false, true, true, 1>,                                                   \
+         &occ_l<MODE, BM, BN, 32, WM, WN, true, false, true, 1>, &OCC<BM, BN, WM, WN, NST>},                       \
+        BLOCKED, &launch_lg<MODE, BM, BN, 32, WM, WN, true, true, true>                                            \
+  }
 const LTile kF32Tiles[] = {
     CC_LTILE(PREC_F32, 128, 128, 16, 2, 2, 1), CC_LTILE(PREC_F32, 64, 64, 16, 2, 2, 1),
     CC_LTILE(PREC_F32, 32, 32, 16, 2, 2, 1),   CC_LTILE(PREC_F32, 128, 64, 16, 2, 2, 1),
     CC_LTILE(PREC_F32, 64, 128, 16, 2, 2, 1),  CC_LTILE(PREC_F32, 128, 128, 32, 2, 2, 1),
     CC_LTILE(PREC_F32, 128, 128, 16, 4, 2, 1), CC_LTILE(PREC_F32, 128, 128, 32, 4, 2, 1),
     CC_LTILE(PREC_F32, 128, 128, 32, 4, 2, 2), CC_LTILE(PREC_F32, 256, 128, 32, 4, 2, 1),
-    // 256x128x32 with LDS-direct loads where the shape allows, else staged
-    LTile{"256x128x32_w4x2_lds",
-          256,
-          128,
-          32,
-          {&launch_l<PREC_F32, 256, 128, 32, 4, 2, false, false, 1>, &launch_l<PREC_F32, 256, 128, 32, 4, 2, false, true, 1>,
-           &launch_l<PREC_F32, 256, 128, 32, 4, 2, true, false, 1>, &launch_f32_dma<0>},
-          &launch_f32_dma<1>,
-          &launch_f32_dma<2>,
-          {&launch_lg<PREC_F32, 256, 128, 32, 4, 2, false, false>, &launch_lg<PREC_F32, 256, 128, 32, 4, 2, false, true>,
-           &launch_lg<PREC_F32, 256, 128, 32, 4, 2, true, false>, &launch_lg<PREC_F32, 256, 128, 32, 4, 2, true, true>},
-          {CC_LOCC(PREC_F32, 256, 128, 32, 4, 2, false, 1), &occ_l<PREC_F32, 256, 128, 32, 4, 2, false, false, true, 1>,
-           &occ_l<PREC_F32, 256, 128, 32, 4, 2, false, true, true, 1>,
-           &occ_l<PREC_F32, 256, 128, 32, 4, 2, true, false, true, 1>, &occ_f32_dma},
-          false,
-          &launch_lg<PREC_F32, 256, 128, 32, 4, 2, true, true, true>},
+    CC_LTILE_DMA(PREC_F32, launch_f32_dma, occ_f32_dma, 256, 128, 4, 2, 3, "_lds", false),
+    CC_LTILE_DMA(PREC_F32, launch_f32_dma, occ_f32_dma, 128, 128, 4, 2, 2, "_lds2", false),
+    CC_LTILE_DMA(PREC_F32, launch_f32_dma, occ_f32_dma, 64, 128, 2, 4, 2, "_lds2", false),
 };
 const LTile kB3Tiles[] = {
     CC_LTILE(PREC_BF16X3, 128, 128, 32, 2, 2, 1), CC_LTILE(PREC_BF16X3, 64, 64, 32, 2, 2, 1),
@@ -1092,25 +1122,7 @@ const LTile kB3Tiles[] = {
     CC_LTILE(PREC_BF16X3, 64, 128, 32, 2, 2, 1),  CC_LTILE(PREC_BF16X3, 128, 128, 64, 2, 2, 1),
     CC_LTILE(PREC_BF16X3, 128, 128, 32, 4, 2, 1), CC_LTILE(PREC_BF16X3, 256, 128, 32, 4, 2, 1),
     CC_LTILE(PREC_BF16X3, 128, 128, 32, 4, 2, 2),
-    // 256x128x32 with LDS-direct loads where the shape allows, else staged
-    LTile{"256x128x32_w4x2_lds",
-          256,
-          128,
-          32,
-          {&launch_l<PREC_BF16X3, 256, 128, 32, 4, 2, false, false, 1>,
-           &launch_l<PREC_BF16X3, 256, 128, 32, 4, 2, false, true, 1>,
-           &launch_l<PREC_BF16X3, 256, 128, 32, 4, 2, true, false, 1>, &launch_b3_dma<0>},
-          &launch_b3_dma<1>,
-          &launch_b3_dma<2>,
-          {&launch_lg<PREC_BF16X3, 256, 128, 32, 4, 2, false, false>,
-           &launch_lg<PREC_BF16X3, 256, 128, 32, 4, 2, false, true>,
-           &launch_lg<PREC_BF16X3, 256, 128, 32, 4, 2, true, false>,
-           &launch_lg<PREC_BF16X3, 256, 128, 32, 4, 2, true, true>},
-          {CC_LOCC(PREC_BF16X3, 256, 128, 32, 4, 2, false, 1), &occ_l<PREC_BF16X3, 256, 128, 32, 4, 2, false, false, true, 1>,
-           &occ_l<PREC_BF16X3, 256, 128, 32, 4, 2, false, true, true, 1>,
-           &occ_l<PREC_BF16X3, 256, 128, 32, 4, 2, true, false, true, 1>, &occ_b3_dma},
-          true,
-          &launch_lg<PREC_BF16X3, 256, 128, 32, 4, 2, true, true, true>},
+    CC_LTILE_DMA(PREC_BF16X3, launch_b3_dma, occ_b3_dma, 256, 128, 4, 2, 3, "_lds", true),
     // the same with the next chunk's fragments read behind the current MFMAs
     LTile{"256x128x32_w4x2_ldsp",
           256,
@@ -1146,6 +1158,8 @@ const LTile kB3Tiles[] = {
            &occ_l<PREC_BF16X3, 256, 128, 32, 4, 2, false, true, true, 1>,
            &occ_l<PREC_BF16X3, 256, 128, 32, 4, 2, true, false, true, 1>, &occ_b3_dmw},
           true},
+    CC_LTILE_DMA(PREC_BF16X3, launch_b3_dma, occ_b3_dma, 128, 128, 4, 2, 2, "_lds2", true),
+    CC_LTILE_DMA(PREC_BF16X3, launch_b3_dma, occ_b3_dma, 64, 128, 2, 4, 2, "_lds2", true),
 };
 constexpr int kNumF32 = sizeof(kF32Tiles) / sizeof(kF32Tiles[0]);
 constexpr int kNumB3 = sizeof(kB3Tiles) / sizeof(kB3Tiles[0]);
@@ -1570,6 +1584,81 @@ const char *gemm_lowp_tile_name(int prec, int id) {
   return prec == PREC_F32 ? kF32Tiles[id].name : kB3Tiles[id].name;
 }
 
+namespace {
+
+// The library's own choice runs in two parts.  How K is cut (the split-K
+// factor, the K-split tail of a mostly empty last round) follows the staged
+// tile of pick_l, and with it the order of every sum; which kernel then
+// multiplies is free, since all of them add the same products in the same
+// order.  Copies that an LDS-direct kernel can read go to the one with the least
+// (rounds of workgroups) x (tile area) / (its share of the MFMA rate on large
+// shapes).  Split bf16, 576 x 14400 x 14400: 2654 (staged 64x128) -> 754 us;
+// 400 x 10000 x 10000: 1211 -> 790 us; FP32: 3029 -> 2062 and 1289 -> 1040 us.
+struct ExecTile {
+  int tile;
+  double eff;
+};
+constexpr ExecTile kF32Exec[] = {{kNumF32 - 3, 0.83}, {kNumF32 - 2, 0.80}, {kNumF32 - 1, 0.78}};
+constexpr ExecTile kB3Exec[] = {{9, 0.50}, {11, 0.52}, {kNumB3 - 2, 0.52}, {kNumB3 - 1, 0.40}};
+
+int exec_tile(const GemmDesc &d, int prec, int staged) {
+  const bool f32 = prec == PREC_F32;
+  if (f32 ? !f32_dma_ok(d) : !b3_dma_ok(d)) return staged;
+  const LTile *tiles = f32 ? kF32Tiles : kB3Tiles;
+  if (d.split > 1) {  // the same K slices under the kernel's chunk length
+    const int64_t per = (d.K + d.split - 1) / d.split, b0 = tiles[staged].BK;
+    if ((per + b0 - 1) / b0 * b0 != (per + 31) / 32 * 32) return staged;
+  }
+  int best = staged;
+  double best_cost = 1e300;
+  const ExecTile *ex = f32 ? kF32Exec : kB3Exec;
+  const int n = f32 ? int(sizeof(kF32Exec) / sizeof(ExecTile)) : int(sizeof(kB3Exec) / sizeof(ExecTile));
+  for (int k = 0; k < n; ++k) {
+    const LTile &t = tiles[ex[k].tile];
+    if (!f32 && ex[k].tile == 11 && !b3_whole_ok(d)) continue;  // its staged fallback has another tile
+    const double wgs = double((d.M + t.BM - 1) / t.BM) * double((d.N + t.BN - 1) / t.BN) * d.split;
+    const double cost = std::ceil(wgs / 256.0) * double(t.BM) * t.BN / ex[k].eff;
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = ex[k].tile;
+    }
+  }
+  return best;
+}
+
+// f(part, tile) over the launches of a GEMM: as one, cut, or split along K
+template <class F>
+void lowp_parts(const GemmDesc &d, int prec, int tile_id, F &&f) {
+  const LTile *tiles = prec == PREC_F32 ? kF32Tiles : kB3Tiles;
+  const bool own = tile_id < 0 || tile_id >= num_l(prec);
+  const int t0 = own ? pick_l(tiles, d.M, d.N) : tile_id;
+  const LTile &ti = tiles[t0];
+  // slots of the staged tile on row-major copies, whatever form the copies have
+  GemmDesc g = d;
+  if (own && g.lp_in == 2) g.lp_in = 1;
+  auto run = [&](const GemmDesc &x) { f(x, own ? exec_tile(x, prec, t0) : t0); };
+  if (d.ws && d.split == 1) {
+    const TailCut tc = lowp_cut(g, prec, t0);
+    if (tc.axis && tc.ws_elems <= d.ws_elems) {
+      // operand element size: converted copies (4-byte FP32, 2-byte bf16
+      // planes) or the FP64 tensors themselves
+      const size_t es = d.lp_in ? (prec == PREC_F32 ? 4 : 2) : sizeof(double);
+      gemm_run_cut(d, tc, es, es, run);
+      return;
+    }
+  }
+  GemmDesc x = d;
+  if (d.ws && d.split > 1 && d.ws_elems > 0)
+    x.split = gemm_split_refine(d.M, d.N, d.K, ti.BM, ti.BN, ti.BK, lowp_slots(g, prec, t0), d.split, d.ws_elems);
+  run(x);
+}
+
+}  // namespace
+
+// K slices of 32-long chunks: every part of the library's own choice takes
+// whole blocks of the copies, so exec_tile finds an LDS-direct kernel for it
+bool gemm_b3_auto_blocked(int64_t M, int64_t N) { return kB3Tiles[pick_l(kB3Tiles, M, N)].BK == dma::BK; }
+
 void gemm_lowp(const GemmDesc &d, int prec, hipStream_t s, int tile_id) {
   if (d.M <= 0 || d.N <= 0) return;
   CC_REQUIRE(prec == PREC_F32 || prec == PREC_BF16X3, -1, "gemm_lowp: precision");
@@ -1580,40 +1669,19 @@ void gemm_lowp(const GemmDesc &d, int prec, hipStream_t s, int tile_id) {
     gemm_f64(d, s, -1);  // pure scaling of C: no products involved
     return;
   }
-  const LTile *tiles = prec == PREC_F32 ? kF32Tiles : kB3Tiles;
-  if (tile_id < 0 || tile_id >= num_l(prec)) tile_id = pick_l(tiles, d.M, d.N);
-  const LTile &ti = tiles[tile_id];
-  const int64_t tm = (d.M + ti.BM - 1) / ti.BM, tn = (d.N + ti.BN - 1) / ti.BN;
   CC_REQUIRE(d.split >= 1 && (d.split == 1 || d.ws != nullptr), -1, "gemm: split-K workspace");
   CC_REQUIRE(d.split == 1 || d.ws_elems == 0 || d.ws_elems >= d.split * d.M * d.N, -1,
              "gemm: split-K workspace too small");
-  CC_REQUIRE(tm * tn * d.split < (int64_t(1) << 31), -1, "gemm: too many tiles");
-  auto one = [&](const GemmDesc &g) {
+  lowp_parts(d, prec, tile_id, [&](const GemmDesc &g, int t) {
+    const LTile &ti = (prec == PREC_F32 ? kF32Tiles : kB3Tiles)[t];
     const int64_t gm = (g.M + ti.BM - 1) / ti.BM, gn = (g.N + ti.BN - 1) / ti.BN;
+    CC_REQUIRE(gm * gn * g.split < (int64_t(1) << 31), -1, "gemm: too many tiles");
     if (g.ladder == 2 && akc && bkc) ti.launch_ladder_tail(g, gm, gn, s);
     else if (g.ladder && akc && bkc) ti.launch_ladder(g, gm, gn, s);
     else ti.launch[(akc ? 2 : 0) + (bkc ? 1 : 0)](g, gm, gn, s);
     CC_HIP_CHECK(hipGetLastError());
     if (g.split > 1) splitk_reduce(false, g.ws, g.split, g.M, g.N, g.C, g.ldc, g.alpha, g.beta, s);
-  };
-  if (d.ws && d.split == 1) {
-    const TailCut tc = lowp_cut(d, prec, tile_id);
-    if (tc.axis && tc.ws_elems <= d.ws_elems) {
-      // operand element size: converted copies (4-byte FP32, 2-byte bf16
-      // planes) or the FP64 tensors themselves
-      const size_t es = d.lp_in ? (prec == PREC_F32 ? 4 : 2) : sizeof(double);
-      gemm_run_cut(d, tc, es, es, one);
-      return;
-    }
-  }
-  if (d.ws && d.split > 1 && d.ws_elems > 0) {
-    GemmDesc g = d;
-    g.split = gemm_split_refine(d.M, d.N, d.K, ti.BM, ti.BN, ti.BK, lowp_slots(d, prec, tile_id), d.split,
-                                d.ws_elems);
-    one(g);
-    return;
-  }
-  one(d);
+  });
 }
 
 int64_t gemm_lowp_tail_ws(const GemmDesc &d, int prec, int tile_id) {

@@ -813,7 +813,7 @@ void use_shadows_c(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s, bool 
 bool blocked_for(const cc_plan *p, const Step &st, int tile) {
   if (p->cur_prec != PREC_BF16X3 || st.blk_a < 0 || st.blk_b < 0 || st.blk_use == 0) return false;
   if (!p->bforms[st.blk_a].ptr || !p->bforms[st.blk_b].ptr) return false;
-  if (tile < 0) tile = gemm_lowp_pick(PREC_BF16X3, st.gemm.M, p->cplx ? 2 * st.gemm.N : st.gemm.N);
+  if (tile < 0) return gemm_b3_auto_blocked(st.gemm.M, p->cplx ? 2 * st.gemm.N : st.gemm.N);
   return gemm_lowp_tile_blocked(PREC_BF16X3, tile);
 }
 
@@ -963,7 +963,7 @@ void run_delta_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
   const int tile = st.tile_lp[p->delta_prec];
   if (p->delta_prec == PREC_BF16X3 && r.dblk && con_blk >= 0 && st.blk_use != 0 && p->bforms[con_blk].ptr &&
       p->bforms[con_blk].prec == PREC_BF16X3 &&
-      gemm_lowp_tile_blocked(PREC_BF16X3, tile >= 0 ? tile : gemm_lowp_pick(PREC_BF16X3, d.M, d.N))) {
+      (tile >= 0 ? gemm_lowp_tile_blocked(PREC_BF16X3, tile) : gemm_b3_auto_blocked(d.M, d.N))) {
     const BForm &cf = p->bforms[con_blk];
     const int64_t rows = r.n_op / d.K;
     convert_blocked(X, r.ref_op, rows, d.K, r.dblk, s);

@@ -49,3 +49,36 @@ def test_gemm_f64_direct_partial_chunks(ctx, monkeypatch, direct, staged, M, N, 
     ref = 0.5 * (A @ B.T) - 1.25 * C0
     bound = 2 * K * np.finfo(np.float64).eps * (0.5 * (np.abs(A) @ np.abs(B).T) + 1.25 * np.abs(C0))
     assert np.all(np.abs(out[1] - ref) <= bound + 1e-300)
+
+
+@pytest.mark.parametrize("prec,staged,direct", [("bf16x3", 6, 9), ("bf16x3", 6, 12), ("bf16x3", 6, 13),
+                                                ("f32", 7, 10), ("f32", 7, 11), ("f32", 7, 12), ("bf16x3", 6, -1),
+                                                ("f32", 7, -1)])
+# partial last chunks of 4, 8, 16 and 24, whole chunks; sizes below, at and
+# over a tile's edge.  K % 8 == 4 goes to the staged kernel in split bf16.
+@pytest.mark.parametrize("M,N,K", [(1, 1, 8), (63, 130, 40), (128, 128, 32), (130, 257, 72), (257, 64, 100),
+                                   (300, 270, 1000), (65, 700, 2016)])
+def test_gemm_lowp_direct_partial_chunks(ctx, monkeypatch, prec, staged, direct, M, N, K):
+    """Every reduced-precision kernel, and the library's own choice, adds the
+    same products in the same order: bit-identical results."""
+    from paper_2409_06759_amd import engine as E
+    print(f"direct {prec} tile {direct} M={M} N={N} K={K}", flush=True)
+    monkeypatch.setenv("CC_GEMM_TAIL", "0")
+    monkeypatch.setenv("CC_GEMM_BLOCKED", "0")
+    rng = np.random.default_rng(M + 5 * N + K)
+    A, B, C0 = rng.normal(size=(M, K)), rng.normal(size=(N, K)), rng.normal(size=(M, N))
+    Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    out = []
+    for t in (staged, direct):
+        if t >= 0:
+            monkeypatch.setenv("CC_GEMM_TILE", str(t))
+        else:
+            monkeypatch.delenv("CC_GEMM_TILE")
+        Cd = torch.from_numpy(C0).cuda()
+        E.gemm(ctx, Ad, Bd, Cd, 0.5, -1.25, prec=E.PRECS[prec])
+        out.append(Cd.cpu().numpy())
+    assert np.array_equal(out[0], out[1])
+    ref = 0.5 * (A @ B.T) - 1.25 * C0
+    eps = (K + 2) * 2.0 ** -24 + (3 * 2.0 ** -17 if prec == "bf16x3" else 0.0)
+    bound = 2 * eps * 0.5 * (np.abs(A) @ np.abs(B).T) + 4 * np.finfo(float).eps * np.abs(1.25 * C0)
+    assert np.all(np.abs(out[1] - ref) <= bound)
