@@ -142,7 +142,7 @@ struct cc_plan {
   std::vector<ccmi::Slot> slots;
   std::map<std::string, int> index;
   std::vector<ccmi::Step> setup, iter;
-  std::map<std::string, int> view_cache;  // (tensor, labels, conj, version) -> slot
+  std::map<std::string, int> view_cache;  // (tensor, order of its dimensions, conj, version) -> slot
   std::map<int, int> version;             // writes seen so far while planning
   std::map<int, bool> touched;            // first write of an iteration uses beta = 0
   size_t workspace = 0;
