@@ -97,10 +97,9 @@ int64_t batch_slot_elems(const cc_plan *p, int s) {
   return sl.name == "t1" ? int64_t(p->o) * p->v : int64_t(p->o) * p->o * p->v * p->v;
 }
 
-// the split-K factor a grouped launch of this step uses (FP64 real systems
-// have one of their own)
+// the split-K factor of this step's launches (FP64 has one of its own)
 int &split_of(const cc_batch *B, Step &st) {
-  return B->prec == PREC_F64 && !B->cplx ? st.split64 : st.gemm.split;
+  return B->prec == PREC_F64 ? st.split64 : st.gemm.split;
 }
 
 // (Re)build the device tables of every grouped step from the plans' current
@@ -387,7 +386,7 @@ void run_gstep(cc_batch *B, size_t k, hipStream_t s) {
         d.B = ptr_of(p, st.b);
         d.C = ptr_of(p, st.c);
         d.ws = st.b2 >= 0 ? ptr_of(p, st.b2) : nullptr;
-        if (cplx) gemm_c128(d, s, st.tile_z);
+        if (cplx) gemm_c128(gemm_f64_desc(st, d), s, st.tile_z);
         else if (B->prec == PREC_F64) gemm_f64(gemm_f64_desc(st, d), s, st.tile);
         else gemm_lowp(d, B->prec, s, st.tile_lp[B->prec]);
       } else if (st.kind == Step::PERMUTE) {

@@ -150,6 +150,8 @@ struct F64Choice {
   int tile, split;
 };
 F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems);
+// the same for the complex GEMM (ws_elems: complex elements)
+F64Choice gemm_c128_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems);
 // the split-K factor re-chosen for a forced tile (gemm_split_refine)
 int gemm_f64_refined_split(const GemmDesc &d, int tile_id, int64_t ws_elems);
 int gemm_split_pick(int64_t M, int64_t N, int64_t K, int tile_id);

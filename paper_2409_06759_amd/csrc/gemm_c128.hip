@@ -6,8 +6,8 @@
 // with separate real and imaginary accumulators (8 real flop per complex
 // multiply-add, the algorithmic count of the complex residual).  Tiles are
 // staged into planar real/imaginary LDS panels, double buffered; split-K and
-// the XCD-aware tile order follow the real FP64 kernel.  The 64x128x16
-// LDS-direct configuration loads K-contiguous operands straight into three
+// the XCD-aware tile order follow the real FP64 kernel.  The LDS-direct
+// configurations load K-contiguous operands straight into two or three
 // interleaved (re, im) LDS stages.  Conjugated operands
 // never reach this kernel: the contraction planner materialises them as
 // conjugated views.
@@ -187,31 +187,30 @@ __global__ __launch_bounds__(WM *WN *kWave) void gemm_c128_kernel(GemmDesc d, in
     }
 }
 
-// ---- 64x128x16 with LDS-direct loads ----------------------------------------
-// Both operands K-contiguous, K a multiple of 16 (the complex ladder's
-// layout).  Each lane's 16 bytes (one complex element) go straight into LDS
-// with global_load_lds_dwordx4: three 48 KiB stages, two chunks of K in
-// flight, no staging registers.  A 16-row block of a stage is four quarters
-// of 64 slots; slot L of quarter s holds element (row L & 15, k = 4 (L >> 4)
-// + s), the value lane L feeds the f64 MFMAs at step s (as in the staged
-// kernel), so each quarter is read contiguously across the wave.  Rows past
-// M or N load the last valid row instead: they only reach outputs that are
-// never stored.  The products and their order are those of the staged
-// 64x128 kernel, so results are bitwise the same.  Waits as in the real
-// LDS-direct kernel: "vmcnt <= 6" after the next chunk's six loads, a
-// barrier, and "lgkmcnt == 0" before it for the stage being overwritten.
-namespace zdma {
-constexpr int BM = 64, BN = 128, BK = 16, WM = 2, WN = 4, NT = WM * WN * kWave;
-constexpr int FM = BM / WM / 16, FN = BN / WN / 16;      // 2 x 2 blocks of 16x16 per wave
-constexpr int A_EL = BM * BK, B_EL = BN * BK, STAGE = A_EL + B_EL;  // complex elements
-constexpr int NSTAGE = 3;
-constexpr int LOADS = (4 * (BM / 16) + 4 * (BN / 16)) / (WM * WN);
-static_assert(LOADS == 6, "the explicit waits count six loads per chunk");
-}  // namespace zdma
+// ---- LDS-direct configurations (K chunk 16) ---------------------------------
+// Both operands K-contiguous (the complex ladder's layout).  Each lane's 16
+// bytes (one complex element) go straight into LDS with
+// global_load_lds_dwordx4: two or three stages, one or two chunks of K in
+// flight, no staging registers; elements past K load a zero in device memory.
+// A 16-row block of a stage is four quarters of 64 slots; slot L of quarter s
+// holds element (row L & 15, k = 4 (L >> 4) + s), the value lane L feeds the
+// f64 MFMAs at step s (as in the staged kernel), so each quarter is read
+// contiguously across the wave.  Rows past M or N load the last valid row
+// instead: they only reach outputs that are never stored.  The products and
+// their order are those of the staged kernels, so results are bitwise the
+// same.  Waits as in the real LDS-direct kernel: "vmcnt <= LOADS" after the
+// next chunk's loads, a barrier, and "lgkmcnt == 0" before it for the stage
+// being overwritten.
+__device__ __attribute__((aligned(16))) const double kZeroElement[2] = {0.0, 0.0};
 
-__global__ __launch_bounds__(zdma::NT) void gemm_c128_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
-  using namespace zdma;
-  __shared__ __attribute__((aligned(16))) double2 S[NSTAGE * STAGE];
+template <int BM, int BN, int WM, int WN, int NST>
+__global__ __launch_bounds__(WM *WN *kWave) void gemm_c128_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
+  constexpr int BK = 16, FM = BM / WM / 16, FN = BN / WN / 16;
+  constexpr int A_EL = BM * BK, STAGE = (BM + BN) * BK;  // complex elements
+  constexpr int LOADS = 4 * (BM / 16 + BN / 16) / (WM * WN);
+  static_assert(4 * (BM / 16 + BN / 16) % (WM * WN) == 0, "whole loads per wave");
+  static_assert(NST == 2 || NST == 3, "the explicit waits are written for one or two chunks in flight");
+  __shared__ __attribute__((aligned(16))) double2 S[NST * STAGE];
 
   const int64_t tiles = tilesM * tilesN, total = tiles * d.split;
   const int64_t L0 = xcd_remap(blockIdx.x, total);
@@ -224,30 +223,38 @@ __global__ __launch_bounds__(zdma::NT) void gemm_c128_dma_kernel(GemmDesc d, int
   const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
-  const int64_t nk = K / BK;
+  const int64_t nk = (K + BK - 1) / BK;
 
-  // load j of this wave (j = 6 wave + u): A (block j >> 2, quarter j & 3) for
-  // j < 16, else B (block (j - 16) >> 2, quarter j & 3); a block-quarter of A
-  // sits at elements (blk * 4 + quarter) * 64 of the stage, of B at A_EL + ...
+  // load j of this wave (j = LOADS wave + u): block j >> 2 of the stage (A
+  // before B), quarter j & 3; a block-quarter sits at elements
+  // (blk * 4 + quarter) * 64 of the stage
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(S));
   const double2 *src[LOADS];
   uint32_t dst[LOADS];
+  int kof[LOADS];
   const double2 *Ag = static_cast<const double2 *>(d.A) + kb;
   const double2 *Bg = static_cast<const double2 *>(d.B) + kb;
   const int wv = __builtin_amdgcn_readfirstlane(wave);  // wave-uniform, so the choice below is too
 #pragma unroll
   for (int u = 0; u < LOADS; ++u) {
-    const int j = LOADS * wv + u;
-    const bool isa = j < 4 * (BM / 16);
-    const int jj = isa ? j : j - 4 * (BM / 16), blk = jj >> 2, qt = jj & 3;
-    const int64_t lim = isa ? M : N, want = (isa ? m0 : n0) + blk * 16 + r;
+    const int j = LOADS * wv + u, blk = j >> 2;
+    const bool isa = blk < BM / 16;
+    const int64_t lim = isa ? M : N, want = isa ? m0 + blk * 16 + r : n0 + (blk - BM / 16) * 16 + r;
     const int64_t row = want < lim ? want : lim - 1;
-    src[u] = (isa ? Ag + row * d.sam : Bg + row * d.sbn) + 4 * q + qt;
-    dst[u] = __builtin_amdgcn_readfirstlane(lds0 + 16u * uint32_t((isa ? 0 : A_EL) + (blk * 4 + qt) * 64));
+    kof[u] = 4 * q + (j & 3);
+    src[u] = (isa ? Ag + row * d.sam : Bg + row * d.sbn) + kof[u];
+    dst[u] = __builtin_amdgcn_readfirstlane(lds0 + 16u * uint32_t(j * 64));
   }
   auto issue = [&](int stage, int64_t k0) {
+    if (k0 + BK <= K) {
 #pragma unroll
-    for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(16 * STAGE));
+      for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(16 * STAGE));
+    } else {  // the last, partial chunk: zeros past K
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u)
+        lds_load16(k0 + kof[u] < K ? static_cast<const void *>(src[u] + k0) : kZeroElement,
+                   dst[u] + uint32_t(stage) * uint32_t(16 * STAGE));
+    }
   };
 
   d4 acr[FM][FN], aci[FM][FN];
@@ -260,12 +267,12 @@ __global__ __launch_bounds__(zdma::NT) void gemm_c128_dma_kernel(GemmDesc d, int
     }
 
   if (nk > 0) issue(0, 0);
-  if (nk > 1) issue(1, BK);
-  int cur = 0, nxt = 2;
+  if (NST == 3 && nk > 1) issue(1, BK);
+  int cur = 0, nxt = NST - 1;
   for (int64_t kt = 0; kt < nk; ++kt) {
-    if (kt + 1 < nk) asm volatile("s_waitcnt vmcnt(6) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + 2 < nk) issue(nxt, (kt + 2) * BK);
+    if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
     const double2 *St = S + cur * STAGE;
     // steps 0-1 are read first and steps 2-3 behind the MFMAs of step 0, so
     // those reads overlap them (at most eight LDS reads in flight)
@@ -294,8 +301,8 @@ __global__ __launch_bounds__(zdma::NT) void gemm_c128_dma_kernel(GemmDesc d, int
         }
       if (s == 0) __builtin_amdgcn_sched_barrier(0);
     }
-    cur = cur == NSTAGE - 1 ? 0 : cur + 1;
-    nxt = nxt == NSTAGE - 1 ? 0 : nxt + 1;
+    cur = cur == NST - 1 ? 0 : cur + 1;
+    nxt = nxt == NST - 1 ? 0 : nxt + 1;
   }
 
   // epilogue (as the staged kernel): accumulator t of lane l is row (l >> 4) + 4t, column l & 15
@@ -331,7 +338,7 @@ __global__ __launch_bounds__(zdma::NT) void gemm_c128_dma_kernel(GemmDesc d, int
 }
 
 bool c128_dma_ok(const GemmDesc &d) {
-  return d.sak == 1 && d.sbk == 1 && d.K % zdma::BK == 0 && (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 &&
+  return d.sak == 1 && d.sbk == 1 && d.K > 0 && (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 &&
          (reinterpret_cast<uintptr_t>(d.B) & 15) == 0;
 }
 
@@ -354,30 +361,86 @@ void launch_z(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
          &launch_z<BM, BN, BK, WM, WN, true, false>, &launch_z<BM, BN, BK, WM, WN, true, true>}   \
   }
 
+template <int BM, int BN, int WM, int WN, int NST>
 void launch_z_dma(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
   if (c128_dma_ok(d))
-    hipLaunchKernelGGL(gemm_c128_dma_kernel, dim3(tm * tn * d.split), dim3(zdma::NT), 0, s, d, tm, tn);
+    hipLaunchKernelGGL((gemm_c128_dma_kernel<BM, BN, WM, WN, NST>), dim3(tm * tn * d.split), dim3(WM * WN * kWave), 0,
+                       s, d, tm, tn);
   else
-    launch_z<64, 128, 16, 2, 2, true, true>(d, tm, tn, s);
+    launch_z<BM, BN, 16, WM, WN, true, true>(d, tm, tn, s);
 }
+
+// LDS-direct where the layout allows, else the staged kernel of the tile
+#define CC_ZTILE_DMA(BM, BN, WM, WN, NST, NAME)                                                   \
+  ZTile {                                                                                         \
+    #BM "x" #BN "x16_w" #WM "x" #WN NAME, BM, BN, 16,                                             \
+        {&launch_z<BM, BN, 16, WM, WN, false, false>, &launch_z<BM, BN, 16, WM, WN, false, true>, \
+         &launch_z<BM, BN, 16, WM, WN, true, false>, &launch_z_dma<BM, BN, WM, WN, NST>}          \
+  }
 
 const ZTile kZTiles[] = {CC_ZTILE(64, 64, 16, 2, 2), CC_ZTILE(32, 32, 16, 2, 2), CC_ZTILE(128, 64, 16, 2, 2),
                          CC_ZTILE(64, 128, 16, 2, 2),
-                         // 64x128x16 with LDS-direct loads where the layout allows, else staged
-                         ZTile{"64x128x16_w2x4_lds",
-                               64,
-                               128,
-                               16,
-                               {&launch_z<64, 128, 16, 2, 2, false, false>, &launch_z<64, 128, 16, 2, 2, false, true>,
-                                &launch_z<64, 128, 16, 2, 2, true, false>, &launch_z_dma}}};
+                         CC_ZTILE_DMA(64, 128, 2, 4, 3, "_lds"),
+                         CC_ZTILE_DMA(64, 64, 4, 2, 2, "_lds2"),
+                         CC_ZTILE_DMA(32, 32, 2, 2, 2, "_lds2")};
 constexpr int kNumZ = sizeof(kZTiles) / sizeof(kZTiles[0]);
+
+// The same kind of model as the real FP64 one (f64_model_us), fitted to the
+// timings of every configuration and split-K factor on the 139 GEMM shapes of
+// complex CCSD at o = 4..20, v = 20..90: on them its choice is 1.3% slower
+// than the fastest, and 1.33 times faster than the rule it replaced (rounds of
+// 512 workgroups x tile area over a split chosen for 64 x 64 tiles):
+// 1600 x 8000 x 8000 17.1 -> 12.4 ms, 256 x 6400 x 6400 1.55 -> 1.33 ms,
+// 1280^3 359 -> 291 us.
+constexpr int kZBig = 5, kZSmall = 6;  // 64x64 and 32x32 (LDS-direct, or their staged kernels)
+// per operand form (0: M/N-contiguous, 1: LDS-direct): MFMA share of the 64x64
+// and the 32x32 tile, cycles of one chunk alone, cycles per workgroup set
+// (fixed; per 1,024 outputs), HBM TB/s, microseconds and TB/s of the partial
+// sums, share of the shorter time that is not hidden
+constexpr double kZConst[2][9] = {{0.80, 0.70, 2493, 32, 595, 5.28, 4.94, 13.5, 0.35},
+                                  {0.77, 0.71, 1584, 353, 60, 8.09, 3.02, 8.7, 0.23}};
+
+double c128_model_us(int tile, int form, int64_t M, int64_t N, int64_t K, int64_t split) {
+  const ZTile &ti = kZTiles[tile];
+  const double *c = kZConst[form];
+  const bool big = tile == kZBig;
+  const int64_t n = ((K + split - 1) / split + 15) / 16;
+  const double area = double(ti.BM) * ti.BN;
+  const double wgs = double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN) * double(split);
+  const double w = std::ceil(wgs / 256.0), conc = std::min(w, big ? 2.0 : form ? 5.0 : 4.0);
+  const double chunk = std::max(conc * area / c[big ? 0 : 1], c[2]);
+  const double mfma = (w / conc) * (double(n) * chunk + c[3] + c[4] * area / 1024.0 * conc) / 2400.0;
+  const double mem = (double(M) * K + double(N) * K + (split == 1 ? 2.0 * double(M) * N : 0.0)) * 16.0 / c[5] * 1e-6;
+  const double red = split > 1 ? c[6] + 32.0 * double(split) * double(M) * N / c[7] * 1e-6 : 0.0;
+  return 3.0 + std::max(mfma, mem) + c[8] * std::min(mfma, mem) + red;
+}
 
 }  // namespace
 
 int gemm_c128_num_tiles() { return kNumZ; }
 const char *gemm_c128_tile_name(int id) { return (id >= 0 && id < kNumZ) ? kZTiles[id].name : "?"; }
 
-void gemm_c128(const GemmDesc &d, hipStream_t s, int tile_id) {
+F64Choice gemm_c128_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems) {
+  static constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512};
+  F64Choice best{kZSmall, 1};
+  double best_us = 1e300;
+  for (int t : {kZBig, kZSmall}) {
+    const ZTile &ti = kZTiles[t];
+    const int64_t tiles = ((M + ti.BM - 1) / ti.BM) * ((N + ti.BN - 1) / ti.BN);
+    for (int s : kSplits) {
+      if (s > 1 && (int64_t(s) * 64 > K || tiles * s > 4096 || int64_t(s) * M * N > ws_elems)) break;
+      const double us = c128_model_us(t, lds_direct ? 1 : 0, M, N, K, s);
+      if (us < best_us) {
+        best_us = us;
+        best = F64Choice{t, s};
+      }
+    }
+  }
+  return best;
+}
+
+void gemm_c128(const GemmDesc &d0, hipStream_t s, int tile_id) {
+  GemmDesc d = d0;
   if (d.M <= 0 || d.N <= 0) return;
   const bool akc = (d.sak == 1), bkc = (d.sbk == 1);
   CC_REQUIRE(akc || d.sam == 1, -1, "gemm: A needs a unit stride in m or k");
@@ -397,17 +460,10 @@ void gemm_c128(const GemmDesc &d, hipStream_t s, int tile_id) {
     return;
   }
   if (tile_id < 0 || tile_id >= kNumZ) {
-    // fewest rounds of resident workgroups, then the larger tile
-    double best_cost = 1e300;
-    for (int t = 0; t < kNumZ; ++t) {
-      const double n = double((d.M + kZTiles[t].BM - 1) / kZTiles[t].BM) *
-                       double((d.N + kZTiles[t].BN - 1) / kZTiles[t].BN);
-      const double cost = std::ceil(n * d.split / 512.0) * (double(kZTiles[t].BM) * kZTiles[t].BN + 2048.0);
-      if (cost < best_cost) {
-        best_cost = cost;
-        tile_id = t;
-      }
-    }
+    const F64Choice ch = gemm_c128_choose(
+        d.M, d.N, d.K, c128_dma_ok(d), d.split > 1 && d.ws ? (d.ws_elems > 0 ? d.ws_elems : d.split * d.M * d.N) : 0);
+    tile_id = ch.tile;
+    d.split = ch.split;
   }
   const ZTile &ti = kZTiles[tile_id];
   const int64_t tm = (d.M + ti.BM - 1) / ti.BM, tn = (d.N + ti.BN - 1) / ti.BN;

@@ -354,7 +354,7 @@ struct Planner {
   // Split-K partial sums, or room for the K-split tail of a launch whose last
   // round of workgroups would be mostly empty (real GEMMs only).
   void reserve_ws(Step &g, int64_t M, int64_t N, int64_t K) {
-    const int64_t smax = p->cplx ? g.gemm.split : std::max(g.gemm.split, g.split64);
+    const int64_t smax = std::max(g.gemm.split, g.split64);
     const int64_t split = smax > 1 ? smax * M * N : 0;
     // complex: room for the tail of the realified M x 2N x 2K reduced-precision
     // GEMM, in complex elements
@@ -369,12 +369,16 @@ struct Planner {
     }
   }
 
-  // Split-K factors, and for real systems the FP64 tile with its own factor
-  // (partial sums of at most 2^24 elements, as gemm_split_pick's).
+  // Split-K factors, and the FP64 tile with its own factor (partial sums of at most 2^24 elements, as gemm_split_pick's).
   void choose_split(Step &g) {
     const GemmDesc &d = g.gemm;
     g.gemm.split = gemm_split_pick(d.M, d.N, d.K, -1);
-    if (p->cplx) return;
+    if (p->cplx) {
+      const F64Choice ch = gemm_c128_choose(d.M, d.N, d.K, d.sak == 1 && d.sbk == 1, int64_t(1) << 24);
+      g.tile_z = ch.tile;
+      g.split64 = ch.split;
+      return;
+    }
     const bool direct = d.sak == 1 && d.sbk == 1 && d.K % 2 == 0 && d.sam % 2 == 0 && d.sbn % 2 == 0;
     const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, direct, int64_t(1) << 24);
     g.tile = ch.tile;
@@ -1083,7 +1087,7 @@ void use_blocked(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s, bool co
 void run_f64(const GemmDesc &d, const Step &st, hipStream_t s) { gemm_f64(gemm_f64_desc(st, d), s, st.tile); }
 
 void run_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
-  if (p->cplx && (p->cur_prec == PREC_F64 || !st.lowp_ok)) gemm_c128(d, s, st.tile_z);
+  if (p->cplx && (p->cur_prec == PREC_F64 || !st.lowp_ok)) gemm_c128(gemm_f64_desc(st, d), s, st.tile_z);
   else if (p->cplx) {
     const int tile = st.tile_lp[p->cur_prec];
     if (blocked_for(p, st, tile)) use_blocked(p, d, st, s, true);
@@ -1161,7 +1165,7 @@ void run_delta_gemm(cc_plan *p, GemmDesc &d, const Step &st, hipStream_t s) {
     g.C = r.ref_out;
     g.ldc = d.N;
     g.beta = 0.0;
-    if (p->cplx) gemm_c128(g, s, st.tile_z);
+    if (p->cplx) gemm_c128(gemm_f64_desc(st, g), s, st.tile_z);
     else run_f64(g, st, s);
     add_product(C, w * d.ldc, d.beta, r.ref_out, d.M, w * d.N, s);
     return;
@@ -1767,7 +1771,7 @@ void plan_autotune(cc_plan *p, int reps) {
       int best = slot, best_blk = 0;
       float best_ms = 1e30f;
       auto launch = [&](int t, int b) {
-        if (cz) gemm_c128(d, s, t);
+        if (cz) gemm_c128(gemm_f64_desc(*st, d), s, t);
         else if (prec == PREC_F64) {
           GemmDesc g = d;
           g.split = f64_split(t);
@@ -1866,7 +1870,7 @@ std::string plan_describe(const cc_plan *p) {
              << " M=" << st.gemm.M << " N=" << st.gemm.N << " K=" << st.gemm.K << " sam=" << st.gemm.sam
              << " sak=" << st.gemm.sak << " sbn=" << st.gemm.sbn << " sbk=" << st.gemm.sbk
              << " ldc=" << st.gemm.ldc << " alpha=" << st.gemm.alpha << " beta=" << st.gemm.beta
-             << " split=" << (p->cplx || (p->cur_prec != PREC_F64 && st.lowp_ok) ? st.gemm.split : st.split64)
+             << " split=" << (p->cur_prec != PREC_F64 && st.lowp_ok ? st.gemm.split : st.split64)
              << " tile=" << (st.tile >= 0 ? gemm_f64_tile_name(st.tile) : "auto") << "\n";
           break;
         case Step::OUTER:

@@ -82,3 +82,24 @@ def test_gemm_lowp_direct_partial_chunks(ctx, monkeypatch, prec, staged, direct,
     eps = (K + 2) * 2.0 ** -24 + (3 * 2.0 ** -17 if prec == "bf16x3" else 0.0)
     bound = 2 * eps * 0.5 * (np.abs(A) @ np.abs(B).T) + 4 * np.finfo(float).eps * np.abs(1.25 * C0)
     assert np.all(np.abs(out[1] - ref) <= bound)
+
+
+@pytest.mark.parametrize("direct", [4, 5, 6])
+# any K: below, at and over a chunk; sizes below, at and over a tile's edge
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 130, 13), (64, 64, 16), (65, 31, 17), (32, 129, 47), (130, 70, 500)])
+def test_gemm_c128_direct_partial_chunks(ctx, monkeypatch, direct, M, N, K):
+    from paper_2409_06759_amd import engine as E
+    print(f"direct c128 tile {direct} M={M} N={N} K={K}", flush=True)
+    rng = np.random.default_rng(M + 5 * N + K)
+    A, B, C0 = (rng.normal(size=s) + 1j * rng.normal(size=s) for s in ((M, K), (N, K), (M, N)))
+    Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    out = []
+    for t in (0, direct):
+        monkeypatch.setenv("CC_GEMM_TILE", str(t))
+        Cd = torch.from_numpy(C0).cuda()
+        E.gemm(ctx, Ad, Bd, Cd, 0.5, -1.25)
+        out.append(Cd.cpu().numpy())
+    assert np.array_equal(out[0], out[1])
+    ref = 0.5 * (A @ B.T) - 1.25 * C0
+    bound = 8 * K * np.finfo(np.float64).eps * (0.5 * (np.abs(A) @ np.abs(B).T) + 1.25 * np.abs(C0))
+    assert np.all(np.abs(out[1] - ref) <= bound)
