@@ -510,9 +510,15 @@ void batch_autotune(cc_batch *B, int reps) {
     for (size_t k = 0; k < B->gsteps.size(); ++k) {
       if (B->gsteps[k].kind != Step::GEMM || !B->gsteps[k].grouped) continue;
       int best = B->gsteps[k].tile;
+      const int first = best;
+      bool split = false;
+      for (cc_plan *p : B->plans) split = split || split_of(B, p->iter[k]) > 1;
       float best_ms = 1e30f;
       for (int t = 0; t < ntiles; ++t) {
         if (prec != PREC_F64 && !gemm_lowp_tile_grouped(prec, t)) continue;
+        // reduced-precision sums depend on where the K slices of a split lie,
+        // which a tile of another K chunk would move
+        if (prec != PREC_F64 && split && gemm_lowp_tile_chunk(prec, t) != gemm_lowp_tile_chunk(prec, first)) continue;
         for (cc_plan *p : B->plans) tile_of(p->iter[k]) = t;
         build_tables(B);
         run_gstep(B, k, s);

@@ -1552,6 +1552,8 @@ bool gemm_lowp_tile_grouped(int prec, int tile_id) {
          (prec == PREC_F32 ? kF32Tiles : kB3Tiles)[tile_id].launch_grouped_lp != nullptr;
 }
 
+int gemm_lowp_tile_chunk(int prec, int tile_id) { return (prec == PREC_F32 ? kF32Tiles : kB3Tiles)[tile_id].BK; }
+
 void gemm_lowp_tile_shape(int prec, int tile_id, int *bm, int *bn) {
   const LTile &t = (prec == PREC_F32 ? kF32Tiles : kB3Tiles)[tile_id];
   *bm = t.BM;
