@@ -95,7 +95,8 @@ struct AsmEntry {
 struct R1Entry {
   int o, v;
   const void *R1;
-  void *t1;  // nullptr: no update
+  void *t1;   // nullptr: no update
+  void *out;  // copy of R1 (may be nullptr)
   const double *d_oo, *d_vv;
   double shift;
   int dressed;
@@ -171,6 +172,29 @@ void launch_t3(const T3Entry &e, bool cplx, hipStream_t s);
 void launch_pair(const PairEntry &e, bool cplx, hipStream_t s);
 void launch_r1(const R1Entry &e, bool cplx, hipStream_t s);
 void launch_fin(const FinEntry &e, hipStream_t s);
+void launch_asm_r1(const AsmEntry &e, const R1Entry &r, hipStream_t s);  // both steps, real
+
+// ---- merged launches -----------------------------------------------------------
+// One launch runs independent steps of small real systems: item b owns
+// workgroups [off[b], off[b+1]) and holds the entry of its kind.  A pointer of
+// value 1, 2 or 3 in an entry stands for the t1, t2 or t3 given at the launch.
+struct LevelItem {
+  enum Kind { PERM_FLAT, PERM_TILED, OUTER, FILL, SPLITK, TAU, PAIR, GEMM_MN, GEMM_MK, GEMM_KN, GEMM_KK };
+  int kind, pad = 0;
+  alignas(16) unsigned char u[sizeof(PermEntry)];
+  template <class E> void set(Kind k, const E &e) {
+    static_assert(sizeof(E) <= sizeof(u), "entry size");
+    kind = k;
+    __builtin_memcpy(u, &e, sizeof(E));
+  }
+};
+constexpr int kLevelItems = 64;  // per launch
+struct LevelExt {
+  void *t1, *t2, *t3;
+};
+constexpr int kLevelTile = 32;  // GEMM tile edge (tiles of the merged launches)
+bool gemm_f64_tile_merged(int tile_id);
+void launch_level(const LevelItem *items, const int *off, int n, int blocks, const LevelExt &ext, hipStream_t s);
 
 // ---- grouped launches (entries and offsets in device memory) -----------------
 void launch_perm_grouped(const PermEntry *e, const int64_t *off, int n, int64_t blocks, bool tiled, bool cplx,

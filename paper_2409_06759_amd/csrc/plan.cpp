@@ -344,6 +344,11 @@ struct TriplesMerger {
   }
 };
 
+// Merged launches: real FP64 systems of at most this many doubles amplitudes, and
+// the partial sums of one of their steps.  Every GEMM has buffers of its own, so
+// the bound keeps them to tens of MB.
+constexpr int64_t kMergeAmps = int64_t(1) << 20, kMergeWork = int64_t(1) << 21;
+
 struct Planner {
   cc_plan *p;
   int scratch = -1;        // shared buffer for GEMM outputs that need a permute
@@ -369,6 +374,10 @@ struct Planner {
     }
   }
 
+  bool small() const {
+    return !p->cplx && p->prec == PREC_F64 && int64_t(p->o) * p->o * p->v * p->v <= kMergeAmps;
+  }
+
   // Split-K factors, and the FP64 tile with its own factor (partial sums of at most 2^24 elements, as gemm_split_pick's).
   void choose_split(Step &g) {
     const GemmDesc &d = g.gemm;
@@ -383,6 +392,16 @@ struct Planner {
     const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, direct, int64_t(1) << 24);
     g.tile = ch.tile;
     g.split64 = ch.split;
+    if (small()) {
+      // (a batch, whose launches group one step of all its systems, takes the
+      // factor, so that its systems' results stay those of their own plans)
+      const F64Choice own = gemm_f64_choose_merged(d.M, d.N, d.K, direct, kMergeWork);
+      g.split64 = own.split;
+      if (p->merge) {
+        g.tile = own.tile;
+        g.gemm.split = own.split;
+      }
+    }
   }
 
   int slot(const std::string &name) {
@@ -807,6 +826,8 @@ struct Planner {
 
   void build(const cc_system *sys) {
     const bool ccsd = p->method == CC_CCSD;
+    p->merge = small() && !p->lowp_all && !p->private_work;
+    if (p->merge) p->private_work = true;
     const char *inputs[] = {"foo", "fov", "fvv", "oooo", "ooov", "oovv", "ovvo", "ovvv", "vvvv"};
     const char *spaces[] = {"oo", "ov", "vv", "oooo", "ooov", "oovv", "ovvo", "ovvv", "vvvv"};
     const void *ptrs[] = {sys->f_oo, sys->f_ov, sys->f_vv, sys->oooo, sys->ooov,
@@ -1347,8 +1368,8 @@ AsmEntry asm_entry(cc_plan *p) {
 }
 
 R1Entry r1_entry(cc_plan *p) {
-  return R1Entry{p->o, p->v, p->slots[p->index["R1"]].ptr, p->update ? p->t1 : nullptr, p->d_oo, p->d_vv,
-                 p->shift, p->dressed, p->slots[p->index["Fmi"]].ptr, p->slots[p->index["Fae"]].ptr,
+  return R1Entry{p->o, p->v, p->slots[p->index["R1"]].ptr, p->update ? p->t1 : nullptr, p->r1_out, p->d_oo,
+                 p->d_vv, p->shift, p->dressed, p->slots[p->index["Fmi"]].ptr, p->slots[p->index["Fae"]].ptr,
                  p->n1part};
 }
 
@@ -1404,14 +1425,9 @@ void exec(cc_plan *p, Step &st, hipStream_t s) {
     case Step::ASSEMBLE:
       launch_asm(asm_entry(p), cplx, s);
       break;
-    case Step::R1UPD: {
-      void *R1 = p->slots[p->index["R1"]].ptr;
-      if (p->r1_out)
-        CC_HIP_CHECK(hipMemcpyAsync(p->r1_out, R1, size_t(p->o) * p->v * p->esize,
-                                    hipMemcpyDeviceToDevice, s));
+    case Step::R1UPD:
       launch_r1(r1_entry(p), cplx, s);
       break;
-    }
     case Step::FINALIZE:
       launch_fin(fin_entry(p), s);
       break;
@@ -1422,9 +1438,211 @@ void exec(cc_plan *p, Step &st, hipStream_t s) {
                   cplx, s);
       break;
     case Step::TRIPLES:
-      CC_REQUIRE(p->t3 != nullptr, CC_EINVAL, "triples amplitudes not bound (cc_plan_set_triples)");
       launch_t3(t3_entry(p), cplx, s);
       break;
+  }
+}
+
+}  // namespace
+
+namespace {
+
+// What a step reads and writes, as slots (a merged launch may hold no two
+// steps of which one writes what the other reads or writes).
+void step_access(const cc_plan *p, const Step &st, std::vector<int> &rd, std::vector<int> &wr) {
+  rd.clear();
+  wr.clear();
+  if (st.kind == Step::TAU_E) {
+    for (const char *x : {"t1", "t2", "oovv", "fov"}) rd.push_back(p->index.at(x));
+    if (p->method == CC_CCSD)
+      for (const char *x : {"tau", "taut"}) wr.push_back(p->index.at(x));
+    return;
+  }
+  for (int x : {st.a, st.b, st.c})
+    if (x >= 0) rd.push_back(x);
+  wr.push_back(st.c);
+}
+
+const void *level_ptr(cc_plan *p, int slot) {
+  const Slot &sl = p->slots[slot];
+  if (!sl.external) return sl.ptr;
+  return reinterpret_cast<const void *>(uintptr_t(sl.name == "t1" ? 1 : sl.name == "t2" ? 2 : 3));
+}
+
+}  // namespace
+
+// Dependency levels of the iteration and the items of their merged launches
+// (level of a step: one past the latest step it has to follow; the partial
+// products of a split GEMM and their sum are two levels).
+void plan_levels(cc_plan *p) {
+  if (!p->merge) return;
+  p->levels.clear();
+  struct Op {
+    int step = -1;  // not merged
+    int level = 0;
+    int64_t units = 0, weight = 0;
+    LevelItem item;
+  };
+  std::vector<Op> ops;
+  std::vector<int> last_write(p->slots.size(), 0), last_read(p->slots.size(), 0), rd, wr;
+  size_t i = 0;
+  for (; i < p->iter.size(); ++i) {
+    const Step &st = p->iter[i];
+    if (st.kind == Step::ASSEMBLE || st.kind == Step::R1UPD || st.kind == Step::TRIPLES || st.kind == Step::FINALIZE)
+      break;
+    Op op, red;
+    auto in = [&](int x) { return level_ptr(p, x); };
+    auto out = [&](int x) { return const_cast<void *>(level_ptr(p, x)); };
+    switch (st.kind) {
+      case Step::PERMUTE: {
+        const PermEntry e = make_perm_entry(st.perm, in(st.a), out(st.c));
+        op.units = e.units;
+        op.item.set(e.tiled ? LevelItem::PERM_TILED : LevelItem::PERM_FLAT, e);
+        break;
+      }
+      case Step::OUTER: {
+        const OuterEntry e = make_outer_entry(st.outer, in(st.a), in(st.b), out(st.c));
+        op.units = e.units;
+        op.item.set(LevelItem::OUTER, e);
+        break;
+      }
+      case Step::FILL: {
+        const FillEntry e = make_fill_entry(ptr_of(p, st.c), st.nelem);
+        op.units = e.units;
+        op.item.set(LevelItem::FILL, e);
+        break;
+      }
+      case Step::PAIR: {
+        const PairEntry e =
+            make_pair_entry(in(st.a), out(st.c), p->pair_tab[st.pair_rows], p->pair_tab[st.pair_cols], st.pair_np,
+                            st.pair_nq, st.pair_ldq, st.pair_n[0], st.pair_n[1], st.pair_n[2], st.pair_mode);
+        op.units = e.units;
+        op.item.set(LevelItem::PAIR, e);
+        break;
+      }
+      case Step::TAU_E: {
+        const bool ccsd = p->method == CC_CCSD;
+        auto sl = [&](const char *x) { return level_ptr(p, p->index.at(x)); };
+        const TauEntry e = make_tau_entry(p->o, p->v, ccsd ? sl("t1") : nullptr, sl("t2"), sl("oovv"), sl("fov"),
+                                          ccsd ? const_cast<void *>(sl("tau")) : nullptr,
+                                          ccsd ? const_cast<void *>(sl("taut")) : nullptr, p->epart);
+        op.units = e.units;
+        op.weight = 1;
+        op.item.set(LevelItem::TAU, e);
+        break;
+      }
+      default: {  // GEMM
+        const GemmDesc &g = st.gemm;
+        if (!gemm_f64_tile_merged(st.tile) || g.M <= 0 || g.N <= 0 || g.K <= 0 || p->slots[st.c].external ||
+            (g.sak != 1 && g.sam != 1) || (g.sbk != 1 && g.sbn != 1)) {
+          op.step = int(i);
+          break;
+        }
+        GemmGroupEntry e{gemm_f64_desc(st, g), (g.M + kLevelTile - 1) / kLevelTile, (g.N + kLevelTile - 1) / kLevelTile};
+        e.d.A = in(st.a);
+        e.d.B = in(st.b);
+        e.d.C = ptr_of(p, st.c);
+        e.d.ws = st.b2 >= 0 ? ptr_of(p, st.b2) : nullptr;
+        e.d.ws_elems = st.b2 >= 0 ? p->slots[st.b2].elems : 0;
+        CC_REQUIRE(e.d.split == 1 || (e.d.ws && e.d.ws_elems >= e.d.split * g.M * g.N), CC_EINTERNAL,
+                   "merged launch: split-K workspace");
+        op.units = e.tilesM * e.tilesN * e.d.split;
+        op.weight = 2 + g.K / e.d.split;
+        op.item.set(g.sak == 1 ? (g.sbk == 1 ? LevelItem::GEMM_KK : LevelItem::GEMM_KN)
+                               : (g.sbk == 1 ? LevelItem::GEMM_MK : LevelItem::GEMM_MN),
+                    e);
+        if (e.d.split > 1) {
+          const SplitkEntry r =
+              make_splitk_entry(e.d.ws, e.d.split, g.M, g.N, e.d.C, g.ldc, g.alpha, g.beta);
+          red.units = r.units;
+          red.item.set(LevelItem::SPLITK, r);
+        }
+      }
+    }
+    step_access(p, st, rd, wr);
+    int lev = 0;
+    if (red.units > 0) {  // partial products into the step's own workspace, then their sum into C
+      for (int x : {st.a, st.b}) lev = std::max(lev, last_write[x]);
+      op.level = ++lev;
+      for (int x : {st.a, st.b}) last_read[x] = std::max(last_read[x], lev);
+      ops.push_back(op);
+      lev = std::max({lev, last_write[st.c], last_read[st.c]});
+      red.level = ++lev;
+      last_read[st.c] = last_write[st.c] = lev;
+      ops.push_back(red);
+      continue;
+    }
+    for (int x : rd) lev = std::max(lev, last_write[x]);
+    for (int x : wr) lev = std::max({lev, last_write[x], last_read[x]});
+    op.level = ++lev;
+    for (int x : rd) last_read[x] = std::max(last_read[x], lev);
+    for (int x : wr) last_write[x] = lev;
+    if (op.step >= 0 || op.units > 0) ops.push_back(op);
+  }
+  p->level_tail = i;
+  for (; i < p->iter.size(); ++i) {
+    const Step::Kind k = p->iter[i].kind;
+    CC_REQUIRE(k == Step::ASSEMBLE || k == Step::R1UPD || k == Step::TRIPLES || k == Step::FINALIZE, CC_EINTERNAL,
+               "merged launches: order of the steps");
+  }
+  // by level; within one the longest workgroups first, steps of their own last
+  std::stable_sort(ops.begin(), ops.end(), [](const Op &x, const Op &y) {
+    if (x.level != y.level) return x.level < y.level;
+    if ((x.step >= 0) != (y.step >= 0)) return x.step < 0;
+    return x.weight > y.weight;
+  });
+  std::vector<LevelItem> items;
+  std::vector<int> off;
+  int cur = -1;
+  for (const Op &op : ops) {
+    if (op.step >= 0) {
+      p->levels.push_back({op.step, 0, 0, 0, 0});
+      cur = -1;
+      continue;
+    }
+    if (cur < 0 || op.level != cur || p->levels.back().n == kLevelItems ||
+        p->levels.back().blocks + op.units >= (int64_t(1) << 30)) {
+      CC_REQUIRE(op.units < (int64_t(1) << 30), CC_EINTERNAL, "merged launch: too many workgroups");
+      p->levels.push_back({-1, int(items.size()), 0, int(off.size()), 0});
+      cur = op.level;
+    }
+    auto &L = p->levels.back();
+    items.push_back(op.item);
+    off.push_back(L.blocks);
+    L.n += 1;
+    L.blocks += int(op.units);
+  }
+  if (items.empty()) return;
+  std::vector<unsigned char> tab(items.size() * sizeof(LevelItem) + off.size() * sizeof(int));
+  std::memcpy(tab.data(), items.data(), items.size() * sizeof(LevelItem));
+  std::memcpy(tab.data() + items.size() * sizeof(LevelItem), off.data(), off.size() * sizeof(int));
+  hipStream_t s = p->ctx->stream;
+  CC_HIP_CHECK(hipStreamSynchronize(s));  // launches that read the table before
+  if (p->level_tab) (void)hipFree(p->level_tab);
+  p->level_tab = nullptr;
+  p->level_tab = dev_alloc(tab.size());
+  p->level_items = items.size();
+  CC_HIP_CHECK(hipMemcpyAsync(p->level_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, s));
+  CC_HIP_CHECK(hipStreamSynchronize(s));
+}
+
+namespace {
+
+void run_levels(cc_plan *p, hipStream_t s) {
+  const LevelItem *items = static_cast<const LevelItem *>(p->level_tab);
+  const int *off = reinterpret_cast<const int *>(items + p->level_items);
+  const LevelExt ext{p->t1, p->t2, p->t3};
+  for (const auto &L : p->levels) {
+    if (L.step >= 0) exec(p, p->iter[L.step], s);
+    else launch_level(items + L.first, off + L.off, L.n, L.blocks, ext, s);
+  }
+  for (size_t i = p->level_tail; i < p->iter.size(); ++i) {
+    if (p->iter[i].kind == Step::ASSEMBLE && i + 1 < p->iter.size() && p->iter[i + 1].kind == Step::R1UPD) {
+      launch_asm_r1(asm_entry(p), r1_entry(p), s);
+      ++i;
+      continue;
+    }
+    exec(p, p->iter[i], s);
   }
 }
 
@@ -1487,25 +1705,39 @@ void plan_layout(cc_plan *p, const cc_system *sys) {
 
 void plan_build(cc_plan *p, const cc_system *sys) {
   plan_layout(p, sys);
-  // allocate owned slots
-  for (Slot &s : p->slots) {
-    if (!s.owned) continue;
-    const size_t bytes = size_t(std::max<int64_t>(s.elems, 1)) * p->esize;
-    s.ptr = dev_alloc(bytes);
-    p->workspace += bytes;
-  }
+  // owned slots and the small arrays, in one allocation (a plan has about a
+  // hundred of them, and each allocation takes 5 to 10 us)
   p->n_epart = int(tau_units(p->o, p->v));
   p->n_n2part = int(asm_units(p->o, p->v));
-  p->d_oo = static_cast<double *>(dev_alloc(sizeof(double) * p->o));
-  p->d_vv = static_cast<double *>(dev_alloc(sizeof(double) * p->v));
-  p->epart = static_cast<double *>(dev_alloc(sizeof(double) * 2 * p->n_epart));
-  p->n2part = static_cast<double *>(dev_alloc(sizeof(double) * p->n_n2part));
-  p->n1part = static_cast<double *>(dev_alloc(sizeof(double) * 2));
-  if (p->triples) {
-    p->n_n3part = int(t3_units(p->o, p->v));
-    p->n3part = static_cast<double *>(dev_alloc(sizeof(double) * p->n_n3part));
+  p->n_n3part = p->triples ? int(t3_units(p->o, p->v)) : 0;
+  size_t total = 0;
+  auto room = [&total](size_t bytes) {
+    const size_t at = total;
+    total += (bytes + 255) / 256 * 256;
+    return at;
+  };
+  std::vector<size_t> at(p->slots.size(), 0);
+  for (size_t i = 0; i < p->slots.size(); ++i) {
+    const Slot &s = p->slots[i];
+    if (!s.owned) continue;
+    const size_t bytes = size_t(std::max<int64_t>(s.elems, 1)) * p->esize;
+    at[i] = room(bytes);
+    p->workspace += bytes;
   }
-  p->scalars = static_cast<double *>(dev_alloc(sizeof(double) * 4));
+  const struct {
+    double **ptr;
+    size_t n;
+  } arrays[] = {{&p->d_oo, size_t(p->o)},       {&p->d_vv, size_t(p->v)},       {&p->epart, size_t(2) * p->n_epart},
+                {&p->n2part, size_t(p->n_n2part)}, {&p->n1part, 2},             {&p->n3part, size_t(p->n_n3part)},
+                {&p->scalars, 4}};
+  size_t aat[7];
+  for (int k = 0; k < 7; ++k) aat[k] = room(sizeof(double) * arrays[k].n);
+  p->mem = dev_alloc(total);
+  char *base = static_cast<char *>(p->mem);
+  for (size_t i = 0; i < p->slots.size(); ++i)
+    if (p->slots[i].owned) p->slots[i].ptr = base + at[i];
+  for (int k = 0; k < 7; ++k)
+    if (arrays[k].n) *arrays[k].ptr = reinterpret_cast<double *>(base + aat[k]);
   hipStream_t s = p->ctx->stream;
   fock_diag(p->cplx, p->o, p->v, sys->f_oo, sys->f_vv, p->d_oo, p->d_vv, s);
   fill_zero(p->n1part, 2, false, s);
@@ -1617,6 +1849,7 @@ void plan_build(cc_plan *p, const cc_system *sys) {
       st.blk_a = form(p->cplx ? 2 : 1, st.a, g.K);
       st.blk_b = form(p->cplx ? 3 : 1, st.b, g.K);
     }
+  plan_levels(p);
 }
 
 void plan_free(cc_plan *p) {
@@ -1624,8 +1857,8 @@ void plan_free(cc_plan *p) {
   p->events.clear();
   if (p->graph) (void)hipGraphExecDestroy(p->graph);
   p->graph = nullptr;
-  for (Slot &s : p->slots)
-    if (s.owned && s.ptr) (void)hipFree(s.ptr);
+  if (p->mem) (void)hipFree(p->mem);
+  p->mem = nullptr;
   for (void *q : p->shadow)
     if (q) (void)hipFree(q);
   p->shadow.clear();
@@ -1639,14 +1872,15 @@ void plan_free(cc_plan *p) {
     d.ref_op = d.ref_out = d.ref_b = nullptr;
     d.dshadow = d.dblk = d.ref_a_lp = d.cur_b_lp = d.dshadow_b = nullptr;
   }
-  for (double *q : {p->d_oo, p->d_vv, p->epart, p->n2part, p->n1part, p->scalars, p->n3part})
-    if (q) (void)hipFree(q);
   for (int *q : p->pair_tab)
     if (q) (void)hipFree(q);
+  if (p->level_tab) (void)hipFree(p->level_tab);
+  p->level_tab = nullptr;
 }
 
 void plan_run(cc_plan *p) {
   hipStream_t s = p->ctx->stream;
+  CC_REQUIRE(!p->triples || p->t3 != nullptr, CC_EINVAL, "triples amplitudes not bound (cc_plan_set_triples)");
   {
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     CC_HIP_CHECK(hipStreamIsCapturing(s, &cs));
@@ -1665,7 +1899,9 @@ void plan_run(cc_plan *p) {
     return;
   }
   if (!p->profiling) {
-    for (Step &st : p->iter) exec(p, st, s);
+    if (p->level_tab && p->cur_prec == PREC_F64 && p->delta_mode == 0) run_levels(p, s);
+    else
+      for (Step &st : p->iter) exec(p, st, s);
     return;
   }
   const size_t n = p->iter.size();
@@ -1814,6 +2050,7 @@ void plan_autotune(cc_plan *p, int reps) {
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  plan_levels(p);
   if (p->graph) (void)hipGraphExecDestroy(p->graph);
   p->graph = nullptr;
 }

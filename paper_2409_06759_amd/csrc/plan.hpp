@@ -133,6 +133,16 @@ struct cc_plan {
   // every GEMM gets its own output scratch and split-K workspace (batched
   // plans, whose steps may run concurrently), instead of one shared buffer each
   bool private_work = false;
+  // small real FP64 systems: private buffers too, and an iteration's steps run
+  // in merged launches, one per dependency level (Level::step: a step of its own)
+  bool merge = false;
+  struct Level {
+    int step, first, n, off, blocks;
+  };
+  std::vector<Level> levels;
+  size_t level_tail = 0;          // steps from here on are run after the levels
+  void *level_tab = nullptr;      // items, then offsets
+  size_t level_items = 0;
   int *pair_tab[4] = {nullptr, nullptr, nullptr, nullptr};  // device index-pair tables
   // triples (op lists that read t3 or accumulate Y3): bound per plan
   bool triples = false;
@@ -146,6 +156,7 @@ struct cc_plan {
   std::map<int, int> version;             // writes seen so far while planning
   std::map<int, bool> touched;            // first write of an iteration uses beta = 0
   size_t workspace = 0;
+  void *mem = nullptr;                    // the owned slots and the arrays below
   // scalar machinery (device)
   double *d_oo = nullptr, *d_vv = nullptr;
   double *epart = nullptr, *n2part = nullptr, *n1part = nullptr, *scalars = nullptr;
@@ -189,6 +200,7 @@ struct cc_plan {
 namespace ccmi {
 void plan_layout(cc_plan *p, const cc_system *sys);  // planning only, no device work
 void plan_build(cc_plan *p, const cc_system *sys);
+void plan_levels(cc_plan *p);          // merged launches of small systems
 void plan_free(cc_plan *p);
 void plan_run(cc_plan *p);           // enqueue one residual (+ update) on the stream
 void plan_prepare(cc_plan *p);       // allocate / refresh operand copies; never under capture
