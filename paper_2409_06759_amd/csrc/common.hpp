@@ -38,6 +38,27 @@ __device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t total) {
   return (x < rem) ? x * (per + 1) + l : rem * (per + 1) + (x - rem) * per + l;
 }
 
+// Quotient of non-negative integers: 20 instructions when both fit in 32 bits,
+// against 140 of the 64-bit division.
+__device__ __forceinline__ int64_t idiv(int64_t a, int64_t b) {
+  return uint64_t(a | b) >> 32 ? a / b : int64_t(uint32_t(a) / uint32_t(b));
+}
+
+// A workgroup's K slice and output tile: logical tile L0 of tilesM x tilesN x
+// split (fewer than 2^31), and the k range [kb, kb + K) of its slice.
+struct TileAt {
+  int64_t ks, m, n;
+};
+__device__ __forceinline__ TileAt tile_at(int64_t L0, int64_t tilesM, int64_t tilesN, int split) {
+  const uint32_t tiles = uint32_t(tilesM) * uint32_t(tilesN);
+  const uint32_t ks = split == 1 ? 0u : uint32_t(L0) / tiles, L = uint32_t(L0) - ks * tiles;
+  const uint32_t n = L / uint32_t(tilesM);
+  return TileAt{ks, L - n * uint32_t(tilesM), n};
+}
+__device__ __forceinline__ int64_t k_slice(int64_t K, int split, int BK) {
+  return ((split == 1 ? K : idiv(K + split - 1, split)) + BK - 1) & ~int64_t(BK - 1);  // BK: a power of two
+}
+
 // ---- LDS-direct loads ----
 // 16 bytes per lane from src (global) into LDS at lds_base + 16 * lane, with
 // lds_base a wave-uniform byte offset in the shared aperture.  Issued from
@@ -144,8 +165,8 @@ const char *gemm_c128_tile_name(int id);
 int gemm_f64_num_tiles();
 const char *gemm_f64_tile_name(int id);
 // Tile and split-K factor of an FP64 GEMM from a model of its time; partial
-// sums of at most ws_elems elements (0: no split).  lds_direct: the operands
-// suit the LDS-direct kernels (K-contiguous, even K and row lengths).
+// sums of at most ws_elems elements (0: no split).  lds_direct: both operands
+// are K-contiguous (the LDS-direct kernels).
 struct F64Choice {
   int tile, split;
 };

@@ -137,15 +137,17 @@ __device__ __forceinline__ void perm_tiled_body(const PermEntry &E, int64_t bid,
   const T *__restrict__ in = static_cast<const T *>(rs(E.in));
   T *__restrict__ out = static_cast<T *>(rs(E.out));
   T *tile = static_cast<T *>(smem);  // TO rows of TI + 1 (TO <= 256): 1,280 elements
-  int64_t b = bid;
-  const int64_t ti = b % p.tiles_i; b /= p.tiles_i;
-  const int64_t to = b % p.tiles_o; b /= p.tiles_o;
+  // workgroup -> tile (fewer than 2^31 of them, so every count fits 32 bits)
+  uint32_t b = uint32_t(bid);
+  const uint32_t nti = uint32_t(p.tiles_i), nto = uint32_t(p.tiles_o);
+  const int64_t ti = b % nti; b /= nti;
+  const int64_t to = b % nto; b /= nto;
   int64_t ib = 0, ob = 0;
   for (int d = p.nrest - 1; d >= 0; --d) {
-    const int64_t x = b % p.rest_dims[d];
-    b /= p.rest_dims[d];
-    ib += x * p.rest_istr[d];
-    ob += x * p.rest_ostr[d];
+    const uint32_t n = uint32_t(p.rest_dims[d]), x = b % n;
+    b /= n;
+    ib += int64_t(x) * p.rest_istr[d];
+    ob += int64_t(x) * p.rest_ostr[d];
   }
   const int lti = p.lti, lto = 10 - lti, TI = 1 << lti, TO = 1 << lto;
   const int64_t Do = p.dims[p.d_o], Di = p.dims[p.d_i];
@@ -184,8 +186,8 @@ __device__ __forceinline__ void outer_body(const OuterEntry &E, int64_t bid, voi
   for (int64_t e = bid * CH + threadIdx.x; e < e1; e += 256) {
     int64_t rem = e, ia = 0, ibb = 0;
     for (int d = p.rank - 1; d >= 0; --d) {
-      const int64_t x = rem % p.dims[d];
-      rem /= p.dims[d];
+      const int64_t quo = idiv(rem, p.dims[d]), x = rem - quo * p.dims[d];
+      rem = quo;
       ia += x * p.sa[d];
       ibb += x * p.sb[d];
     }
@@ -226,7 +228,7 @@ __device__ __forceinline__ void splitk_body(const SplitkEntry &E, int64_t bid, v
   if (lane == 0 && e < total) {
     T sum = part[oi];
     for (int l = 1; l < L; ++l) sum = add(sum, part[l * nout + oi]);
-    const int64_t m = e / E.N, n = e % E.N;
+    const int64_t m = idiv(e, E.N), n = e - m * E.N;
     T v = sc(E.alpha, sum);
     if (E.beta != 0.0) v = add(v, sc(E.beta, C[m * E.ldc + n]));
     C[m * E.ldc + n] = v;
@@ -252,9 +254,10 @@ __device__ __forceinline__ void tau_body(const TauEntry &E, int64_t bid, void *s
   for (int64_t e = bid * CH_TAU + threadIdx.x; e < e1; e += RED_THREADS) {
     T x = t2[e];
     if (t1 != nullptr) {
-      const int b = e % v, a = (e / v) % v;
-      const int64_t ij = e / vv;
-      const int j = ij % o, i = ij / o;
+      const int64_t ija = idiv(e, v);
+      const int b = int(e - ija * v);
+      const uint32_t ij = uint32_t(idiv(ija, v));
+      const int a = int(ija - int64_t(ij) * v), i = ij / uint32_t(o), j = ij - uint32_t(i) * uint32_t(o);
       const T p = sub(mul(t1[i * v + a], t1[j * v + b]), mul(t1[i * v + b], t1[j * v + a]));
       const T full = add(x, p), half = add(x, sc(0.5, p));
       tau[e] = full;
@@ -320,8 +323,9 @@ __device__ __forceinline__ void asm_body(const AsmEntry &E, int64_t bid, void *s
   const int tiles = (v + 31) / 32;
   const int64_t ntp = int64_t(tiles) * (tiles + 1) / 2;
   int ta, tb, i, j;
-  tri_decode(bid % ntp, tiles, ta, tb);
-  tri_decode(bid / ntp, o, i, j);
+  const uint32_t pair = uint32_t(bid) / uint32_t(ntp);  // fewer than 2^31 workgroups
+  tri_decode(uint32_t(bid) - pair * uint32_t(ntp), tiles, ta, tb);
+  tri_decode(pair, o, i, j);
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   const int64_t vv = int64_t(v) * v;
   const int64_t base_ij = (int64_t(i) * o + j) * vv, base_ji = (int64_t(j) * o + i) * vv;
@@ -449,7 +453,7 @@ __device__ __forceinline__ void pair_body(const PairEntry &E, int64_t bid, void 
   const int64_t total = E.nP * E.nQ;
   const int64_t e1 = std::min<int64_t>(total, (bid + 1) * CH);
   for (int64_t e = bid * CH + threadIdx.x; e < e1; e += 256) {
-    const int64_t P = e / E.nQ, Q = e % E.nQ;
+    const int64_t P = idiv(e, E.nQ), Q = e - P * E.nQ;
     const int r0 = E.rows[2 * P], r1 = E.rows[2 * P + 1], c0 = E.cols[2 * Q], c1 = E.cols[2 * Q + 1];
     const int64_t q = ((int64_t(r0) * E.n1 + r1) * E.n2 + c0) * E.n3 + c1;
     const int64_t pe = P * E.ldq + Q;  // packed side

@@ -59,26 +59,19 @@ __global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_grouped(const GemmGrou
   gemm_f64_body<BM, BN, BK, WM, WN, AKC, BKC>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b], smem);
 }
 
-template <int BM, int BN, int WM, int WN, int NST, int TAG>
+template <int BM, int BN, int WM, int WN, int NST, int TAG, bool ODD>
 __global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_dma_kernel(GemmDesc d, int64_t tilesM, int64_t tilesN) {
   __shared__ __attribute__((aligned(16))) double S[Dma64<BM, BN, WM, WN, NST>::ELEMS];
-  gemm_f64_dma_body<BM, BN, WM, WN, NST>(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split), S);
+  gemm_f64_dma_body<BM, BN, WM, WN, NST, ODD>(d, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * d.split), S);
 }
 
-// Grouped launch: the systems whose operands the LDS-direct loads cannot
-// take (odd K or row length) run the staged body of the same tile.
 template <int BM, int BN, int WM, int WN, int NST>
 __global__ __launch_bounds__(WM *WN *kWave) void gemm_f64_dma_grouped(const GemmGroupEntry *__restrict__ e,
                                                                       const int64_t *__restrict__ off, int n) {
-  using St = Cfg<BM, BN, 16, WM, WN, true, true>;
-  constexpr int SN = 2 * (St::A_ELEMS + St::B_ELEMS), DN = Dma64<BM, BN, WM, WN, NST>::ELEMS;
-  __shared__ __attribute__((aligned(16))) double S[SN > DN ? SN : DN];
+  __shared__ __attribute__((aligned(16))) double S[Dma64<BM, BN, WM, WN, NST>::ELEMS];
   const int b = group_find(off, n, blockIdx.x);
   const GemmGroupEntry &g = e[b];
-  if (f64_dma_ok(g.d))
-    gemm_f64_dma_body<BM, BN, WM, WN, NST>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b], S);
-  else
-    gemm_f64_body<BM, BN, 16, WM, WN, true, true>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b], S);
+  gemm_f64_dma_body<BM, BN, WM, WN, NST, true>(g.d, g.tilesM, g.tilesN, int64_t(blockIdx.x) - off[b], S);
 }
 
 struct TileInfo {
@@ -133,16 +126,14 @@ void launch_cfg(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
 
 template <int BM, int BN, int WM, int WN, int NST, int TAG>
 void launch_f64_dma(const GemmDesc &d, int64_t tm, int64_t tn, hipStream_t s) {
-  if (f64_dma_ok(d))
-    hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, NST, TAG>), dim3(tm * tn * d.split), dim3(WM * WN * kWave), 0,
-                       s, d, tm, tn);
-  else
-    launch_cfg<BM, BN, 16, WM, WN, true, true, TAG>(d, tm, tn, s);
+  const dim3 grid(tm * tn * d.split), block(WM * WN * kWave);
+  if (d.K & 1) hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, NST, TAG, true>), grid, block, 0, s, d, tm, tn);
+  else hipLaunchKernelGGL((gemm_f64_dma_kernel<BM, BN, WM, WN, NST, TAG, false>), grid, block, 0, s, d, tm, tn);
 }
 template <int BM, int BN, int WM, int WN, int NST>
 int occ_f64_dma() {
   int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f64_dma_kernel<BM, BN, WM, WN, NST, 0>, WM * WN * kWave, 0) !=
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, gemm_f64_dma_kernel<BM, BN, WM, WN, NST, 0, false>, WM * WN * kWave, 0) !=
       hipSuccess) {
     (void)hipGetLastError();
     return 0;
@@ -154,7 +145,7 @@ void launch_grp_dma(const GemmGroupEntry *e, const int64_t *off, int n, int64_t 
   hipLaunchKernelGGL((gemm_f64_dma_grouped<BM, BN, WM, WN, NST>), dim3(blocks), dim3(WM * WN * kWave), 0, s, e, off, n);
 }
 
-// LDS-direct where the operands allow, else the staged kernel of the tile
+// LDS-direct where both operands are K-contiguous, else the staged kernel of the tile
 #define CC_TILE_DMA(BM, BN, WM, WN, NST, NAME)                                                                              \
   TileInfo {                                                                                                     \
     #BM "x" #BN "x16_w" #WM "x" #WN NAME, BM, BN, 16, WM *WN * kWave, {                                        \
@@ -187,6 +178,7 @@ const TileInfo kTiles[] = {
     CC_TILE_DMA(256, 128, 4, 2, 3, "_lds"),
     CC_TILE_DMA(64, 128, 2, 4, 2, "_lds2"),
     CC_TILE_DMA(32, 32, 2, 2, 3, "_lds"),
+    CC_TILE_DMA(64, 64, 4, 2, 3, "_lds"),
 };
 constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
@@ -294,7 +286,7 @@ int64_t gemm_tail_ws_bound(int64_t M, int64_t N, int64_t K) {
 
 int64_t gemm_f64_tail_ws(const GemmDesc &d, int tile_id) {
   if (d.M <= 0 || d.N <= 0 || d.K <= 0) return 0;
-  if (tile_id < 0 || tile_id >= kNumTiles) tile_id = gemm_f64_choose(d.M, d.N, d.K, f64_dma_ok(d), 0).tile;
+  if (tile_id < 0 || tile_id >= kNumTiles) tile_id = gemm_f64_choose(d.M, d.N, d.K, d.sak == 1 && d.sbk == 1, 0).tile;
   return f64_cut(d, tile_id).ws_elems;
 }
 
@@ -316,23 +308,28 @@ const char *gemm_f64_tile_name(int id) { return (id >= 0 && id < kNumTiles) ? kT
 // was 37% slower, on launches over 50 us: ladder 1024 x 25600 x 25600
 // 28.3 -> 20.0 ms, 2000^3 394 -> 295 us, 160000 x 400 x 400 1.97 -> 1.28 ms,
 // 10 x 6400000 x 10 0.61 -> 0.46 ms.  The autotuner refines it by timing.
+// The 64x64 configuration was fitted to 4,000 timings of 160 small and middle
+// shapes; it is the fastest one from about 800^3 (34 -> 32 us) to 1300^3
+// (105 -> 95 us) and on long contractions (400 x 2000 x 10000 376 -> 317 us).
 struct F64Model {
   int tile;       // kTiles index
   int resident;   // workgroups per CU
-  double eff[2];  // share of the MFMA rate: M/N-contiguous or odd operands; LDS-direct ones
+  // operand forms: [0] an M/N-contiguous one, [1] both K-contiguous
+  double eff[2];    // share of the MFMA rate (0: not this form)
+  double alone[2];  // cycles of one chunk when nothing hides its latency
 };
 constexpr F64Model kF64Models[] = {
-    {3, 6, {0.78, 0.32}},                       // 32x32 staged: launches bound by memory
-    {11, 2, {0.74, 0.0}},                       // 128x128 staged
-    {16, 1, {0.0, 0.92}},                       // 256x128 LDS-direct
-    {kNumTiles - 2, 3, {0.74, 0.92}},           // 64x128 LDS-direct, two stages
-    {kNumTiles - 1, 6, {0.0, 0.57}},            // 32x32 LDS-direct (staged: the first line)
+    {3, 6, {0.78, 0.32}, {1044, 702}},   // 32x32 staged: launches bound by memory
+    {11, 2, {0.74, 0.0}, {1044, 702}},   // 128x128 staged
+    {16, 1, {0.0, 0.92}, {1044, 702}},   // 256x128 LDS-direct
+    {17, 3, {0.74, 0.92}, {1044, 702}},  // 64x128 LDS-direct, two stages
+    {18, 6, {0.0, 0.57}, {1044, 702}},   // 32x32 LDS-direct (staged: the first line)
+    {19, 3, {0.0, 0.83}, {1044, 1100}},  // 64x64 LDS-direct
 };
-// per operand form: cycles of one chunk alone, cycles per workgroup set
-// (fixed; per 1,024 outputs), HBM TB/s, microseconds and TB/s of the split-K
-// partial sums, L2 TB/s, share of the shorter time that is not hidden
-constexpr double kF64Const[2][8] = {{1044, 159, 454, 5.24, 2.9, 7.6, 10.0, 0.54},
-                                    {702, 359, 417, 5.9, 2.3, 3.4, 26.5, 0.14}};
+// per operand form: cycles per workgroup set besides its chunks (fixed; per
+// 1,024 outputs), HBM TB/s, microseconds and TB/s of the split-K partial sums,
+// L2 TB/s, share of the shorter time that is not hidden
+constexpr double kF64Const[2][7] = {{159, 454, 5.24, 2.9, 7.6, 10.0, 0.54}, {359, 417, 5.9, 2.3, 3.4, 26.5, 0.14}};
 
 double f64_model_us(const F64Model &m, int form, int64_t M, int64_t N, int64_t K, int64_t split) {
   const TileInfo &ti = kTiles[m.tile];
@@ -341,13 +338,13 @@ double f64_model_us(const F64Model &m, int form, int64_t M, int64_t N, int64_t K
   const double area = double(ti.BM) * ti.BN;
   const double wgs = double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN) * double(split);
   const double w = std::ceil(wgs / 256.0), conc = std::min(w, double(m.resident));
-  const double chunk = std::max(conc * area / 4.0 / m.eff[form], c[0]);  // 128 flop per cycle and CU
-  const double mfma = (w / conc) * (double(n) * chunk + c[1] + c[2] * area / 1024.0 * conc) / 2400.0;
-  const double l2 = wgs * double(ti.BM + ti.BN) * double(n) * 128.0 / c[6] * 1e-6;
-  const double mem = (double(M) * K + double(N) * K + (split == 1 ? 2.0 * double(M) * N : 0.0)) * 8.0 / c[3] * 1e-6;
+  const double chunk = std::max(conc * area / 4.0 / m.eff[form], m.alone[form]);  // 128 flop per cycle and CU
+  const double mfma = (w / conc) * (double(n) * chunk + c[0] + c[1] * area / 1024.0 * conc) / 2400.0;
+  const double l2 = wgs * double(ti.BM + ti.BN) * double(n) * 128.0 / c[5] * 1e-6;
+  const double mem = (double(M) * K + double(N) * K + (split == 1 ? 2.0 * double(M) * N : 0.0)) * 8.0 / c[2] * 1e-6;
   const double work = std::max(mfma, l2);
-  const double red = split > 1 ? c[4] + 16.0 * double(split) * double(M) * N / c[5] * 1e-6 : 0.0;
-  return 3.0 + std::max(work, mem) + c[7] * std::min(work, mem) + red;
+  const double red = split > 1 ? c[3] + 16.0 * double(split) * double(M) * N / c[4] * 1e-6 : 0.0;
+  return 3.0 + std::max(work, mem) + c[6] * std::min(work, mem) + red;
 }
 
 static F64Choice f64_best(int64_t M, int64_t N, int64_t K, int form, int64_t ws_elems, bool merged, double *us_out) {
@@ -376,10 +373,10 @@ F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int6
   return f64_best(M, N, K, lds_direct ? 1 : 0, ws_elems, false, &us);
 }
 
-bool gemm_f64_tile_merged(int tile_id) { return tile_id == 3 || tile_id == kNumTiles - 1; }
+bool gemm_f64_tile_merged(int tile_id) { return tile_id == 3 || tile_id == 18; }
 
 // A merged launch saves the step its own, about 3 us of the model's time, so
-// the 32 x 32 tiles are taken unless another tile is faster by more than that.
+// the small tiles are taken unless another tile is faster by more than that.
 F64Choice gemm_f64_choose_merged(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems) {
   double us, us32;
   const F64Choice any = f64_best(M, N, K, lds_direct ? 1 : 0, ws_elems, false, &us);
@@ -442,7 +439,7 @@ void gemm_f64(const GemmDesc &d0, hipStream_t s, int tile_id) {
     // the library's choice, of the split-K factor too where the caller
     // allowed one (within the workspace it gave)
     const F64Choice ch = gemm_f64_choose(
-        d.M, d.N, d.K, f64_dma_ok(d),
+        d.M, d.N, d.K, akc && bkc,
         d.split > 1 && d.ws ? (d.ws_elems > 0 ? d.ws_elems : d.split * d.M * d.N) : 0);
     tile_id = ch.tile;
     d.split = ch.split;

@@ -34,9 +34,8 @@ __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM,
   using C = Cfg<BM, BN, BK, WM, WN, AKC, BKC>;
   // buffer b of A at smem + b*A_ELEMS, of B at smem + 2*A_ELEMS + b*B_ELEMS
 
-  const int64_t tiles = tilesM * tilesN;
-  const int64_t ks = L0 / tiles, L = L0 % tiles;
-  const int64_t m0 = (L % tilesM) * BM, n0 = (L / tilesM) * BN;
+  const TileAt at = tile_at(L0, tilesM, tilesN, d.split);
+  const int64_t ks = at.ks, m0 = at.m * BM, n0 = at.n * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WN) * C::WTM, wn0 = (wave % WN) * C::WTN;
   const int q = lane >> 4, r = lane & 15;
@@ -45,7 +44,7 @@ __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM,
   const double *__restrict__ B = static_cast<const double *>(d.B);
   const int64_t M = d.M, N = d.N;
   // split-K: this workgroup covers k in [kb, kb + K) of the full range
-  const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
+  const int64_t kchunk = k_slice(d.K, d.split, BK);
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
   A += kb * d.sak;
@@ -177,10 +176,14 @@ __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM,
 }
 
 // ---- LDS-direct configurations (K chunk 16) ---------------------------------
-// Both operands K-contiguous with 16-byte aligned rows and an even K (the
-// particle-particle ladder's layout); rows past M or N load the last valid
-// row instead, which only reaches outputs that are never stored, and k pairs
-// past K load zeros from a zero pair in device memory.  Each lane's 16
+// Both operands K-contiguous (the particle-particle ladder's layout); the
+// rows need no alignment beyond their elements' (global loads take any dword
+// address).  Rows past M or N load the last valid row instead, which only
+// reaches outputs that are never stored, and k pairs past K load zeros from a
+// zero pair in device memory.  The last k of an odd K has no pair: its lanes
+// load zeros too, and write the element over the first of them once the chunk
+// has landed.  Odd K took the staged kernels before: 169 x 3721 x 3721
+// went from 188 to 113 us (41 TF, as at K = 3720).  Each lane's 16
 // bytes go straight from HBM/L2 into LDS (global_load_lds_dwordx4): no
 // staging registers, three LDS stages, two chunks of K in flight.  A 16-row
 // block of a stage is two halves of 64 slots of 16 bytes; slot L of half h
@@ -205,26 +208,21 @@ struct Dma64 {
   static_assert(BM % (16 * WM) == 0 && BN % (16 * WN) == 0, "tile/wave mismatch");
 };
 
-// the shapes and layouts the LDS-direct kernels handle
-__host__ __device__ __forceinline__ bool f64_dma_ok(const GemmDesc &d) {
-  return d.sak == 1 && d.sbk == 1 && d.K > 0 && d.K % 2 == 0 && d.sam % 2 == 0 && d.sbn % 2 == 0 &&
-         (reinterpret_cast<uintptr_t>(d.A) & 15) == 0 && (reinterpret_cast<uintptr_t>(d.B) & 15) == 0;
-}
-
-template <int BM, int BN, int WM, int WN, int NST>
+// ODD: K may be odd (of its own: the element's registers cost the 256 x 128
+// tile 3% of its rate).
+template <int BM, int BN, int WM, int WN, int NST, bool ODD>
 __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t tilesM, int64_t tilesN, int64_t L0,
                                                   double *S) {
   using C = Dma64<BM, BN, WM, WN, NST>;
   constexpr int BK = C::BK, FM = C::FM, FN = C::FN, A_EL = C::A_EL, STAGE = C::STAGE, NSTAGE = C::NSTAGE,
                 LOADS = C::LOADS;
-  const int64_t tiles = tilesM * tilesN;
-  const int64_t ks = L0 / tiles, L = L0 % tiles;
-  const int64_t m0 = (L % tilesM) * BM, n0 = (L / tilesM) * BN;
+  const TileAt at = tile_at(L0, tilesM, tilesN, d.split);
+  const int64_t ks = at.ks, m0 = at.m * BM, n0 = at.n * BN;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
   const int q = lane >> 4, r = lane & 15;
   const int64_t M = d.M, N = d.N;
-  const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
+  const int64_t kchunk = k_slice(d.K, d.split, BK);
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
   const int64_t nk = (K + BK - 1) / BK;
@@ -254,7 +252,7 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
     } else {  // the last, partial chunk: zeros past K
 #pragma unroll
       for (int u = 0; u < LOADS; ++u)
-        lds_load16(k0 + kof[u] < K ? src[u] + k0 : kZeroPair, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
+        lds_load16(k0 + kof[u] + 1 < K ? src[u] + k0 : kZeroPair, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
     }
   };
 
@@ -265,6 +263,14 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
     for (int j = 0; j < FN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
 
   static_assert(NST == 2 || NST == 3, "the explicit waits are written for one or two chunks in flight");
+  // odd K: the last element of the rows this lane loads, fetched up front
+  const bool oddk = ODD && (K & 1) != 0;
+  const int64_t kl = (nk - 1) * BK;
+  double last[LOADS];
+  if (oddk) {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) last[u] = kl + kof[u] + 1 == K ? src[u][kl] : 0.0;
+  }
   if (nk > 0) issue(0, 0);
   if (NST == 3 && nk > 1) issue(1, BK);
   int cur = 0, nxt = NST - 1;
@@ -272,6 +278,12 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
     if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
     if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
+    if (oddk && kt == nk - 1) {
+#pragma unroll
+      for (int u = 0; u < LOADS; ++u)
+        if (kl + kof[u] + 1 == K) S[cur * STAGE + ((dst[u] - lds0) >> 3) + 2 * lane] = last[u];
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
     const double *St = S + cur * STAGE;
     // the k pair of steps 0-1 of every fragment is read first; the pair of
     // steps 2-3 is read behind the MFMAs of step 0, so it overlaps them (at

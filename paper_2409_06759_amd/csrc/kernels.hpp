@@ -179,7 +179,10 @@ void launch_asm_r1(const AsmEntry &e, const R1Entry &r, hipStream_t s);  // both
 // workgroups [off[b], off[b+1]) and holds the entry of its kind.  A pointer of
 // value 1, 2 or 3 in an entry stands for the t1, t2 or t3 given at the launch.
 struct LevelItem {
-  enum Kind { PERM_FLAT, PERM_TILED, OUTER, FILL, SPLITK, TAU, PAIR, GEMM_MN, GEMM_MK, GEMM_KN, GEMM_KK };
+  enum Kind {
+    PERM_FLAT, PERM_TILED, OUTER, FILL, SPLITK, TAU, PAIR,
+    GEMM_MN, GEMM_MK, GEMM_KN, GEMM_KK  // contiguous dimension of A and B
+  };
   int kind, pad = 0;
   alignas(16) unsigned char u[sizeof(PermEntry)];
   template <class E> void set(Kind k, const E &e) {
@@ -192,8 +195,7 @@ constexpr int kLevelItems = 64;  // per launch
 struct LevelExt {
   void *t1, *t2, *t3;
 };
-constexpr int kLevelTile = 32;  // GEMM tile edge (tiles of the merged launches)
-bool gemm_f64_tile_merged(int tile_id);
+bool gemm_f64_tile_merged(int tile_id);  // a configuration of the merged launches
 void launch_level(const LevelItem *items, const int *off, int n, int blocks, const LevelExt &ext, hipStream_t s);
 
 // ---- grouped launches (entries and offsets in device memory) -----------------

@@ -5,9 +5,11 @@
 // the cost of a launch and the drain of the one before; its dependency chain
 // is a dozen levels long.  One launch per level runs the same bodies on the
 // same entries, from a table in device memory that is uploaded once per plan.
-// GEMMs run on 32 x 32 tiles (the LDS-direct kernel's where the operands allow):
-// larger tiles would cost the other bodies their occupancy, and steps that
-// need them keep launches of their own.
+// GEMMs run on 32 x 32 tiles (the LDS-direct kernel's where both operands are
+// K-contiguous): larger tiles would cost the other bodies their occupancy, and
+// steps that need them keep launches of their own.  16 x 16 tiles whose four
+// waves share the K chunks, faster by themselves, gained nothing here: what
+// counts is how much code a launch of a few microseconds has to fetch.
 #include "elementwise_dev.hpp"
 #include "gemm_f64_dev.hpp"
 #include "kernels.hpp"
@@ -33,7 +35,7 @@ using Cfg32 = Cfg<32, 32, 16, 2, 2, AKC, BKC>;
 using Direct32 = Dma64<32, 32, 2, 2, 3>;
 constexpr int kLdsLevel = Direct32::ELEMS * 8;
 static_assert(kLdsLevel >= kLdsTile<double> && kLdsLevel >= kLdsPart<double> && kLdsLevel >= kLdsSum, "LDS");
-static_assert(kLdsLevel >= 16 * (Cfg32<true, true>::A_ELEMS + Cfg32<true, true>::B_ELEMS) &&
+static_assert(kLdsLevel >= 16 * (Cfg32<true, false>::A_ELEMS + Cfg32<true, false>::B_ELEMS) &&
                   kLdsLevel >= 16 * (Cfg32<false, false>::A_ELEMS + Cfg32<false, false>::B_ELEMS),
               "LDS");
 
@@ -76,8 +78,7 @@ __global__ __launch_bounds__(256) void level_kernel(const LevelItem *__restrict_
       d.B = rs(d.B);
       double *S = reinterpret_cast<double *>(smem);
       if (it.kind == LevelItem::GEMM_KK) {
-        if (f64_dma_ok(d)) gemm_f64_dma_body<32, 32, 2, 2, 3>(d, g.tilesM, g.tilesN, bid, S);
-        else gemm_f64_body<32, 32, 16, 2, 2, true, true>(d, g.tilesM, g.tilesN, bid, S);
+        gemm_f64_dma_body<32, 32, 2, 2, 3, true>(d, g.tilesM, g.tilesN, bid, S);
       } else if (it.kind == LevelItem::GEMM_KN) {
         gemm_f64_body<32, 32, 16, 2, 2, true, false>(d, g.tilesM, g.tilesN, bid, S);
       } else if (it.kind == LevelItem::GEMM_MK) {

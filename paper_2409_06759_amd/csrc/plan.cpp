@@ -344,10 +344,10 @@ struct TriplesMerger {
   }
 };
 
-// Merged launches: real FP64 systems of at most this many doubles amplitudes, and
+// Merged launches: real FP64 systems whose largest amplitude tensor is no larger, and
 // the partial sums of one of their steps.  Every GEMM has buffers of its own, so
-// the bound keeps them to tens of MB.
-constexpr int64_t kMergeAmps = int64_t(1) << 20, kMergeWork = int64_t(1) << 21;
+// the bounds keep them to some tens of MB.
+constexpr int64_t kMergeAmps = int64_t(1) << 20, kMergeWork = int64_t(1) << 23;
 
 struct Planner {
   cc_plan *p;
@@ -375,7 +375,8 @@ struct Planner {
   }
 
   bool small() const {
-    return !p->cplx && p->prec == PREC_F64 && int64_t(p->o) * p->o * p->v * p->v <= kMergeAmps;
+    const int64_t ov = int64_t(p->o) * p->v, amps = ov * ov * (p->triples ? ov : 1);
+    return !p->cplx && p->prec == PREC_F64 && amps <= kMergeAmps;
   }
 
   // Split-K factors, and the FP64 tile with its own factor (partial sums of at most 2^24 elements, as gemm_split_pick's).
@@ -388,7 +389,7 @@ struct Planner {
       g.split64 = ch.split;
       return;
     }
-    const bool direct = d.sak == 1 && d.sbk == 1 && d.K % 2 == 0 && d.sam % 2 == 0 && d.sbn % 2 == 0;
+    const bool direct = d.sak == 1 && d.sbk == 1;
     const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, direct, int64_t(1) << 24);
     g.tile = ch.tile;
     g.split64 = ch.split;
@@ -826,8 +827,6 @@ struct Planner {
 
   void build(const cc_system *sys) {
     const bool ccsd = p->method == CC_CCSD;
-    p->merge = small() && !p->lowp_all && !p->private_work;
-    if (p->merge) p->private_work = true;
     const char *inputs[] = {"foo", "fov", "fvv", "oooo", "ooov", "oovv", "ovvo", "ovvv", "vvvv"};
     const char *spaces[] = {"oo", "ov", "vv", "oooo", "ooov", "oovv", "ovvo", "ovvv", "vvvv"};
     const void *ptrs[] = {sys->f_oo, sys->f_ov, sys->f_vv, sys->oooo, sys->ooov,
@@ -874,6 +873,8 @@ struct Planner {
                                     o.A == "t1" || (!un && o.B == "t1"), o.tag.c_str()});
       }
     }
+    p->merge = small() && !p->lowp_all && !p->private_work;
+    if (p->merge) p->private_work = true;
     scratch = add_work("scratch", {1});
     splitws = add_work("splitk_ws", {1});
     if (p->packed) {
@@ -1538,7 +1539,9 @@ void plan_levels(cc_plan *p) {
           op.step = int(i);
           break;
         }
-        GemmGroupEntry e{gemm_f64_desc(st, g), (g.M + kLevelTile - 1) / kLevelTile, (g.N + kLevelTile - 1) / kLevelTile};
+        int bm, bn;
+        gemm_f64_tile_shape(st.tile, &bm, &bn);
+        GemmGroupEntry e{gemm_f64_desc(st, g), (g.M + bm - 1) / bm, (g.N + bn - 1) / bn};
         e.d.A = in(st.a);
         e.d.B = in(st.b);
         e.d.C = ptr_of(p, st.c);
@@ -1548,9 +1551,8 @@ void plan_levels(cc_plan *p) {
                    "merged launch: split-K workspace");
         op.units = e.tilesM * e.tilesN * e.d.split;
         op.weight = 2 + g.K / e.d.split;
-        op.item.set(g.sak == 1 ? (g.sbk == 1 ? LevelItem::GEMM_KK : LevelItem::GEMM_KN)
-                               : (g.sbk == 1 ? LevelItem::GEMM_MK : LevelItem::GEMM_MN),
-                    e);
+        const int form = (g.sak == 1 ? 2 : 0) + (g.sbk == 1 ? 1 : 0);
+        op.item.set(LevelItem::Kind(LevelItem::GEMM_MN + form), e);
         if (e.d.split > 1) {
           const SplitkEntry r =
               make_splitk_entry(e.d.ws, e.d.split, g.M, g.N, e.d.C, g.ldc, g.alpha, g.beta);
@@ -1988,6 +1990,11 @@ void plan_autotune(cc_plan *p, int reps) {
         if (g.split > 1 && cap > 0) g.split = gemm_f64_refined_split(g, t, cap);
         return g.split;
       };
+      // a step of a merged launch: only tiles it can hold
+      auto allowed = [&](int t) {
+        return !p->merge || prec != PREC_F64 || !gemm_f64_tile_merged(st->tile) || gemm_f64_tile_merged(t);
+      };
+      if (it != cache.end() && !allowed(it->second % kBlockedChoice)) continue;
       if (it != cache.end()) {
         if (!cz && prec == PREC_F64) st->split64 = f64_split(it->second % kBlockedChoice);
         slot = it->second % kBlockedChoice;
@@ -2017,7 +2024,8 @@ void plan_autotune(cc_plan *p, int reps) {
       };
       // every configuration on the row-major copies, and the LDS-direct
       // ones also on the blocked copies
-      for (int t = 0; t < ntiles; ++t)
+      for (int t = 0; t < ntiles; ++t) {
+        if (!allowed(t)) continue;
         for (int b = 0; b < ((blk && gemm_lowp_tile_blocked(prec, t)) ? 2 : 1); ++b) {
           launch(t, b);
           CC_HIP_CHECK(hipEventRecord(e0, s));
@@ -2032,6 +2040,7 @@ void plan_autotune(cc_plan *p, int reps) {
             best_blk = b;
           }
         }
+      }
       if (!cz && prec == PREC_F64) st->split64 = f64_split(best);
       slot = best;
       if (blk) st->blk_use = best_blk;

@@ -51,6 +51,17 @@ def test_gemm_f64_direct_partial_chunks(ctx, monkeypatch, direct, staged, M, N, 
     assert np.all(np.abs(out[1] - ref) <= bound + 1e-300)
 
 
+# (and 64x64, against the staged tile of that size)
+@pytest.mark.parametrize("direct,staged", PAIRS + [(19, 2)])
+# the last k on its own, at every place of a chunk it can have; rows of odd
+# length (8-byte aligned) with an even K
+@pytest.mark.parametrize("M,N,K,pad", [(1, 1, 1, 0), (33, 130, 15, 0), (64, 128, 17, 1), (70, 65, 35, 2), (65, 129, 37, 0),
+                                       (31, 257, 39, 4), (257, 31, 41, 3), (128, 64, 59, 1), (129, 64, 62, 3),
+                                       (300, 270, 1031, 0)])
+def test_gemm_f64_direct_odd_rows(ctx, monkeypatch, direct, staged, M, N, K, pad):
+    test_gemm_f64_direct_partial_chunks(ctx, monkeypatch, direct, staged, M, N, K, pad)
+
+
 @pytest.mark.parametrize("prec,staged,direct", [("bf16x3", 6, 9), ("bf16x3", 6, 12), ("bf16x3", 6, 13),
                                                 ("f32", 7, 10), ("f32", 7, 11), ("f32", 7, 12), ("bf16x3", 6, -1),
                                                 ("f32", 7, -1)])
