@@ -59,11 +59,23 @@ __global__ __launch_bounds__(RED_THREADS) void g_r1(const R1Entry *__restrict__ 
   __shared__ double sh[RED_THREADS];
   r1_body<T>(es[blockIdx.x], sh);
 }
-// Doubles assembly and, in one more workgroup, the singles update.
-__global__ __launch_bounds__(RED_THREADS) void k_asm_r1(AsmEntry e, R1Entry r) {
+// Doubles assembly, the singles update in one more workgroup, and the scalars
+// in the workgroup that finishes last (whose sums are in the order of k_fin's).
+__global__ __launch_bounds__(RED_THREADS) void k_asm_r1_fin(AsmEntry e, R1Entry r, FinEntry f, unsigned *ticket) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsAsm<double>];
   if (int64_t(blockIdx.x) < e.units) asm_body<double>(e, blockIdx.x, smem);
   else r1_body<double>(r, smem);
+  // the partial sums (each written by its workgroup's thread 0) before the ticket
+  __shared__ unsigned last;
+  if (threadIdx.x == 0) {
+    __threadfence();
+    last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  fin_body(f, smem);
+  if (threadIdx.x == 0) *ticket = 0;
 }
 __global__ __launch_bounds__(RED_THREADS) void k_fin(FinEntry e) {
   __shared__ double sh[RED_THREADS];
@@ -240,9 +252,10 @@ void launch_r1(const R1Entry &e, bool cplx, hipStream_t s) {
   else hipLaunchKernelGGL(k_r1<double>, dim3(1), dim3(RED_THREADS), 0, s, e);
   CC_HIP_CHECK(hipGetLastError());
 }
-void launch_asm_r1(const AsmEntry &e, const R1Entry &r, hipStream_t s) {
-  CC_REQUIRE(e.units + 1 < (int64_t(1) << 31), -1, "grid too large");
-  hipLaunchKernelGGL(k_asm_r1, dim3(e.units + 1), dim3(RED_THREADS), 0, s, e, r);
+void launch_asm_r1_fin(const AsmEntry &e, const R1Entry *r, const FinEntry &f, unsigned *ticket, hipStream_t s) {
+  const int64_t blocks = e.units + (r ? 1 : 0);
+  CC_REQUIRE(blocks > 0 && blocks < (int64_t(1) << 31), -1, "grid too large");
+  hipLaunchKernelGGL(k_asm_r1_fin, dim3(blocks), dim3(RED_THREADS), 0, s, e, r ? *r : R1Entry{}, f, ticket);
   CC_HIP_CHECK(hipGetLastError());
 }
 void launch_fin(const FinEntry &e, hipStream_t s) {

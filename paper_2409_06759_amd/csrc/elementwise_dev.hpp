@@ -629,6 +629,11 @@ __device__ __forceinline__ void fin_body(const FinEntry &E, void *smem) {
     E.scalars[0] = sqrt(n2);
     E.scalars[1] = sa;
     E.scalars[2] = sb;
+    if (E.host != nullptr) {
+      E.host[0] = sqrt(n2);
+      E.host[1] = sa;
+      E.host[2] = sb;
+    }
   }
 }
 

@@ -113,6 +113,7 @@ struct FinEntry {
   double *scalars;       // [0] = ||R||, [1] = Re E, [2] = Im E
   const double *n3part = nullptr;  // triples norm partials (may be nullptr)
   int nn3 = 0;
+  double *host = nullptr;          // pinned host copy of the three scalars (may be nullptr)
 };
 
 // Packed index pairs: for a rank-4 tensor X[n0][n1][n2][n3] and index-pair
@@ -172,7 +173,9 @@ void launch_t3(const T3Entry &e, bool cplx, hipStream_t s);
 void launch_pair(const PairEntry &e, bool cplx, hipStream_t s);
 void launch_r1(const R1Entry &e, bool cplx, hipStream_t s);
 void launch_fin(const FinEntry &e, hipStream_t s);
-void launch_asm_r1(const AsmEntry &e, const R1Entry &r, hipStream_t s);  // both steps, real
+// Real: the assembly, the singles update (r may be nullptr) and the scalars in
+// one launch; ticket: a zero counter, zero again afterwards.
+void launch_asm_r1_fin(const AsmEntry &e, const R1Entry *r, const FinEntry &f, unsigned *ticket, hipStream_t s);
 
 // ---- merged launches -----------------------------------------------------------
 // One launch runs independent steps of small real systems: item b owns

@@ -1377,6 +1377,7 @@ R1Entry r1_entry(cc_plan *p) {
 FinEntry fin_entry(cc_plan *p) {
   FinEntry f{p->epart, p->n_epart, p->n2part, p->n_n2part,
              p->method == CC_CCSD ? p->n1part : nullptr, p->scalars};
+  f.host = p->host_out;
   if (p->triples) {
     f.n3part = p->n3part;
     f.nn3 = p->n_n3part;
@@ -1638,14 +1639,13 @@ void run_levels(cc_plan *p, hipStream_t s) {
     if (L.step >= 0) exec(p, p->iter[L.step], s);
     else launch_level(items + L.first, off + L.off, L.n, L.blocks, ext, s);
   }
-  for (size_t i = p->level_tail; i < p->iter.size(); ++i) {
-    if (p->iter[i].kind == Step::ASSEMBLE && i + 1 < p->iter.size() && p->iter[i + 1].kind == Step::R1UPD) {
-      launch_asm_r1(asm_entry(p), r1_entry(p), s);
-      ++i;
-      continue;
-    }
-    exec(p, p->iter[i], s);
+  if (!p->triples) {
+    const bool ccsd = p->method == CC_CCSD;
+    const R1Entry r = ccsd ? r1_entry(p) : R1Entry{};
+    launch_asm_r1_fin(asm_entry(p), ccsd ? &r : nullptr, fin_entry(p), p->ticket, s);
+    return;
   }
+  for (size_t i = p->level_tail; i < p->iter.size(); ++i) exec(p, p->iter[i], s);
 }
 
 }  // namespace
@@ -1726,23 +1726,26 @@ void plan_build(cc_plan *p, const cc_system *sys) {
     at[i] = room(bytes);
     p->workspace += bytes;
   }
+  double *ticket = nullptr;
   const struct {
     double **ptr;
     size_t n;
   } arrays[] = {{&p->d_oo, size_t(p->o)},       {&p->d_vv, size_t(p->v)},       {&p->epart, size_t(2) * p->n_epart},
                 {&p->n2part, size_t(p->n_n2part)}, {&p->n1part, 2},             {&p->n3part, size_t(p->n_n3part)},
-                {&p->scalars, 4}};
-  size_t aat[7];
-  for (int k = 0; k < 7; ++k) aat[k] = room(sizeof(double) * arrays[k].n);
+                {&p->scalars, 4},               {&ticket, 1}};
+  size_t aat[8];
+  for (int k = 0; k < 8; ++k) aat[k] = room(sizeof(double) * arrays[k].n);
   p->mem = dev_alloc(total);
   char *base = static_cast<char *>(p->mem);
   for (size_t i = 0; i < p->slots.size(); ++i)
     if (p->slots[i].owned) p->slots[i].ptr = base + at[i];
-  for (int k = 0; k < 7; ++k)
+  for (int k = 0; k < 8; ++k)
     if (arrays[k].n) *arrays[k].ptr = reinterpret_cast<double *>(base + aat[k]);
   hipStream_t s = p->ctx->stream;
   fock_diag(p->cplx, p->o, p->v, sys->f_oo, sys->f_vv, p->d_oo, p->d_vv, s);
   fill_zero(p->n1part, 2, false, s);
+  fill_zero(ticket, 1, false, s);
+  p->ticket = reinterpret_cast<unsigned *>(ticket);
   if (p->packed) {
     auto upload = [&](std::vector<int> h, int **dst) {
       if (h.empty()) h.assign(2, 0);

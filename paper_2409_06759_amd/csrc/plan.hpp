@@ -143,6 +143,7 @@ struct cc_plan {
   size_t level_tail = 0;          // steps from here on are run after the levels
   void *level_tab = nullptr;      // items, then offsets
   size_t level_items = 0;
+  unsigned *ticket = nullptr;     // of the last launch; zero between runs
   int *pair_tab[4] = {nullptr, nullptr, nullptr, nullptr};  // device index-pair tables
   // triples (op lists that read t3 or accumulate Y3): bound per plan
   bool triples = false;
@@ -166,6 +167,7 @@ struct cc_plan {
   bool update = false;
   double shift = 0.0;
   int dressed = 0;
+  double *host_out = nullptr;  // pinned: a run also writes its scalars there
   // graph replay
   hipGraphExec_t graph = nullptr;
   void *graph_key[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -195,6 +197,7 @@ struct cc_plan {
   int delta_prec = 1;             // precision of the correction products
   std::vector<ccmi::DeltaRef> deltas;
   int graph_delta = -1;
+  double *graph_host = nullptr;
 };
 
 namespace ccmi {
