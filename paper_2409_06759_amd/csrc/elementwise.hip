@@ -59,12 +59,18 @@ __global__ __launch_bounds__(RED_THREADS) void g_r1(const R1Entry *__restrict__ 
   __shared__ double sh[RED_THREADS];
   r1_body<T>(es[blockIdx.x], sh);
 }
-// Doubles assembly, the singles update in one more workgroup, and the scalars
-// in the workgroup that finishes last (whose sums are in the order of k_fin's).
+// Doubles assembly, the singles update in one more workgroup, and, with a
+// ticket, the scalars in the workgroup that finishes last (whose sums are in
+// the order of k_fin's).  Each workgroup's fence before its ticket writes back
+// what its L2 holds: with many of them that costs more than the launch saved
+// (about 900 workgroups: 604 us per residual against 584), so the scalars are
+// left to a launch of their own above kFinUnits.
+constexpr int64_t kFinUnits = 128;
 __global__ __launch_bounds__(RED_THREADS) void k_asm_r1_fin(AsmEntry e, R1Entry r, FinEntry f, unsigned *ticket) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kLdsAsm<double>];
   if (int64_t(blockIdx.x) < e.units) asm_body<double>(e, blockIdx.x, smem);
   else r1_body<double>(r, smem);
+  if (ticket == nullptr) return;
   // the partial sums (each written by its workgroup's thread 0) before the ticket
   __shared__ unsigned last;
   if (threadIdx.x == 0) {
@@ -255,8 +261,10 @@ void launch_r1(const R1Entry &e, bool cplx, hipStream_t s) {
 void launch_asm_r1_fin(const AsmEntry &e, const R1Entry *r, const FinEntry &f, unsigned *ticket, hipStream_t s) {
   const int64_t blocks = e.units + (r ? 1 : 0);
   CC_REQUIRE(blocks > 0 && blocks < (int64_t(1) << 31), -1, "grid too large");
-  hipLaunchKernelGGL(k_asm_r1_fin, dim3(blocks), dim3(RED_THREADS), 0, s, e, r ? *r : R1Entry{}, f, ticket);
+  const bool fin = blocks <= kFinUnits;
+  hipLaunchKernelGGL(k_asm_r1_fin, dim3(blocks), dim3(RED_THREADS), 0, s, e, r ? *r : R1Entry{}, f, fin ? ticket : nullptr);
   CC_HIP_CHECK(hipGetLastError());
+  if (!fin) launch_fin(f, s);
 }
 void launch_fin(const FinEntry &e, hipStream_t s) {
   hipLaunchKernelGGL(k_fin, dim3(1), dim3(RED_THREADS), 0, s, e);

@@ -173,8 +173,9 @@ void launch_t3(const T3Entry &e, bool cplx, hipStream_t s);
 void launch_pair(const PairEntry &e, bool cplx, hipStream_t s);
 void launch_r1(const R1Entry &e, bool cplx, hipStream_t s);
 void launch_fin(const FinEntry &e, hipStream_t s);
-// Real: the assembly, the singles update (r may be nullptr) and the scalars in
-// one launch; ticket: a zero counter, zero again afterwards.
+// Real: the assembly, the singles update (r may be nullptr) and the scalars, in
+// one launch where the system is small; ticket: a zero counter, zero again
+// afterwards.
 void launch_asm_r1_fin(const AsmEntry &e, const R1Entry *r, const FinEntry &f, unsigned *ticket, hipStream_t s);
 
 // ---- merged launches -----------------------------------------------------------
