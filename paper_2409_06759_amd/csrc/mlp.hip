@@ -23,17 +23,21 @@ constexpr int64_t NPAR = HID * 3 + HID + HID * HID + HID + HID + 1;  // 17153
 constexpr int64_t OFF_W1 = 0, OFF_B1 = HID * 3, OFF_W2 = OFF_B1 + HID, OFF_B2 = OFF_W2 + HID * HID,
                   OFF_W3 = OFF_B2 + HID, OFF_B3 = OFF_W3 + HID;
 
+// k-th pair i < j of n, in row order (row r starts at r (2n - 1 - r) / 2)
 __device__ __forceinline__ void tri(int64_t k, int n, int &i, int &j) {
-  int r = 0;
-  while (k >= n - 1 - r) {
-    k -= n - 1 - r;
-    ++r;
-  }
+  const double m = 2.0 * n - 1.0;
+  int r = max(0, int(0.5 * (m - sqrt(m * m - 8.0 * double(k)))));
+  auto first = [n](int q) { return int64_t(q) * (2 * n - 1 - q) / 2; };
+  while (first(r + 1) <= k) ++r;  // (the root is off by one at most)
+  while (first(r) > k) --r;
   i = r;
-  j = r + 1 + int(k);
+  j = r + 1 + int(k - first(r));
 }
 
 // e_ij = sum_{a<b} <ij||ab>^2 / D_ij^ab for every i < j (one workgroup each).
+// Bound by the latency of its loads and the FP64 divisions (50 of each per
+// thread at v = 160).  Walking the rows and loading eight at a time, instead of
+// a search from row 0 for every pair: 170 -> 39 us at o = 32, v = 160.
 __global__ __launch_bounds__(256) void pair_energy_kernel(int o, int v, const double *__restrict__ oovv,
                                                           const double *__restrict__ d_oo,
                                                           const double *__restrict__ d_vv,
@@ -44,12 +48,29 @@ __global__ __launch_bounds__(256) void pair_energy_kernel(int o, int v, const do
   const int64_t base = (int64_t(i) * o + j) * v * v;
   double s = 0.0;
   const int64_t nab = int64_t(v) * (v - 1) / 2;
-  for (int64_t u = threadIdx.x; u < nab; u += 256) {
-    int a, b;
-    tri(u, v, a, b);
-    const double x = oovv[base + int64_t(a) * v + b];
-    const double D = (d_oo[i] + d_oo[j]) - (d_vv[a] + d_vv[b]);
-    s += x * x / D;
+  // eight pairs per round, their loads in flight together
+  constexpr int U = 8;
+  int a = 0, b = 1;
+  if (threadIdx.x < nab) tri(threadIdx.x, v, a, b);
+  for (int64_t u0 = threadIdx.x; u0 < nab; u0 += 256 * U) {
+    double x[U], D[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      x[q] = 0.0;
+      D[q] = 1.0;
+      if (u0 + 256 * q < nab) {
+        x[q] = oovv[base + int64_t(a) * v + b];
+        D[q] = (d_oo[i] + d_oo[j]) - (d_vv[a] + d_vv[b]);
+        b += 256;  // the pair 256 further on
+        while (b >= v && a < v - 2) {
+          ++a;
+          b += a + 1 - v;
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (u0 + 256 * q < nab) s += x[q] * x[q] / D[q];
   }
   sh[threadIdx.x] = s;
   __syncthreads();
@@ -60,7 +81,8 @@ __global__ __launch_bounds__(256) void pair_energy_kernel(int o, int v, const do
   if (threadIdx.x == 0) epair[blockIdx.x] = sh[0];
 }
 
-// Raw (x, D, e) or standardised features of unique amplitudes, (ij, ab) order.
+// Raw (x, D, e) or standardised features of unique amplitudes, (ij, ab) order
+// (bound by HBM: 200 MB at o = 32, v = 160, 47 us; 100 with a search for the pairs).
 __global__ __launch_bounds__(256) void features_kernel(int o, int v, const double *__restrict__ oovv,
                                                        const double *__restrict__ d_oo,
                                                        const double *__restrict__ d_vv,
@@ -69,11 +91,12 @@ __global__ __launch_bounds__(256) void features_kernel(int o, int v, const doubl
   const int64_t nab = int64_t(v) * (v - 1) / 2, n = nab * (int64_t(o) * (o - 1) / 2);
   for (int64_t u = blockIdx.x * int64_t(256) + threadIdx.x; u < n; u += int64_t(gridDim.x) * 256) {
     int i, j, a, b;
-    tri(u / nab, o, i, j);
-    tri(u % nab, v, a, b);
+    const int64_t ij = idiv(u, nab);
+    tri(ij, o, i, j);
+    tri(u - ij * nab, v, a, b);
     const double x = oovv[(int64_t(i) * o + j) * v * v + int64_t(a) * v + b];
     const double D = (d_oo[i] + d_oo[j]) - (d_vv[a] + d_vv[b]);
-    const double e = epair[u / nab];
+    const double e = epair[ij];
     if (standardise) {
       z[3 * u] = x / st.sx;
       z[3 * u + 1] = (D - st.mD) / st.sD;
@@ -103,29 +126,66 @@ __global__ __launch_bounds__(256) void gather_targets_kernel(int o, int v, const
   const int64_t nab = int64_t(v) * (v - 1) / 2, n = nab * (int64_t(o) * (o - 1) / 2);
   for (int64_t u = blockIdx.x * int64_t(256) + threadIdx.x; u < n; u += int64_t(gridDim.x) * 256) {
     int i, j, a, b;
-    tri(u / nab, o, i, j);
-    tri(u % nab, v, a, b);
+    const int64_t ij = idiv(u, nab);
+    tri(ij, o, i, j);
+    tri(u - ij * nab, v, a, b);
     y[u] = t2[(int64_t(i) * o + j) * v * v + int64_t(a) * v + b] * inv_st;
   }
 }
 
-// predictions f (scaled by st) -> antisymmetric t2 (four images, zero diagonals)
+// predictions f (scaled by st) -> antisymmetric t2 (four images, zero diagonals).
+// Bound by HBM (f read once, t2 written): one workgroup takes an i < j and a
+// pair of 32-wide tiles of (a, b) and writes the images through LDS, each
+// coalesced; the (i, i) blocks are zeros, by workgroups of their own.  One element
+// per thread, with the transposed images gathered, took 160 us at o = 32,
+// v = 160; this 48 (260 MB, 5.4 TB/s).
+constexpr int64_t CH_ZERO = 4096;  // zeros per workgroup
 __global__ __launch_bounds__(256) void scatter_t2_kernel(int o, int v, const double *__restrict__ f, double st,
                                                          double *__restrict__ t2) {
-  const int64_t total = int64_t(o) * o * v * v;
-  for (int64_t e = blockIdx.x * int64_t(256) + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
-    const int b = e % v, a = (e / v) % v;
-    const int64_t ij = e / (int64_t(v) * v);
-    const int j = ij % o, i = ij / o;
-    double val = 0.0;
-    if (i != j && a != b) {
-      const int ii = i < j ? i : j, jj = i < j ? j : i, aa = a < b ? a : b, bb = a < b ? b : a;
-      const double sgn = ((i < j) == (a < b)) ? 1.0 : -1.0;
-      const int64_t pij = int64_t(ii) * (2 * o - ii - 1) / 2 + (jj - ii - 1);
-      const int64_t pab = int64_t(aa) * (2 * v - aa - 1) / 2 + (bb - aa - 1);
-      val = sgn * st * f[pij * (int64_t(v) * (v - 1) / 2) + pab];
+  __shared__ double T[32][33];
+  const int64_t vv = int64_t(v) * v, nab = int64_t(v) * (v - 1) / 2;
+  const uint32_t nt = (v + 31) / 32, ntp = nt * (nt + 1) / 2, npair = uint32_t(o) * (o - 1) / 2, nval = npair * ntp;
+  if (blockIdx.x >= nval) {
+    const uint32_t nch = uint32_t((vv + CH_ZERO - 1) / CH_ZERO), z = blockIdx.x - nval, i = z / nch;
+    double *p = t2 + int64_t(i) * (o + 1) * vv;
+    const int64_t e0 = int64_t(z - i * nch) * CH_ZERO;
+    for (int64_t e = e0 + threadIdx.x; e < e0 + CH_ZERO && e < vv; e += 256) p[e] = 0.0;
+    return;
+  }
+  const uint32_t pij = blockIdx.x / ntp;
+  int i, j, ta, tb;
+  tri(pij, o, i, j);
+  tri(blockIdx.x - pij * ntp, nt + 1, ta, tb);
+  --tb;  // ta <= tb
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5, a0 = ta * 32, b0 = tb * 32;
+  const double *F = f + int64_t(pij) * nab;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int a = a0 + ty + 8 * k, b = b0 + tx;
+    T[ty + 8 * k][tx] = a < b && b < v ? st * F[int64_t(a) * (2 * v - a - 1) / 2 + (b - a - 1)] : 0.0;
+  }
+  __syncthreads();
+  double *ij = t2 + (int64_t(i) * o + j) * vv, *ji = t2 + (int64_t(j) * o + i) * vv;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int la = ty + 8 * k, a = a0 + la, b = b0 + tx;
+    if (a < v && b < v) {
+      const bool up = a < b;
+      const double x = up ? T[la][tx] : T[tx][la];
+      const double y = a == b ? 0.0 : -x;
+      ij[int64_t(a) * v + b] = up ? x : y;
+      ji[int64_t(a) * v + b] = up ? y : x;
     }
-    t2[e] = val;
+  }
+  if (ta == tb) return;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int lb = ty + 8 * k, b = b0 + lb, a = a0 + tx;
+    if (a < v && b < v) {
+      const double x = T[tx][lb];
+      ij[int64_t(b) * v + a] = -x;
+      ji[int64_t(b) * v + a] = x;
+    }
   }
 }
 
@@ -853,11 +913,31 @@ void backward_chunk(int prec, const double *P, const double *z, const double *y,
   CC_HIP_CHECK(hipGetLastError());
 }
 
-void device_diag(cc_ctx *ctx, const cc_system *sys, double **d_oo, double **d_vv) {
-  CC_HIP_CHECK(hipMalloc(d_oo, sizeof(double) * sys->o));
-  CC_HIP_CHECK(hipMalloc(d_vv, sizeof(double) * sys->v));
-  fock_diag(false, sys->o, sys->v, sys->f_oo, sys->f_vv, *d_oo, *d_vv, ctx->stream);
+// Scratch of the features: pair energies and the two Fock diagonals.
+int64_t features_scratch(int o, int v) { return int64_t(o) * (o - 1) / 2 + o + v; }
+
+// Enqueue the features of a system; scratch holds features_scratch() doubles.
+void features(const cc_system *sys, const cc_mlp_stats *stats, double *z, double *scratch, hipStream_t s) {
+  const int o = sys->o, v = sys->v;
+  const int64_t npair = int64_t(o) * (o - 1) / 2, n = npair * (int64_t(v) * (v - 1) / 2);
+  double *ep = scratch, *d_oo = ep + npair, *d_vv = d_oo + o;
+  fock_diag(false, o, v, sys->f_oo, sys->f_vv, d_oo, d_vv, s);
+  const cc_mlp_stats st = stats ? *stats : cc_mlp_stats{1, 0, 1, 0, 1, 1};
+  hipLaunchKernelGGL(pair_energy_kernel, dim3(npair), dim3(256), 0, s, o, v, static_cast<const double *>(sys->oovv),
+                     d_oo, d_vv, ep);
+  hipLaunchKernelGGL(features_kernel, dim3(grid_of(n)), dim3(256), 0, s, o, v, static_cast<const double *>(sys->oovv),
+                     d_oo, d_vv, ep, st, stats ? 1 : 0, z);
+  CC_HIP_CHECK(hipGetLastError());
 }
+
+// Device scratch of one call.
+struct Scratch {
+  double *p = nullptr;
+  explicit Scratch(int64_t n) { CC_HIP_CHECK(hipMalloc(&p, sizeof(double) * n)); }
+  ~Scratch() { (void)hipFree(p); }
+  Scratch(const Scratch &) = delete;
+  Scratch &operator=(const Scratch &) = delete;
+};
 
 }  // namespace
 }  // namespace ccmi
@@ -904,22 +984,9 @@ int cc_mlp_features(cc_ctx *ctx, const cc_system *sys, const cc_mlp_stats *stats
     check_sys_real(sys);
     if (!z_out) throw CCError(CC_EINVAL, "z_out is NULL");
     CC_HIP_CHECK(hipSetDevice(ctx->device));
-    hipStream_t s = ctx->stream;
-    const int o = sys->o, v = sys->v;
-    const int64_t npair = int64_t(o) * (o - 1) / 2, n = cc_mlp_num_samples(o, v);
-    double *d_oo = nullptr, *d_vv = nullptr, *ep = nullptr;
-    ccmi::device_diag(ctx, sys, &d_oo, &d_vv);
-    CC_HIP_CHECK(hipMalloc(&ep, sizeof(double) * npair));
-    cc_mlp_stats st = stats ? *stats : cc_mlp_stats{1, 0, 1, 0, 1, 1};
-    hipLaunchKernelGGL(ccmi::pair_energy_kernel, dim3(npair), dim3(256), 0, s, o, v,
-                       static_cast<const double *>(sys->oovv), d_oo, d_vv, ep);
-    hipLaunchKernelGGL(ccmi::features_kernel, dim3(ccmi::grid_of(n)), dim3(256), 0, s, o, v,
-                       static_cast<const double *>(sys->oovv), d_oo, d_vv, ep, st, stats ? 1 : 0, z_out);
-    CC_HIP_CHECK(hipGetLastError());
-    CC_HIP_CHECK(hipStreamSynchronize(s));
-    (void)hipFree(d_oo);
-    (void)hipFree(d_vv);
-    (void)hipFree(ep);
+    ccmi::Scratch w(ccmi::features_scratch(sys->o, sys->v));
+    ccmi::features(sys, stats, z_out, w.p, ctx->stream);
+    CC_HIP_CHECK(hipStreamSynchronize(ctx->stream));
     return CC_OK;
   });
 }
@@ -1063,29 +1130,34 @@ int cc_mlp_train(cc_ctx *ctx, int prec, double *params, double *adam_m, double *
 int cc_guess_mlp(cc_ctx *ctx, const cc_system *sys, int prec, const double *params, const cc_mlp_stats *stats,
                  cc_amps *t_out) {
   if (!ctx) return mfail(nullptr, CC_EINVAL, "ctx is NULL");
-  return mguard(ctx, [&] {
+  return mguard(ctx, [&]() -> int {
     check_sys_real(sys);
     check_prec(prec);
     if (!params || !stats || !t_out || !t_out->t2) throw CCError(CC_EINVAL, "bad arguments");
     const int o = sys->o, v = sys->v;
     const int64_t n = cc_mlp_num_samples(o, v);
-    double *z = nullptr, *f = nullptr;
-    CC_HIP_CHECK(hipMalloc(&z, sizeof(double) * 3 * n));
-    CC_HIP_CHECK(hipMalloc(&f, sizeof(double) * n));
-    int st = cc_mlp_features(ctx, sys, stats, z);
-    if (st == CC_OK) st = cc_mlp_forward(ctx, prec, params, z, n, f);
-    if (st == CC_OK) {
-      hipLaunchKernelGGL(ccmi::scatter_t2_kernel, dim3(ccmi::grid_of(int64_t(o) * o * v * v)), dim3(256), 0,
-                         ctx->stream, o, v, f, stats->st, static_cast<double *>(t_out->t2));
-      if (t_out->t1)
-        hipLaunchKernelGGL(ccmi::fill_kernel, dim3(ccmi::grid_of(int64_t(o) * v)), dim3(256), 0, ctx->stream,
-                           static_cast<double *>(t_out->t1), 0.0, int64_t(o) * v);
-      CC_HIP_CHECK(hipGetLastError());
-      CC_HIP_CHECK(hipStreamSynchronize(ctx->stream));
+    CC_HIP_CHECK(hipSetDevice(ctx->device));
+    hipStream_t s = ctx->stream;
+    ccmi::Scratch w(4 * n + ccmi::features_scratch(o, v));
+    double *z = w.p, *f = z + 3 * n;
+    ccmi::features(sys, stats, z, f + n, s);
+    if (prec == CC_PREC_F32) {
+      ccmi::forward_fused(params, z, n, f, s);
+    } else {
+      const int st = cc_mlp_forward(ctx, prec, params, z, n, f);
+      if (st != CC_OK) return st;
     }
-    (void)hipFree(z);
-    (void)hipFree(f);
-    return st;
+    const int64_t nt = (v + 31) / 32, vv = int64_t(v) * v;
+    const int64_t blocks = (int64_t(o) * (o - 1) / 2) * (nt * (nt + 1) / 2) + o * ((vv + ccmi::CH_ZERO - 1) / ccmi::CH_ZERO);
+    CC_REQUIRE(blocks < (int64_t(1) << 31), -1, "grid too large");
+    hipLaunchKernelGGL(ccmi::scatter_t2_kernel, dim3(blocks), dim3(256), 0, s, o, v, f, stats->st,
+                       static_cast<double *>(t_out->t2));
+    if (t_out->t1)
+      hipLaunchKernelGGL(ccmi::fill_kernel, dim3(ccmi::grid_of(int64_t(o) * v)), dim3(256), 0, s,
+                         static_cast<double *>(t_out->t1), 0.0, int64_t(o) * v);
+    CC_HIP_CHECK(hipGetLastError());
+    CC_HIP_CHECK(hipStreamSynchronize(s));
+    return CC_OK;
   });
 }
 

@@ -64,3 +64,41 @@ def test_fused_minibatches_in_the_order_given(E, ctx, n, batch, ordered):
         losses.append(lv)
     assert abs(loss[0] - np.mean(losses)) < 2e-5
     assert np.abs(net.m.cpu().numpy() - m).max() < 2e-5 * max(1.0, np.abs(m).max())
+
+
+# pairs i < j and a < b at the edges of the 32-wide tiles, of the 256-thread
+# strides of the pair sums, and at the smallest sizes
+@pytest.mark.parametrize("o,v", [(2, 2), (2, 3), (3, 23), (2, 31), (5, 32), (3, 33), (2, 64), (4, 65), (7, 100)])
+def test_features_and_guess_at_tile_edges(E, ctx, o, v):
+    from ccinputs.synth import make_system
+    print(f"features and guess o={o} v={v}", flush=True)
+    s = make_system(o, v, 50 + v)
+    d = E.DeviceSystem(s)
+    oovv = d.t["oovv"].cpu().numpy()
+    eo, ev = np.diag(d.t["f_oo"].cpu().numpy()).real, np.diag(d.t["f_vv"].cpu().numpy()).real
+    io, jo = np.triu_indices(o, 1)
+    av, bv = np.triu_indices(v, 1)
+    x = oovv[io, jo][:, av, bv]
+    D = (eo[io] + eo[jo])[:, None] - (ev[av] + ev[bv])[None, :]
+    e = (x * x / D).sum(1)
+    raw = E.MLP.raw_features(ctx, d)
+    z = raw.cpu().numpy().reshape(len(io), len(av), 3)
+    assert np.array_equal(z[..., 0], x)
+    assert np.allclose(z[..., 1], D, rtol=1e-15, atol=0)
+    # at most nab rounding errors of terms of one sign
+    assert np.all(np.abs(z[..., 2] - e[:, None]) <= (len(av) + 4) * np.finfo(np.float64).eps * np.abs(e)[:, None])
+    net = E.MLP(ctx, E.MLP.init_params(3), STATS | {"st": 0.37}, E.F32)
+    zs, _ = net.standardise(raw)
+    f = net.forward(zs).cpu().numpy().reshape(len(io), len(av))
+    want = np.zeros((o, o, v, v))
+    for p, (i, j) in enumerate(zip(io, jo)):
+        m = np.zeros((v, v))
+        m[av, bv] = 0.37 * f[p]
+        want[i, j] = m - m.T
+        want[j, i] = m.T - m
+    t1, t2 = E.zeros_amps(d, E.CCSD)
+    t1.fill_(1.0)
+    t2.fill_(1.0)
+    net.guess(d, t1, t2)
+    assert np.array_equal(t2.cpu().numpy(), want) and torch.all(t1 == 0)
+    assert np.array_equal(E.MLP.targets(ctx, o, v, t2).cpu().numpy(), want[io, jo][:, av, bv].ravel())
