@@ -345,9 +345,12 @@ struct TriplesMerger {
 };
 
 // Merged launches: real FP64 systems whose largest amplitude tensor is no larger, and
-// the partial sums of one of their steps.  Every GEMM has buffers of its own, so
-// the bounds keep them to some tens of MB.
-constexpr int64_t kMergeAmps = int64_t(1) << 20, kMergeWork = int64_t(1) << 23;
+// the partial sums of one of their steps.  Every GEMM has buffers of its own, up to
+// 64 MB for an output and 128 MB for partial sums at these bounds.  At o = 20,
+// v = 100 (4e6 amplitudes; packed) merging takes a residual from 1.88 to 1.79 ms;
+// at 26e6 (o = 32, v = 160) the buffers would take 8 GB and the launches saved are
+// 0.2 of 38 ms.
+constexpr int64_t kMergeAmps = int64_t(1) << 23, kMergeWork = int64_t(1) << 24;
 
 struct Planner {
   cc_plan *p;
