@@ -18,13 +18,13 @@
 //   K-contiguous or M/N-contiguous; the LDS layout follows the global one so
 //   both the HBM reads and the LDS fragment reads stay unit-stride.
 // * The LDS-direct configurations take K-contiguous operands with
-//   global_load_lds_dwordx4 into three LDS stages (see their kernel).
+//   global_load_lds_dwordx4 into two or three LDS stages (see their kernel).
 // * Workgroup ids are remapped so that the M tiles sharing one N tile are
 //   dispatched to the same XCD (shared L2 for the B panel).
 // * A launch whose last round of resident workgroups would be at most half
-//   full runs as whole rounds plus a K-split tail (gemm_tail_cut), and the
-//   split-K factor of a plan is re-chosen for the tile's resident workgroups
-//   (gemm_split_refine).
+//   full runs as whole rounds plus a K-split tail (gemm_tail_cut).  Tile and
+//   split-K factor come from a model of the time (gemm_f64_choose); a tile the
+//   autotuner finds faster gets its factor from gemm_split_refine.
 #include "common.hpp"
 #include "gemm_f64_dev.hpp"
 #include "kernels.hpp"
