@@ -1512,6 +1512,10 @@ void plan_levels(cc_plan *p) {
         break;
       }
       case Step::FILL: {
+        if (p->slots[st.c].external) {
+          op.step = int(i);
+          break;
+        }
         const FillEntry e = make_fill_entry(ptr_of(p, st.c), st.nelem);
         op.units = e.units;
         op.item.set(LevelItem::FILL, e);
