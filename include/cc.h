@@ -102,7 +102,8 @@ typedef struct {
   double level_shift;  /* s >= 0: update t <- t + R / (D - s); s = 0 is plain Jacobi */
   double refine_tol;   /* reduced prec: switch to FP64 steps once ||R|| < refine_tol, or when the
                           norm fell by less than 10% over 5 steps (refinement phase) */
-  int32_t use_graph;   /* 1: capture one iteration as a HIP graph and replay it */
+  int32_t use_graph;   /* 1: capture one iteration as a HIP graph and replay it (small systems, whose
+                          iteration is a dozen launches, are launched directly either way) */
   int32_t check_every; /* k >= 1: launch k steps, then read their norms and energies back at
                           once (0 counts as 1); decisions on step n act from the next batch on,
                           so up to k - 1 further updates may already be in t_inout when the

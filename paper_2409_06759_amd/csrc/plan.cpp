@@ -1890,6 +1890,10 @@ void plan_free(cc_plan *p) {
   p->level_tab = nullptr;
 }
 
+bool plan_merged(const cc_plan *p) {
+  return p->level_tab && p->cur_prec == PREC_F64 && p->delta_mode == 0 && !p->profiling;
+}
+
 void plan_run(cc_plan *p) {
   hipStream_t s = p->ctx->stream;
   CC_REQUIRE(!p->triples || p->t3 != nullptr, CC_EINVAL, "triples amplitudes not bound (cc_plan_set_triples)");
@@ -1911,7 +1915,7 @@ void plan_run(cc_plan *p) {
     return;
   }
   if (!p->profiling) {
-    if (p->level_tab && p->cur_prec == PREC_F64 && p->delta_mode == 0) run_levels(p, s);
+    if (plan_merged(p)) run_levels(p, s);
     else
       for (Step &st : p->iter) exec(p, st, s);
     return;

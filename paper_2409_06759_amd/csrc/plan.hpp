@@ -203,6 +203,7 @@ struct cc_plan {
 namespace ccmi {
 void plan_layout(cc_plan *p, const cc_system *sys);  // planning only, no device work
 void plan_build(cc_plan *p, const cc_system *sys);
+bool plan_merged(const cc_plan *p);   // the next run takes the merged launches
 void plan_levels(cc_plan *p);          // merged launches of small systems
 void plan_free(cc_plan *p);
 void plan_run(cc_plan *p);           // enqueue one residual (+ update) on the stream
