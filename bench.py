@@ -42,7 +42,7 @@ def log(*a):
 
 def source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("gemm_f64.hip", "common.hpp"):
+    for f in ("gemm_f64.hip", "gemm_f64_dev.hpp", "common.hpp"):
         h.update((ROOT / "paper_2409_06759_amd" / "csrc" / f).read_bytes())
     return h.hexdigest()[:16]
 
