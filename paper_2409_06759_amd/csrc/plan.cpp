@@ -274,7 +274,7 @@ struct TriplesMerger {
       }
       if (mem.size() < 2) break;
       const Form &f0 = forms[mem[0].second][mem[0].first];
-      const std::string wname = "Y3w" + std::to_string(made++);
+      const std::string wname = "Y3w#" + std::to_string(made++);  // '#' starts a comment: no name of a list holds one
       std::string spaces;
       for (char c : f0.sl) spaces += occ(c) ? 'o' : 'v';
       out.work.emplace_back(wname, spaces);
@@ -369,7 +369,7 @@ struct Planner {
     const int64_t tail = p->cplx ? (gemm_tail_ws_bound(M, 2 * N, 2 * K) + 1) / 2 : gemm_tail_ws_bound(M, N, K);
     if (split > 0 || tail > 0) {
       if (p->private_work) {
-        g.b2 = add_work("splitk_ws_" + std::to_string(p->slots.size()), {std::max(split, tail)});
+        g.b2 = add_work("splitk_ws#" + std::to_string(p->slots.size()), {std::max(split, tail)});
         return;
       }
       splitws_elems = std::max<int64_t>(splitws_elems, std::max(split, tail));
@@ -434,6 +434,8 @@ struct Planner {
     return id;
   }
 
+  // A buffer of the planner's own.  One that is made for a list takes a name with
+  // a '#' in it, which no name of the list can hold.
   int add_work(const std::string &name, const std::vector<int64_t> &dims) {
     Slot s;
     s.name = name;
@@ -650,7 +652,7 @@ struct Planner {
     } else {
       const int64_t need = M * N;
       int sc = scratch;
-      if (p->private_work) sc = add_work("scratch_" + std::to_string(p->slots.size()), {need});
+      if (p->private_work) sc = add_work("scratch#" + std::to_string(p->slots.size()), {need});
       else if (need > scratch_elems) scratch_elems = need;
       g.c = sc;
       g.gemm.alpha = op.alpha;
@@ -878,8 +880,8 @@ struct Planner {
     }
     p->merge = small() && !p->lowp_all && !p->private_work;
     if (p->merge) p->private_work = true;
-    scratch = add_work("scratch", {1});
-    splitws = add_work("splitk_ws", {1});
+    scratch = add_work("scratch#", {1});
+    splitws = add_work("splitk_ws#", {1});
     if (p->packed) {
       if (p->custom) throw CCError(CC_EINVAL, "packed pairs apply to the built-in table");
       const int64_t no0 = int64_t(p->o) * (p->o - 1) / 2, nv0 = int64_t(p->v) * (p->v - 1) / 2;
