@@ -132,10 +132,12 @@ void *dev_alloc(size_t bytes) {
 // and, where S_q is an intermediate made by one op for this term alone, that op
 // adds into W directly.  At o = 10, v = 40 (64e6 elements of Y3): 38.7 -> 14.8 ms.
 // Terms move to the place of the last one of their group, so X must not be
-// written in between; a list that reads Y3 is left as it is.
+// written in between; a list that reads Y3 is left as it is, and so is one that
+// the planner refuses (a tensor that merging removes would escape its checks).
 struct TriplesMerger {
   const OpList &in;
   int o, v;
+  const std::map<std::string, std::string> &known;  // spaces of the plan's own tensors
 
   static bool occ(char c) { return c >= 'i' && c <= 'n'; }
   double size(const std::string &labels) const {
@@ -161,7 +163,7 @@ struct TriplesMerger {
     Form f;
     const std::string &xl = common ? op.bl : op.al, &sl = common ? op.al : op.bl;
     const std::string &xn = common ? op.B : op.A;
-    if (op.cl.size() != 6 || size(sl) * 2.0 > size("ijkabc")) return f;
+    if (op.cl.size() != 6 || sl.size() > kMaxRank || size(sl) * 2.0 > size("ijkabc")) return f;
     for (int k = 0; k < 6; ++k)
       if (occ(op.cl[k]) != (k < 3)) return f;
     std::map<char, char> m;
@@ -225,10 +227,30 @@ struct TriplesMerger {
     }
   }
 
+  // Every tensor declared once, and every operand's labels distinct and in its
+  // tensor's spaces (labels i..n and a..h).
+  bool well_formed() const {
+    std::map<std::string, std::string> spaces = known;
+    for (const auto &w : in.work)
+      if (w.second.find_first_not_of("ov") != std::string::npos || !spaces.emplace(w.first, w.second).second) return false;
+    auto fits = [&](const std::string &name, const std::string &labels) {
+      auto it = spaces.find(name);
+      if (it == spaces.end() || it->second.size() != labels.size()) return false;
+      for (size_t k = 0; k < labels.size(); ++k)
+        if (labels[k] < 'a' || labels[k] > 'n' || occ(labels[k]) != (it->second[k] == 'o') || labels.find(labels[k]) != k)
+          return false;
+      return true;
+    };
+    for (const OpText &op : in.ops)
+      if (!fits(op.C, op.cl) || !fits(op.A, op.al) || (!op.B.empty() && !fits(op.B, op.bl))) return false;
+    return true;
+  }
+
   OpList run() const {
     const size_t n = in.ops.size();
     for (const OpText &op : in.ops)
       if (op.A == "Y3" || op.B == "Y3") return in;
+    if (!well_formed()) return in;
     std::vector<Form> forms[2];
     std::map<std::string, std::vector<std::pair<size_t, int>>> groups;
     for (size_t q = 0; q < n; ++q)
@@ -862,7 +884,9 @@ struct Planner {
         if (!ccsd) throw CCError(CC_EINVAL, "op list: triples need the CCSD method (singles and doubles)");
         add_slot("t3", "ooovvv", false, true, false);
         add_slot("Y3", "ooovvv", false, false, true);
-        p->custom = std::make_shared<OpList>(TriplesMerger{*p->custom, p->o, p->v}.run());
+        std::map<std::string, std::string> known;
+        for (const auto &kv : p->index) known[kv.first] = p->slots[kv.second].spaces;
+        p->custom = std::make_shared<OpList>(TriplesMerger{*p->custom, p->o, p->v, known}.run());
       }
       for (const auto &w : p->custom->work) {
         if (p->index.count(w.first)) throw CCError(CC_EINVAL, "op list: tensor " + w.first + " already exists");
