@@ -1507,7 +1507,7 @@ const void *level_ptr(cc_plan *p, int slot) {
 // products of a split GEMM and their sum are two levels).
 void plan_levels(cc_plan *p) {
   if (!p->merge) return;
-  p->levels.clear();
+  std::vector<cc_plan::Level> levels;
   struct Op {
     int step = -1;  // not merged
     int level = 0;
@@ -1632,34 +1632,46 @@ void plan_levels(cc_plan *p) {
   int cur = -1;
   for (const Op &op : ops) {
     if (op.step >= 0) {
-      p->levels.push_back({op.step, 0, 0, 0, 0});
+      levels.push_back({op.step, 0, 0, 0, 0});
       cur = -1;
       continue;
     }
-    if (cur < 0 || op.level != cur || p->levels.back().n == kLevelItems ||
-        p->levels.back().blocks + op.units >= (int64_t(1) << 30)) {
+    if (cur < 0 || op.level != cur || levels.back().n == kLevelItems ||
+        levels.back().blocks + op.units >= (int64_t(1) << 30)) {
       CC_REQUIRE(op.units < (int64_t(1) << 30), CC_EINTERNAL, "merged launch: too many workgroups");
-      p->levels.push_back({-1, int(items.size()), 0, int(off.size()), 0});
+      levels.push_back({-1, int(items.size()), 0, int(off.size()), 0});
       cur = op.level;
     }
-    auto &L = p->levels.back();
+    auto &L = levels.back();
     items.push_back(op.item);
     off.push_back(L.blocks);
     L.n += 1;
     L.blocks += int(op.units);
   }
-  if (items.empty()) return;
+  if (items.empty()) {  // nothing to merge: the steps run one by one
+    p->levels.swap(levels);
+    return;
+  }
   std::vector<unsigned char> tab(items.size() * sizeof(LevelItem) + off.size() * sizeof(int));
   std::memcpy(tab.data(), items.data(), items.size() * sizeof(LevelItem));
   std::memcpy(tab.data() + items.size() * sizeof(LevelItem), off.data(), off.size() * sizeof(int));
-  hipStream_t s = p->ctx->stream;
-  CC_HIP_CHECK(hipStreamSynchronize(s));  // launches that read the table before
-  if (p->level_tab) (void)hipFree(p->level_tab);
-  p->level_tab = nullptr;
-  p->level_tab = dev_alloc(tab.size());
-  p->level_items = items.size();
-  CC_HIP_CHECK(hipMemcpyAsync(p->level_tab, tab.data(), tab.size(), hipMemcpyHostToDevice, s));
-  CC_HIP_CHECK(hipStreamSynchronize(s));
+  // A step that the caller captured into a graph of its own reads the table it
+  // was captured with, so tables live as long as the plan; one is added only
+  // where the autotuner changed a tile or a split-K factor.
+  std::vector<int> tiles;
+  for (const Step &st : p->iter)
+    if (st.kind == Step::GEMM) tiles.insert(tiles.end(), {st.tile, st.split64});
+  if (p->level_tabs.empty() || tiles != p->level_tiles) {
+    void *mem = dev_alloc(tab.size());
+    p->level_tabs.push_back(mem);
+    hipStream_t s = p->ctx->stream;
+    CC_HIP_CHECK(hipMemcpyAsync(mem, tab.data(), tab.size(), hipMemcpyHostToDevice, s));
+    CC_HIP_CHECK(hipStreamSynchronize(s));
+    p->level_tab = mem;
+    p->level_items = items.size();
+    p->level_tiles.swap(tiles);
+  }
+  p->levels.swap(levels);
 }
 
 namespace {
@@ -1912,7 +1924,8 @@ void plan_free(cc_plan *p) {
   }
   for (int *q : p->pair_tab)
     if (q) (void)hipFree(q);
-  if (p->level_tab) (void)hipFree(p->level_tab);
+  for (void *q : p->level_tabs) (void)hipFree(q);
+  p->level_tabs.clear();
   p->level_tab = nullptr;
 }
 

@@ -141,8 +141,10 @@ struct cc_plan {
   };
   std::vector<Level> levels;
   size_t level_tail = 0;          // steps from here on are run after the levels
-  void *level_tab = nullptr;      // items, then offsets
+  void *level_tab = nullptr;      // items, then offsets: the last of level_tabs
   size_t level_items = 0;
+  std::vector<int> level_tiles;   // tile and split-K factor of every GEMM it was made for
+  std::vector<void *> level_tabs; // every table made, for graphs the caller captured
   unsigned *ticket = nullptr;     // of the last launch; zero between runs
   int *pair_tab[4] = {nullptr, nullptr, nullptr, nullptr};  // device index-pair tables
   // triples (op lists that read t3 or accumulate Y3): bound per plan
