@@ -261,7 +261,9 @@ int cc_iterate(cc_ctx *ctx, const cc_system *sys, int method, const cc_iter_opts
  * whose output is the interleaved complex C).  Accumulation is FP64 for F64,
  * FP32 otherwise.
  * A real GEMM is split along K as a plan would split it (few output tiles,
- * long K; the factor refined for the tile's resident workgroups), and one
+ * long K; tile and factor from a model of the time in FP64, the factor refined
+ * for the tile's resident workgroups otherwise; both follow this call's sizes
+ * alone, so the same call gives the same bits), and one
  * whose workgroups would end in a mostly empty last round runs as a main part
  * of whole rounds plus the remaining row or column panels split along K into
  * one short round.  Partial sums sit in a device buffer the context keeps
@@ -294,8 +296,9 @@ int cc_gemm_tile_count_c128(void);
  * empty) in a static device buffer of 128 MiB (2^24 doubles) that the
  * library holds on every device it runs on until the process ends; the
  * complex GEMM runs as one launch and uses none.  The split-K factor is
- * cc_gemm's (about 2048 workgroups of 64 x 64 outputs when the output has
- * fewer tiles), so split x M x N stays below 4096 x 4096 < 2^24 doubles;
+ * cc_gemm's, chosen from a model of the time; a GEMM is planned for at most
+ * the partial sums of about 2048 workgroups of 64 x 64 outputs when the output
+ * has fewer tiles, and split x M x N stays below 4096 x 4096 = 2^24 doubles;
  * a GEMM whose partial sums would still exceed the buffer is refused with
  * CC_EINVAL and a message giving both sizes, and a tail cut whose partial
  * sums would not fit is skipped (the GEMM then runs as one launch).  The work is only enqueued on the context's stream (no

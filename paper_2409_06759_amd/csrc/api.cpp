@@ -687,7 +687,7 @@ int cc_gemm(cc_ctx *ctx, int prec, int scalar, int64_t M, int64_t N, int64_t K, 
         ctx->gemm_ws_elems = need;
       }
       d.ws = ctx->gemm_ws;
-      d.ws_elems = ctx->gemm_ws_elems;
+      d.ws_elems = need;  // not all the buffer holds: the choices below follow this call's sizes alone
       return true;
     };
     auto plan_ws = [&](int64_t tail_need) {

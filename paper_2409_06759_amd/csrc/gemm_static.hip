@@ -96,7 +96,9 @@ extern "C" int cc_gemm_noalloc(cc_ctx *ctx, int scalar, int64_t M, int64_t N, in
                                            std::to_string(kScratchElems * 8));
       d.split = split;
       d.ws = ccmi::static_scratch(ctx->device);
-      d.ws_elems = kScratchElems;
+      // the room cc_gemm gives, and with it its choice of the split-K factor
+      d.ws_elems = split > 1 ? std::min(kScratchElems, std::max(int64_t(split) * M * N, ccmi::gemm_tail_ws_bound(M, N, K)))
+                             : kScratchElems;
     }
     ccmi::gemm_f64(d, ctx->stream, -1);
     return CC_OK;
