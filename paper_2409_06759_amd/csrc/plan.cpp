@@ -367,11 +367,11 @@ struct TriplesMerger {
 };
 
 // Merged launches: real FP64 systems whose largest amplitude tensor is no larger, and
-// the partial sums of one of their steps.  Every GEMM has buffers of its own, up to
-// 64 MB for an output and 128 MB for partial sums at these bounds.  At o = 20,
-// v = 100 (4e6 amplitudes; packed) merging takes a residual from 1.88 to 1.79 ms;
-// at 26e6 (o = 32, v = 160) the buffers would take 8 GB and the launches saved are
-// 0.2 of 38 ms.
+// the partial sums of one of their steps.  Every GEMM whose output is permuted has
+// an output buffer of its own (up to 64 MB; at o = 20, v = 100 161 MB of them, where
+// one shared buffer took 32), every merged split one its partial sums (up to 128 MB;
+// there 7).  At o = 20, v = 100 (4e6 amplitudes; packed) merging takes a residual from
+// 1.88 to 1.79 ms; at 26e6 (o = 32, v = 160) the launches saved are 0.2 of 38 ms.
 constexpr int64_t kMergeAmps = int64_t(1) << 23, kMergeWork = int64_t(1) << 24;
 
 struct Planner {
@@ -389,8 +389,16 @@ struct Planner {
     // complex: room for the tail of the realified M x 2N x 2K reduced-precision
     // GEMM, in complex elements
     const int64_t tail = p->cplx ? (gemm_tail_ws_bound(M, 2 * N, 2 * K) + 1) / 2 : gemm_tail_ws_bound(M, N, K);
-    if (split > 0 || tail > 0) {
-      if (p->private_work) {
+    // A step of a merged launch needs its partial sums to itself and has no
+    // tail; the steps of such a plan that keep launches of their own run one
+    // after the other and share a buffer.
+    const bool joins = p->merge && gemm_f64_tile_merged(g.tile);
+    if (split > 0 || (tail > 0 && !joins)) {
+      if (joins) {
+        g.b2 = add_work("splitk_ws#" + std::to_string(p->slots.size()), {split});
+        return;
+      }
+      if (p->private_work && !p->merge) {
         g.b2 = add_work("splitk_ws#" + std::to_string(p->slots.size()), {std::max(split, tail)});
         return;
       }
@@ -1514,6 +1522,7 @@ void plan_levels(cc_plan *p) {
     int64_t units = 0, weight = 0;
     LevelItem item;
   };
+  const int shared_ws = p->index.at("splitk_ws#");  // of the steps planned with launches of their own
   std::vector<Op> ops;
   std::vector<int> last_write(p->slots.size(), 0), last_read(p->slots.size(), 0), rd, wr;
   size_t i = 0;
@@ -1569,7 +1578,7 @@ void plan_levels(cc_plan *p) {
       default: {  // GEMM
         const GemmDesc &g = st.gemm;
         if (!gemm_f64_tile_merged(st.tile) || g.M <= 0 || g.N <= 0 || g.K <= 0 || p->slots[st.c].external ||
-            (g.sak != 1 && g.sam != 1) || (g.sbk != 1 && g.sbn != 1)) {
+            (g.sak != 1 && g.sam != 1) || (g.sbk != 1 && g.sbn != 1) || (st.split64 > 1 && st.b2 == shared_ws)) {
           op.step = int(i);
           break;
         }
