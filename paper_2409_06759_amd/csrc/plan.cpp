@@ -1994,8 +1994,10 @@ void plan_run(cc_plan *p) {
 // iteration (on the plan's own buffers) and keep the fastest.  Results are
 // cached per (M, N, K, layouts) for the life of the process; with
 // CC_AUTOTUNE_CACHE naming a file they are also read from it (lines "key
-// tile", at the first autotune of the process) and appended to it, so that
-// another process (a profiler pass, say) takes the same choices.
+// value", at the first autotune of the process) and appended to it, so that
+// another process (a profiler pass, say) takes the same choices.  An FP64 step
+// keeps the split-K factor it was timed with.  Plans whose steps join merged
+// launches choose among fewer tiles and have keys of their own.
 void plan_autotune(cc_plan *p, int reps) {
   // shared by every context of the process (contexts may live on different
   // host threads): lookups and inserts are serialised
@@ -2010,7 +2012,9 @@ void plan_autotune(cc_plan *p, int reps) {
       std::ifstream in(cache_file);
       std::string k;
       int t;
-      while (in >> k >> t) cache.emplace(k, t);
+      std::map<std::string, int> read;
+      while (in >> k >> t) read[k] = t;  // the last line of a key counts
+      cache.insert(read.begin(), read.end());
     }
   }
   const int prec_plan = p->cplx ? 9 : p->cur_prec;  // 9: complex128 tiles
@@ -2037,18 +2041,17 @@ void plan_autotune(cc_plan *p, int reps) {
                        p->bforms[st->blk_a].ptr && p->bforms[st->blk_b].ptr;
       const std::string key = std::to_string(prec) + ":" + std::to_string(d.M) + "x" +
                               std::to_string(rN) + "x" + std::to_string(rK) + (akc ? "k" : "m") +
-                              (bkc ? "k" : "n") + (blk ? "b" : "");
+                              (bkc ? "k" : "n") + (blk ? "b" : "") + (p->merge && prec == PREC_F64 ? "g" : "");
       int &slot = cz ? st->tile_z : (prec == PREC_F64 ? st->tile : st->tile_lp[prec]);
-      std::unique_lock<std::mutex> lk(cache_mutex);
-      auto it = cache.find(key);
-      // cached value: the tile, plus kBlockedChoice when it runs on the blocked copies
-      constexpr int kBlockedChoice = 1000;
+      // cached value: the tile, plus kBlockedChoice when it runs on the blocked
+      // copies, plus kSplitChoice times an FP64 step's split-K factor
+      constexpr int kBlockedChoice = 1000, kSplitChoice = 10000;
+      const int64_t cap = st->b2 >= 0 ? p->slots[st->b2].elems : 0;
       // an FP64 tile other than the library's choice runs with the factor
       // refined from the general one
       auto f64_split = [&](int t) {
         if (t == st->tile) return st->split64;
         GemmDesc g = st->gemm;
-        const int64_t cap = st->b2 >= 0 ? p->slots[st->b2].elems : 0;
         if (g.split > 1 && cap > 0) g.split = gemm_f64_refined_split(g, t, cap);
         return g.split;
       };
@@ -2056,11 +2059,17 @@ void plan_autotune(cc_plan *p, int reps) {
       auto allowed = [&](int t) {
         return !p->merge || prec != PREC_F64 || !gemm_f64_tile_merged(st->tile) || gemm_f64_tile_merged(t);
       };
-      if (it != cache.end() && !allowed(it->second % kBlockedChoice)) continue;
-      if (it != cache.end()) {
-        if (!cz && prec == PREC_F64) st->split64 = f64_split(it->second % kBlockedChoice);
-        slot = it->second % kBlockedChoice;
-        if (blk) st->blk_use = it->second >= kBlockedChoice ? 1 : 0;
+      std::unique_lock<std::mutex> lk(cache_mutex);
+      auto it = cache.find(key);
+      const int cached = it != cache.end() ? it->second : -1, cached_tile = cached % kBlockedChoice;
+      // (a file may come from a library with other configurations)
+      if (cached >= 0 && cached_tile < ntiles && allowed(cached_tile)) {
+        if (prec == PREC_F64) {
+          const int64_t split = cached / kSplitChoice;
+          st->split64 = split >= 1 && split <= 1024 && (split == 1 || split * d.M * d.N <= cap) ? int(split) : f64_split(cached_tile);
+        }
+        slot = cached_tile;
+        if (blk) st->blk_use = cached % kSplitChoice >= kBlockedChoice ? 1 : 0;
         continue;
       }
       lk.unlock();
@@ -2103,10 +2112,10 @@ void plan_autotune(cc_plan *p, int reps) {
           }
         }
       }
-      if (!cz && prec == PREC_F64) st->split64 = f64_split(best);
+      if (prec == PREC_F64) st->split64 = f64_split(best);
       slot = best;
       if (blk) st->blk_use = best_blk;
-      const int value = best + (best_blk ? kBlockedChoice : 0);
+      const int value = best + (best_blk ? kBlockedChoice : 0) + (prec == PREC_F64 ? st->split64 * kSplitChoice : 0);
       lk.lock();
       cache[key] = value;
       if (cache_file && *cache_file) {
