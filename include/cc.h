@@ -300,8 +300,9 @@ int cc_gemm_tile_count_c128(void);
  * the partial sums of about 2048 workgroups of 64 x 64 outputs when the output
  * has fewer tiles, and split x M x N stays below 4096 x 4096 = 2^24 doubles;
  * a GEMM whose partial sums would still exceed the buffer is refused with
- * CC_EINVAL and a message giving both sizes, and a tail cut whose partial
- * sums would not fit is skipped (the GEMM then runs as one launch).  The work is only enqueued on the context's stream (no
+ * CC_EINVAL and a message giving both sizes, and a factor or a tail cut whose
+ * partial sums would not fit is not taken (the GEMM then runs with a smaller
+ * factor than cc_gemm's, or as one launch).  The work is only enqueued on the context's stream (no
  * host synchronisation; launch errors are returned, faults surface at the
  * caller's next synchronisation).  Every call on one device shares that
  * device's buffer: calls that overlap in time on one GPU (other streams,

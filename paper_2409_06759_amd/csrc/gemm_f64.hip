@@ -437,10 +437,9 @@ void gemm_f64(const GemmDesc &d0, hipStream_t s, int tile_id) {
   CC_REQUIRE(d.split >= 1, -1, "gemm: split must be >= 1");
   if (tile_id < 0 || tile_id >= kNumTiles) {
     // the library's choice, of the split-K factor too where the caller
-    // allowed one (within the workspace it gave, and what the static scratch of
-    // the allocation-free entry point holds)
+    // allowed one (within the workspace it gave)
     const int64_t room = d.split > 1 && d.ws ? (d.ws_elems > 0 ? d.ws_elems : d.split * d.M * d.N) : 0;
-    const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, akc && bkc, std::min(room, int64_t(1) << 24));
+    const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, akc && bkc, room);
     tile_id = ch.tile;
     d.split = ch.split;
   } else if (d.ws && d.split > 1 && d.ws_elems > 0 && d.refine) {
