@@ -5,6 +5,7 @@
 #include "common.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace ccmi {
 namespace {
@@ -185,7 +186,7 @@ __device__ __forceinline__ void gemm_f64_body(const GemmDesc &d, int64_t tilesM,
 // has landed.  Odd K took the staged kernels before: 169 x 3721 x 3721
 // went from 188 to 113 us (41 TF, as at K = 3720).  Each lane's 16
 // bytes go straight from HBM/L2 into LDS (global_load_lds_dwordx4): no
-// staging registers, three LDS stages, two chunks of K in flight.  A 16-row
+// staging registers, two or three LDS stages, one or two chunks of K in flight.  A 16-row
 // block of a stage is two halves of 64 slots of 16 bytes; slot L of half h
 // holds row (L & 15), k = 4 (L >> 4) + 2h + {0, 1}, so lane L reads the four
 // k values it feeds the f64 MFMA (k = 4q + s, as in the staged kernel) as
@@ -225,35 +226,44 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
   const int64_t kchunk = k_slice(d.K, d.split, BK);
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
-  const int64_t nk = (K + BK - 1) / BK;
+  constexpr bool RUN = FM * FN > 1;
+  using Int = std::conditional_t<RUN, int, int64_t>;
+  const Int nk = RUN ? Int(__builtin_amdgcn_readfirstlane(int((K + BK - 1) / BK))) : Int((K + BK - 1) / BK);
+  const int nf = RUN ? __builtin_amdgcn_readfirstlane(int(K / BK)) : 0;
 
   // this wave's loads: LOADS of the stage's half blocks (16 rows x 8 k),
   // numbered with the A blocks first; lane l of half h loads row (l & 15),
   // k = 4 (l >> 4) + 2h + {0, 1}
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(S));
-  const double *src[LOADS];
+  const double *src[LOADS];  // of the next chunk to load (RUN), else of the first
   uint32_t dst[LOADS];
-  int kof[LOADS];
   const double *Ag = static_cast<const double *>(d.A) + kb;
   const double *Bg = static_cast<const double *>(d.B) + kb;
+  auto kof = [&](int u) { return 4 * q + 2 * ((wave * LOADS + u) & 1); };
 #pragma unroll
   for (int u = 0; u < LOADS; ++u) {
     const int x = wave * LOADS + u, blk = x >> 1, h = x & 1;
-    kof[u] = 4 * q + 2 * h;
     src[u] = (blk < BM / 16 ? Ag + std::min<int64_t>(m0 + blk * 16 + r, M - 1) * d.sam
                             : Bg + std::min<int64_t>(n0 + (blk - BM / 16) * 16 + r, N - 1) * d.sbn) +
-             kof[u];
+             kof(u);
     dst[u] = __builtin_amdgcn_readfirstlane(lds0 + 8u * uint32_t(blk * 256 + h * 128));
   }
-  auto issue = [&](int stage, int64_t k0) {
-    if (k0 + BK <= K) {
+  auto issue = [&](int stage, Int kt) {
+    const int64_t k0 = RUN ? 0 : int64_t(kt) * BK;
+    if (RUN ? kt < nf : k0 + BK <= K) {
 #pragma unroll
       for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
     } else {  // the last, partial chunk: zeros past K
+      const int64_t left = RUN ? K - int64_t(nf) * BK : K - k0;
 #pragma unroll
       for (int u = 0; u < LOADS; ++u)
-        lds_load16(k0 + kof[u] + 1 < K ? src[u] + k0 : kZeroPair, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
+        lds_load16(kof(u) + 1 < left ? src[u] + k0 : kZeroPair, dst[u] + uint32_t(stage) * uint32_t(8 * STAGE));
     }
+  };
+  auto advance = [&] {
+    if (!RUN) return;
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) src[u] += BK;
   };
 
   d4 acc[FM][FN];
@@ -265,23 +275,28 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
   static_assert(NST == 2 || NST == 3, "the explicit waits are written for one or two chunks in flight");
   // odd K: the last element of the rows this lane loads, fetched up front
   const bool oddk = ODD && (K & 1) != 0;
-  const int64_t kl = (nk - 1) * BK;
+  const int64_t kl = int64_t(nk - 1) * BK;  // its chunk
+  const int odd_at = int(K - 1 - kl);       // its place there
   double last[LOADS];
   if (oddk) {
 #pragma unroll
-    for (int u = 0; u < LOADS; ++u) last[u] = kl + kof[u] + 1 == K ? src[u][kl] : 0.0;
+    for (int u = 0; u < LOADS; ++u) last[u] = kof(u) == odd_at ? src[u][kl] : 0.0;
   }
   if (nk > 0) issue(0, 0);
-  if (NST == 3 && nk > 1) issue(1, BK);
+  advance();
+  if (NST == 3 && nk > 1) {
+    issue(1, 1);
+    advance();
+  }
   int cur = 0, nxt = NST - 1;
-  for (int64_t kt = 0; kt < nk; ++kt) {
+  for (Int kt = 0; kt < nk; ++kt) {
     if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
+    if (kt + NST - 1 < nk) issue(nxt, kt + NST - 1);
     if (oddk && kt == nk - 1) {
 #pragma unroll
       for (int u = 0; u < LOADS; ++u)
-        if (kl + kof[u] + 1 == K) S[cur * STAGE + ((dst[u] - lds0) >> 3) + 2 * lane] = last[u];
+        if (kof(u) == odd_at) S[cur * STAGE + ((dst[u] - lds0) >> 3) + 2 * lane] = last[u];
       asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
     const double *St = S + cur * STAGE;
@@ -312,6 +327,7 @@ __device__ __forceinline__ void gemm_f64_dma_body(const GemmDesc &d, int64_t til
     __builtin_amdgcn_sched_barrier(0);
     read_pair(1);
     __builtin_amdgcn_sched_barrier(0);
+    advance();
     mfma_step(1);
     mfma_step(2);
     mfma_step(3);
