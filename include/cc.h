@@ -424,7 +424,7 @@ int cc_plan_set_correction(cc_plan *plan, int mode, int prec);
  * are cached per shape for the life of the process; if the environment
  * variable CC_AUTOTUNE_CACHE names a file, choices are also read from it at
  * the process's first autotune and new ones appended to it (lines
- * "key value"), so that separate processes take the same choices.  Workspace
+ * "key tile"), so that separate processes take the same choices.  Workspace
  * contents are clobbered; the next step recomputes them.  t is only read. */
 int cc_plan_autotune(cc_plan *plan, const cc_amps *t, int reps);
 /* Per-step timing: with enable != 0 every later cc_plan_step /

@@ -1994,14 +1994,18 @@ void plan_run(cc_plan *p) {
 // iteration (on the plan's own buffers) and keep the fastest.  Results are
 // cached per (M, N, K, layouts) for the life of the process; with
 // CC_AUTOTUNE_CACHE naming a file they are also read from it (lines "key
-// value", at the first autotune of the process) and appended to it, so that
+// tile", at the first autotune of the process) and appended to it, so that
 // another process (a profiler pass, say) takes the same choices.  An FP64 step
-// keeps the split-K factor it was timed with.  Plans whose steps join merged
-// launches choose among fewer tiles and have keys of their own.
+// keeps the split-K factor it was timed with ("key/factor tile" in the file).
+// Plans whose steps join merged launches choose among fewer tiles and have keys
+// of their own.
 void plan_autotune(cc_plan *p, int reps) {
   // shared by every context of the process (contexts may live on different
   // host threads): lookups and inserts are serialised
-  static std::map<std::string, int> cache;
+  struct Kept {
+    int tile, split;  // tile + kBlockedChoice when it runs on the blocked copies; 0: no factor kept
+  };
+  static std::map<std::string, Kept> cache;
   static std::mutex cache_mutex;
   static bool file_read = false;
   const char *cache_file = std::getenv("CC_AUTOTUNE_CACHE");
@@ -2012,8 +2016,12 @@ void plan_autotune(cc_plan *p, int reps) {
       std::ifstream in(cache_file);
       std::string k;
       int t;
-      std::map<std::string, int> read;
-      while (in >> k >> t) read[k] = t;  // the last line of a key counts
+      std::map<std::string, Kept> read;
+      while (in >> k >> t) {  // the last line of a key counts
+        const size_t at = k.find('/');
+        const int split = at == std::string::npos ? 0 : std::atoi(k.c_str() + at + 1);
+        read[k.substr(0, at)] = Kept{t, split};
+      }
       cache.insert(read.begin(), read.end());
     }
   }
@@ -2043,9 +2051,7 @@ void plan_autotune(cc_plan *p, int reps) {
                               std::to_string(rN) + "x" + std::to_string(rK) + (akc ? "k" : "m") +
                               (bkc ? "k" : "n") + (blk ? "b" : "") + (p->merge && prec == PREC_F64 ? "g" : "");
       int &slot = cz ? st->tile_z : (prec == PREC_F64 ? st->tile : st->tile_lp[prec]);
-      // cached value: the tile, plus kBlockedChoice when it runs on the blocked
-      // copies, plus kSplitChoice times an FP64 step's split-K factor
-      constexpr int kBlockedChoice = 1000, kSplitChoice = 10000;
+      constexpr int kBlockedChoice = 1000;
       const int64_t cap = st->b2 >= 0 ? p->slots[st->b2].elems : 0;
       // an FP64 tile other than the library's choice runs with the factor
       // refined from the general one
@@ -2061,15 +2067,16 @@ void plan_autotune(cc_plan *p, int reps) {
       };
       std::unique_lock<std::mutex> lk(cache_mutex);
       auto it = cache.find(key);
-      const int cached = it != cache.end() ? it->second : -1, cached_tile = cached % kBlockedChoice;
+      const Kept kept = it != cache.end() ? it->second : Kept{-1, 0};
+      const int cached_tile = kept.tile % kBlockedChoice;
       // (a file may come from a library with other configurations)
-      if (cached >= 0 && cached_tile < ntiles && allowed(cached_tile)) {
+      if (kept.tile >= 0 && cached_tile < ntiles && allowed(cached_tile)) {
         if (prec == PREC_F64) {
-          const int64_t split = cached / kSplitChoice;
+          const int64_t split = kept.split;
           st->split64 = split >= 1 && split <= 1024 && (split == 1 || split * d.M * d.N <= cap) ? int(split) : f64_split(cached_tile);
         }
         slot = cached_tile;
-        if (blk) st->blk_use = cached % kSplitChoice >= kBlockedChoice ? 1 : 0;
+        if (blk) st->blk_use = kept.tile >= kBlockedChoice ? 1 : 0;
         continue;
       }
       lk.unlock();
@@ -2115,12 +2122,14 @@ void plan_autotune(cc_plan *p, int reps) {
       if (prec == PREC_F64) st->split64 = f64_split(best);
       slot = best;
       if (blk) st->blk_use = best_blk;
-      const int value = best + (best_blk ? kBlockedChoice : 0) + (prec == PREC_F64 ? st->split64 * kSplitChoice : 0);
+      const Kept value{best + (best_blk ? kBlockedChoice : 0), prec == PREC_F64 ? st->split64 : 0};
       lk.lock();
       cache[key] = value;
       if (cache_file && *cache_file) {
         std::ofstream out(cache_file, std::ios::app);
-        out << key << " " << value << "\n";
+        out << key;
+        if (value.split > 0) out << "/" << value.split;
+        out << " " << value.tile << "\n";
       }
     }
   } catch (...) {
