@@ -308,6 +308,12 @@ const char *gemm_f64_tile_name(int id) { return (id >= 0 && id < kNumTiles) ? kT
 // was 37% slower, on launches over 50 us: ladder 1024 x 25600 x 25600
 // 28.3 -> 20.0 ms, 2000^3 394 -> 295 us, 160000 x 400 x 400 1.97 -> 1.28 ms,
 // 10 x 6400000 x 10 0.61 -> 0.46 ms.  The autotuner refines it by timing.
+// A launch that is cut into whole rounds and a K-split tail (gemm_tail_cut) counts as
+// such, and among choices within 5% the one with the least operand traffic through
+// its tiles is taken once the operands exceed 1 GB, four times the last-level
+// cache: at 1024 x 25600 x 25600 the 64 x 128 tile reads three times as much from
+// HBM as 256 x 128 (20.8 against 19.6 ms).  Over 62 shapes of 2e9 flops and more the
+// choice is 4.0% slower than the fastest configuration, 4.9% without the two.
 // The 64x64 configuration was fitted to 4,000 timings of 160 small and middle
 // shapes; it is the fastest one from about 800^3 (34 -> 32 us) to 1300^3
 // (105 -> 95 us) and on long contractions (400 x 2000 x 10000 376 -> 317 us).
@@ -321,7 +327,7 @@ struct F64Model {
 constexpr F64Model kF64Models[] = {
     {3, 6, {0.78, 0.32}, {1044, 702}},   // 32x32 staged: launches bound by memory
     {11, 2, {0.74, 0.0}, {1044, 702}},   // 128x128 staged
-    {16, 1, {0.0, 0.92}, {1044, 702}},   // 256x128 LDS-direct
+    {16, 1, {0.0, 0.89}, {1044, 702}},   // 256x128 LDS-direct
     {17, 3, {0.74, 0.92}, {1044, 702}},  // 64x128 LDS-direct, two stages
     {18, 6, {0.0, 0.57}, {1044, 702}},   // 32x32 LDS-direct (staged: the first line)
     {19, 3, {0.0, 0.83}, {1044, 1100}},  // 64x64 LDS-direct
@@ -337,7 +343,17 @@ double f64_model_us(const F64Model &m, int form, int64_t M, int64_t N, int64_t K
   const int64_t n = (((K + split - 1) / split) + 15) / 16;  // chunks per workgroup
   const double area = double(ti.BM) * ti.BN;
   const double wgs = double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN) * double(split);
-  const double w = std::ceil(wgs / 256.0), conc = std::min(w, double(m.resident));
+  double w = std::ceil(wgs / 256.0);
+  if (split == 1) {  // whole rounds and a K-split tail, where the launch is cut that way
+    const int64_t slots = 256 * m.resident;
+    const TailCut cut = gemm_tail_cut(M, N, K, ti.BM, ti.BN, ti.BK, slots);
+    if (cut.axis) {
+      const int64_t main = cut.axis == 1 ? (M + ti.BM - 1) / ti.BM * (cut.main / ti.BN)
+                                         : (N + ti.BN - 1) / ti.BN * (cut.main / ti.BM);
+      w = std::min(w, m.resident * (double((main + slots - 1) / slots) + 1.0 / cut.split));
+    }
+  }
+  const double conc = std::min(w, double(m.resident));
   const double chunk = std::max(conc * area / 4.0 / m.eff[form], m.alone[form]);  // 128 flop per cycle and CU
   const double mfma = (w / conc) * (double(n) * chunk + c[0] + c[1] * area / 1024.0 * conc) / 2400.0;
   const double l2 = wgs * double(ti.BM + ti.BN) * double(n) * 128.0 / c[5] * 1e-6;
@@ -349,22 +365,39 @@ double f64_model_us(const F64Model &m, int form, int64_t M, int64_t N, int64_t K
 
 static F64Choice f64_best(int64_t M, int64_t N, int64_t K, int form, int64_t ws_elems, bool merged, double *us_out) {
   static constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
-  F64Choice best{3, 1};
-  double best_us = 1e300;
-  for (const F64Model &m : kF64Models) {
+  constexpr int kModels = sizeof(kF64Models) / sizeof(kF64Models[0]);
+  // each tile's best factor
+  F64Choice own[kModels];
+  double own_us[kModels], best_us = 1e300;
+  for (int q = 0; q < kModels; ++q) {
+    const F64Model &m = kF64Models[q];
+    own_us[q] = 1e300;
     if (m.eff[form] <= 0.0 || (merged && !gemm_f64_tile_merged(m.tile))) continue;
     const TileInfo &ti = kTiles[m.tile];
     const int64_t tiles = ((M + ti.BM - 1) / ti.BM) * ((N + ti.BN - 1) / ti.BN);
     for (int s : kSplits) {
       if (s > 1 && (int64_t(s) * 64 > K || tiles * s > 4096 || int64_t(s) * M * N > ws_elems)) break;
       const double us = f64_model_us(m, form, M, N, K, s);
-      if (us < best_us) {
-        best_us = us;
-        best = F64Choice{m.tile, s};
+      if (us < own_us[q]) {
+        own_us[q] = us;
+        own[q] = F64Choice{m.tile, s};
       }
     }
+    best_us = std::min(best_us, own_us[q]);
   }
-  *us_out = best_us;
+  const bool huge = 8.0 * double(M + N) * double(K) > 1e9;
+  F64Choice best{3, 1};
+  double least = 1e300;
+  for (int q = 0; q < kModels; ++q) {
+    if (own_us[q] > best_us * (huge ? 1.05 : 1.0)) continue;
+    const TileInfo &ti = kTiles[kF64Models[q].tile];
+    const double traffic = huge ? double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN) * (ti.BM + ti.BN) : own_us[q];
+    if (traffic < least) {
+      least = traffic;
+      best = own[q];
+      *us_out = own_us[q];
+    }
+  }
   return best;
 }
 
