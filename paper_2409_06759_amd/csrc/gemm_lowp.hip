@@ -418,13 +418,14 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
   const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
-  const int64_t nk = (K + BK - 1) / BK;
+  // chunks, and whole ones
+  const int nk = __builtin_amdgcn_readfirstlane(int((K + BK - 1) / BK)), nf = __builtin_amdgcn_readfirstlane(int(K / BK));
 
   // this wave's loads: LOADS of the stage's 16-row blocks, numbered hi and lo
   // plane by block, A before B; LDS addresses are byte offsets in the shared
   // aperture (its low 32 bits), made wave-uniform for M0
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(S));
-  const unsigned short *src[LOADS];
+  const unsigned short *src[LOADS];  // of the next chunk to load
   uint32_t dst[LOADS];
   // lp_in == 2: operands in 16-row x 32-k blocks of 1 KiB (convert_blocked),
   // a chunk of a 16-row block one contiguous wave load; 16 elements of a
@@ -444,16 +445,22 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
     dst[u] = __builtin_amdgcn_readfirstlane(
         lds0 + 2u * uint32_t(bb < 0 ? pl * A_EL + blk * 512 : 2 * A_EL + pl * B_EL + bb * 512));
   }
-  auto issue = [&](int stage, int64_t k0) {
-    if (k0 + BK <= K) {
+  auto issue = [&](int stage, int kt) {
+    if (kt < nf) {
 #pragma unroll
-      for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0 * kx, dst[u] + uint32_t(stage) * uint32_t(2 * STAGE));
+      for (int u = 0; u < LOADS; ++u) lds_load16(src[u], dst[u] + uint32_t(stage) * uint32_t(2 * STAGE));
     } else {  // the last, partial chunk (row-major copies): zeros past K
-      const bool in = k0 + q * 8 < K;
+      const bool in = q * 8 < int(K - int64_t(nf) * BK);
 #pragma unroll
       for (int u = 0; u < LOADS; ++u)
-        lds_load16(in ? static_cast<const void *>(src[u] + k0) : kZero16, dst[u] + uint32_t(stage) * uint32_t(2 * STAGE));
+        lds_load16(in ? static_cast<const void *>(src[u]) : kZero16, dst[u] + uint32_t(stage) * uint32_t(2 * STAGE));
     }
+  };
+  // behind the MFMAs of the chunk before, off the way from the barrier to the
+  // loads (ladder 1024 x 25600 x 25600 3290 -> 3225 us)
+  auto advance = [&] {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) src[u] += BK * kx;
   };
 
   f4 acc[FM][FN];
@@ -463,12 +470,16 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
     for (int j = 0; j < FN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
   if (nk > 0) issue(0, 0);
-  if (NST == 3 && nk > 1) issue(1, BK);
+  advance();
+  if (NST == 3 && nk > 1) {
+    issue(1, 1);
+    advance();
+  }
   int cur = 0, nxt = NST - 1;
-  for (int64_t kt = 0; kt < nk; ++kt) {
+  for (int kt = 0; kt < nk; ++kt) {
     if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
+    if (kt + NST - 1 < nk) issue(nxt, kt + NST - 1);
     const unsigned short *St = S + cur * STAGE;
     bf8 fah[FM], fal[FM], fbh[FN], fbl[FN];
 #pragma unroll
@@ -486,6 +497,7 @@ __device__ __forceinline__ void gemm_b3_dma_body(const GemmDesc &d, int64_t tile
     // the products at raised wave priority, so that the SIMD's other wave
     // issues its loads and fragment reads around them rather than between
     __builtin_amdgcn_s_setprio(1);
+    advance();
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -829,12 +841,13 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
   const int64_t kchunk = ((d.K + d.split - 1) / d.split + BK - 1) / BK * BK;
   const int64_t kb = ks * kchunk;
   const int64_t K = std::max<int64_t>(0, std::min<int64_t>(d.K - kb, kchunk));
-  const int64_t nk = (K + BK - 1) / BK;
+  // chunks, and whole ones
+  const int nk = __builtin_amdgcn_readfirstlane(int((K + BK - 1) / BK)), nf = __builtin_amdgcn_readfirstlane(int(K / BK));
 
   // loads: (block, k half) pairs, A before B; A block b, half h sits at
   // floats (h * (BM / 16) + b) * 256 of the stage
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(S));
-  const float *src[LOADS];
+  const float *src[LOADS];  // of the next chunk to load
   uint32_t dst[LOADS];
   const float *Ag = static_cast<const float *>(d.A) + kb;
   const float *Bg = static_cast<const float *>(d.B) + kb;
@@ -847,18 +860,24 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
     dst[u] = __builtin_amdgcn_readfirstlane(
         lds0 + 4u * uint32_t(bb < 0 ? (h * (BM / 16) + blk) * 256 : FA_EL + (h * (BN / 16) + bb) * 256));
   }
-  auto issue = [&](int stage, int64_t k0) {
-    if (k0 + BK <= K) {
+  auto issue = [&](int stage, int kt) {
+    if (kt < nf) {
 #pragma unroll
-      for (int u = 0; u < LOADS; ++u) lds_load16(src[u] + k0, dst[u] + uint32_t(stage) * uint32_t(4 * FSTAGE));
+      for (int u = 0; u < LOADS; ++u) lds_load16(src[u], dst[u] + uint32_t(stage) * uint32_t(4 * FSTAGE));
     } else {  // the last, partial chunk: zeros past K
+      const int left = int(K - int64_t(nf) * BK);
 #pragma unroll
       for (int u = 0; u < LOADS; ++u) {
         const int h = (wave * LOADS + u) & 1;
-        lds_load16(k0 + 16 * h + 4 * q < K ? static_cast<const void *>(src[u] + k0) : kZero16,
+        lds_load16(16 * h + 4 * q < left ? static_cast<const void *>(src[u]) : kZero16,
                    dst[u] + uint32_t(stage) * uint32_t(4 * FSTAGE));
       }
     }
+  };
+  // as in the split-bf16 kernel (ladder 10.46 -> 10.26 ms)
+  auto advance = [&] {
+#pragma unroll
+    for (int u = 0; u < LOADS; ++u) src[u] += BK;
   };
 
   f4 acc[FM][FN];
@@ -868,12 +887,16 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
     for (int j = 0; j < FN; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
 
   if (nk > 0) issue(0, 0);
-  if (NST == 3 && nk > 1) issue(1, BK);
+  advance();
+  if (NST == 3 && nk > 1) {
+    issue(1, 1);
+    advance();
+  }
   int cur = 0, nxt = NST - 1;
-  for (int64_t kt = 0; kt < nk; ++kt) {
+  for (int kt = 0; kt < nk; ++kt) {
     if (NST == 3 && kt + 1 < nk) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LOADS) : "memory");
     else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (kt + NST - 1 < nk) issue(nxt, (kt + NST - 1) * BK);
+    if (kt + NST - 1 < nk) issue(nxt, kt + NST - 1);
     const float *St = S + cur * FSTAGE;
     // the second k half is read behind the first half's first MFMA step
     f4 fa[2][FM], fb[2][FN];
@@ -898,6 +921,7 @@ __device__ __forceinline__ void gemm_f32_dma_body(const GemmDesc &d, int64_t til
     __builtin_amdgcn_sched_barrier(0);
     read_half(1);
     __builtin_amdgcn_sched_barrier(0);
+    advance();
 #pragma unroll
     for (int s = 1; s < 4; ++s) mfma_step(0, s);
 #pragma unroll
