@@ -170,9 +170,9 @@ const char *gemm_f64_tile_name(int id);
 struct F64Choice {
   int tile, split;
 };
-F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems);
-// the same for a step that may join a merged launch (32 x 32 tiles)
-F64Choice gemm_f64_choose_merged(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems);
+// merged: also the choice for a step that may join a merged launch (32 x 32 tiles).
+F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems,
+                          F64Choice *merged = nullptr);
 // the same for the complex GEMM (ws_elems: complex elements)
 F64Choice gemm_c128_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems);
 // the split-K factor re-chosen for a forced tile (gemm_split_refine)

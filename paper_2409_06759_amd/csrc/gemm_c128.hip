@@ -397,7 +397,7 @@ const ZTile kZTiles[] = {CC_ZTILE(64, 64, 16, 2, 2), CC_ZTILE(32, 32, 16, 2, 2),
                          CC_ZTILE_DMA(32, 32, 2, 2, 2, "_lds2")};
 constexpr int kNumZ = sizeof(kZTiles) / sizeof(kZTiles[0]);
 
-// The same kind of model as the real FP64 one (f64_model_us), fitted to the
+// The same kind of model as the real FP64 one (F64Tile), fitted to the
 // timings of every configuration and split-K factor on the 139 GEMM shapes of
 // complex CCSD at o = 4..20, v = 20..90: on them its choice is 1.3% slower
 // than the fastest, and 1.33 times faster than the rule it replaced (rounds of

@@ -337,87 +337,102 @@ constexpr F64Model kF64Models[] = {
 // L2 TB/s, share of the shorter time that is not hidden
 constexpr double kF64Const[2][7] = {{159, 454, 5.24, 2.9, 7.6, 10.0, 0.54}, {359, 417, 5.9, 2.3, 3.4, 26.5, 0.14}};
 
-double f64_model_us(const F64Model &m, int form, int64_t M, int64_t N, int64_t K, int64_t split) {
-  const TileInfo &ti = kTiles[m.tile];
-  const double *c = kF64Const[form];
-  const int64_t n = (((K + split - 1) / split) + 15) / 16;  // chunks per workgroup
-  const double area = double(ti.BM) * ti.BN;
-  const double wgs = double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN) * double(split);
-  double w = std::ceil(wgs / 256.0);
-  if (split == 1) {  // whole rounds and a K-split tail, where the launch is cut that way
-    const int64_t slots = 256 * m.resident;
-    const TailCut cut = gemm_tail_cut(M, N, K, ti.BM, ti.BN, ti.BK, slots);
-    if (cut.axis) {
-      const int64_t main = cut.axis == 1 ? (M + ti.BM - 1) / ti.BM * (cut.main / ti.BN)
-                                         : (N + ti.BN - 1) / ti.BN * (cut.main / ti.BM);
-      w = std::min(w, m.resident * (double((main + slots - 1) / slots) + 1.0 / cut.split));
-    }
-  }
-  const double conc = std::min(w, double(m.resident));
-  const double chunk = std::max(conc * area / 4.0 / m.eff[form], m.alone[form]);  // 128 flop per cycle and CU
-  const double mfma = (w / conc) * (double(n) * chunk + c[0] + c[1] * area / 1024.0 * conc) / 2400.0;
-  const double l2 = wgs * double(ti.BM + ti.BN) * double(n) * 128.0 / c[5] * 1e-6;
-  const double mem = (double(M) * K + double(N) * K + (split == 1 ? 2.0 * double(M) * N : 0.0)) * 8.0 / c[2] * 1e-6;
-  const double work = std::max(mfma, l2);
-  const double red = split > 1 ? c[3] + 16.0 * double(split) * double(M) * N / c[4] * 1e-6 : 0.0;
-  return 3.0 + std::max(work, mem) + c[6] * std::min(work, mem) + red;
-}
+// A plan of 25 GEMMs asks for some 5,000 times: the terms that do not depend on
+// the split-K factor are formed once per tile.
+struct F64Tile {
+  const F64Model &m;
+  const TileInfo &ti;
+  int64_t tm, tn, tiles;
+  double us = 1e300;  // with its best factor
+  F64Choice choice;
 
-static F64Choice f64_best(int64_t M, int64_t N, int64_t K, int form, int64_t ws_elems, bool merged, double *us_out) {
-  static constexpr int kSplits[] = {1, 2, 3, 4, 5, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
-  constexpr int kModels = sizeof(kF64Models) / sizeof(kF64Models[0]);
-  // each tile's best factor
-  F64Choice own[kModels];
-  double own_us[kModels], best_us = 1e300;
-  for (int q = 0; q < kModels; ++q) {
-    const F64Model &m = kF64Models[q];
-    own_us[q] = 1e300;
-    if (m.eff[form] <= 0.0 || (merged && !gemm_f64_tile_merged(m.tile))) continue;
-    const TileInfo &ti = kTiles[m.tile];
-    const int64_t tiles = ((M + ti.BM - 1) / ti.BM) * ((N + ti.BN - 1) / ti.BN);
+  F64Tile(const F64Model &model, int64_t M, int64_t N)
+      : m(model), ti(kTiles[m.tile]), tm((M + ti.BM - 1) / ti.BM), tn((N + ti.BN - 1) / ti.BN), tiles(tm * tn),
+        choice{m.tile, 1} {}
+
+  void best(int form, int64_t M, int64_t N, int64_t K, int64_t ws_elems) {
+    static constexpr int kSplits[] = {1,  2,  3,  4,  5,   6,   8,   12,  16,  24,  32,
+                                      48, 64, 96, 128, 192, 256, 384, 512, 768, 1024};
+    const double *c = kF64Const[form];
+    const double area = double(ti.BM) * ti.BN, cyc = area / 4.0 / m.eff[form];  // 128 flop per cycle and CU
+    const double setup = c[1] * area / 1024.0, res = m.resident, mn = double(M) * double(N);
+    const double l2s = double(tiles) * double(ti.BM + ti.BN) * 128.0 / c[5] * 1e-6;
+    const double ins = (double(M) + double(N)) * double(K) * 8.0 / c[2] * 1e-6, outs = 16.0 * mn / c[2] * 1e-6;
+    const double sums = 16.0 * mn / c[4] * 1e-6;
     for (int s : kSplits) {
-      if (s > 1 && (int64_t(s) * 64 > K || tiles * s > 4096 || int64_t(s) * M * N > ws_elems)) break;
-      const double us = f64_model_us(m, form, M, N, K, s);
-      if (us < own_us[q]) {
-        own_us[q] = us;
-        own[q] = F64Choice{m.tile, s};
+      if (s > 1 && (int64_t(s) * 64 > K || tiles * s > 4096 || double(s) * mn > double(ws_elems))) break;
+      const int64_t per = s == 1 ? K : K >> 31 ? (K + s - 1) / s : int64_t((uint32_t(K) + uint32_t(s) - 1) / uint32_t(s));
+      const double n = double((per + 15) >> 4);  // chunks per workgroup
+      double w = double((tiles * s + 255) >> 8);
+      if (s == 1) {  // whole rounds and a K-split tail, where the launch is cut that way
+        const int64_t slots = 256 * m.resident;
+        const TailCut cut = gemm_tail_cut(M, N, K, ti.BM, ti.BN, ti.BK, slots);
+        if (cut.axis) {
+          const int64_t main = cut.axis == 1 ? tm * (cut.main / ti.BN) : tn * (cut.main / ti.BM);
+          w = std::min(w, res * (double((main + slots - 1) / slots) + 1.0 / cut.split));
+        }
+      }
+      const double conc = std::min(w, res);
+      const double chunk = std::max(conc * cyc, m.alone[form]);
+      const double mfma = (w > res ? w / res : 1.0) * (n * chunk + c[0] + setup * conc) * (1.0 / 2400.0);
+      const double mem = s == 1 ? ins + outs : ins, work = std::max(mfma, l2s * double(s) * n);
+      const double red = s > 1 ? c[3] + sums * double(s) : 0.0;
+      const double t = 3.0 + std::max(work, mem) + c[6] * std::min(work, mem) + red;
+      if (t < us) {
+        us = t;
+        choice.split = s;
       }
     }
-    best_us = std::min(best_us, own_us[q]);
   }
-  const bool huge = 8.0 * double(M + N) * double(K) > 1e9;
-  F64Choice best{3, 1};
-  double least = 1e300;
-  for (int q = 0; q < kModels; ++q) {
-    if (own_us[q] > best_us * (huge ? 1.05 : 1.0)) continue;
-    const TileInfo &ti = kTiles[kF64Models[q].tile];
-    const double traffic = huge ? double((M + ti.BM - 1) / ti.BM) * double((N + ti.BN - 1) / ti.BN) * (ti.BM + ti.BN) : own_us[q];
-    if (traffic < least) {
-      least = traffic;
-      best = own[q];
-      *us_out = own_us[q];
-    }
-  }
-  return best;
-}
-
-F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems) {
-  double us;
-  return f64_best(M, N, K, lds_direct ? 1 : 0, ws_elems, false, &us);
-}
+};
 
 bool gemm_f64_tile_merged(int tile_id) { return tile_id == 3 || tile_id == 18; }
 
-// A merged launch saves the step its own, about 3 us of the model's time, so
-// the small tiles are taken unless another tile is faster by more than that.
-F64Choice gemm_f64_choose_merged(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems) {
-  double us, us32;
-  const F64Choice any = f64_best(M, N, K, lds_direct ? 1 : 0, ws_elems, false, &us);
-  const F64Choice own = f64_best(M, N, K, lds_direct ? 1 : 0, ws_elems, true, &us32);
-  return us32 <= us + 3.0 ? own : any;
+F64Choice gemm_f64_choose(int64_t M, int64_t N, int64_t K, bool lds_direct, int64_t ws_elems, F64Choice *merged) {
+  const int form = lds_direct ? 1 : 0;
+  const bool huge = 8.0 * double(M + N) * double(K) > 1e9;
+  F64Choice best{3, 1}, own{3, 1}, near{3, 1};
+  double best_us = 1e300, own_us = 1e300;
+  double us[sizeof(kF64Models) / sizeof(kF64Models[0])];
+  int q = 0;
+  for (const F64Model &m : kF64Models) {
+    us[q] = 1e300;
+    if (m.eff[form] > 0.0) {
+      F64Tile t(m, M, N);
+      t.best(form, M, N, K, ws_elems);
+      us[q] = t.us;
+      if (t.us < best_us) {
+        best_us = t.us;
+        best = t.choice;
+      }
+      if (gemm_f64_tile_merged(m.tile) && t.us < own_us) {
+        own_us = t.us;
+        own = t.choice;
+      }
+    }
+    ++q;
+  }
+  if (huge) {
+    double least = 1e300;
+    q = 0;
+    for (const F64Model &m : kF64Models)
+      if (us[q++] <= best_us * 1.05) {
+        F64Tile t(m, M, N);
+        const double traffic = double(t.tiles) * (t.ti.BM + t.ti.BN);
+        if (traffic >= least) continue;
+        least = traffic;
+        t.best(form, M, N, K, ws_elems);
+        near = t.choice;
+      }
+    best = near;
+  }
+  // A merged launch saves the step its own, about 3 us of the model's time, so
+  // the small tiles are taken unless another tile is faster by more than that.
+  if (merged) *merged = own_us <= best_us + 3.0 ? own : best;
+  return best;
 }
 
-// Split-K factor: about 1024 workgroups (four per CU) when the output has
+// Split-K factor: about 2048 workgroups (eight per CU) when the output has
 // few tiles and the contraction is long (e.g. M = N = o, K = o v^2), each
 // split covering at least 256 of K.
 // Independent of the tile so that the autotuner can change tiles freely.

@@ -423,13 +423,13 @@ struct Planner {
       return;
     }
     const bool direct = d.sak == 1 && d.sbk == 1;
-    const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, direct, int64_t(1) << 24);
+    F64Choice own;
+    const F64Choice ch = gemm_f64_choose(d.M, d.N, d.K, direct, kMergeWork, small() ? &own : nullptr);
     g.tile = ch.tile;
     g.split64 = ch.split;
     if (small()) {
       // (a batch, whose launches group one step of all its systems, takes the
       // factor, so that its systems' results stay those of their own plans)
-      const F64Choice own = gemm_f64_choose_merged(d.M, d.N, d.K, direct, kMergeWork);
       g.split64 = own.split;
       if (p->merge) {
         g.tile = own.tile;
@@ -1670,12 +1670,17 @@ void plan_levels(cc_plan *p) {
   std::vector<int> tiles;
   for (const Step &st : p->iter)
     if (st.kind == Step::GEMM) tiles.insert(tiles.end(), {st.tile, st.split64});
-  if (p->level_tabs.empty() || tiles != p->level_tiles) {
-    void *mem = dev_alloc(tab.size());
-    p->level_tabs.push_back(mem);
+  if (!p->level_tab || tiles != p->level_tiles) {
+    void *mem = p->level_first;
+    if (p->level_tab) {
+      mem = dev_alloc(tab.size());
+      p->level_tabs.push_back(mem);
+    }
+    CC_REQUIRE(p->level_tab || tab.size() <= p->level_room, CC_EINTERNAL, "merged launches: table size");
     hipStream_t s = p->ctx->stream;
-    CC_HIP_CHECK(hipMemcpyAsync(mem, tab.data(), tab.size(), hipMemcpyHostToDevice, s));
-    CC_HIP_CHECK(hipStreamSynchronize(s));
+    p->level_host.swap(tab);  // until the copy has read it
+    CC_HIP_CHECK(hipMemcpyAsync(mem, p->level_host.data(), p->level_host.size(), hipMemcpyHostToDevice, s));
+    if (p->level_tab) CC_HIP_CHECK(hipStreamSynchronize(s));  // (a new plan waits for its setup as well)
     p->level_tab = mem;
     p->level_items = items.size();
     p->level_tiles.swap(tiles);
@@ -1761,18 +1766,32 @@ void plan_layout(cc_plan *p, const cc_system *sys) {
 
 void plan_build(cc_plan *p, const cc_system *sys) {
   plan_layout(p, sys);
-  // owned slots and the small arrays, in one allocation (a plan has about a
-  // hundred of them, and each allocation takes 5 to 10 us)
+  // owned slots and the small arrays, in few allocations (a plan has about a
+  // hundred of them)
   p->n_epart = int(tau_units(p->o, p->v));
   p->n_n2part = int(asm_units(p->o, p->v));
   p->n_n3part = p->triples ? int(t3_units(p->o, p->v)) : 0;
-  size_t total = 0;
-  auto room = [&total](size_t bytes) {
-    const size_t at = total;
-    total += (bytes + 255) / 256 * 256;
+  // Each allocation below 2 MB costs under a microsecond, being carved out of
+  // memory that stays mapped; a larger one is mapped afresh (25 us with its free,
+  // and the setup's kernels wait for the mapping).  So the tensors of a small plan
+  // go into blocks below that size, the others into one block.
+  constexpr size_t kBlock = (size_t(2) << 20) - 4096, kSmallPlan = size_t(16) << 20;
+  struct Place {
+    size_t block, at;
+  };
+  std::vector<size_t> blocks;
+  size_t wanted = 0;
+  for (const Slot &sl : p->slots)
+    if (sl.owned) wanted += size_t(std::max<int64_t>(sl.elems, 1)) * p->esize;
+  const bool small = wanted <= kSmallPlan;
+  auto room = [&](size_t bytes) {
+    bytes = (bytes + 255) / 256 * 256;
+    if (blocks.empty() || (small && blocks.back() + bytes > kBlock)) blocks.push_back(0);
+    const Place at{blocks.size() - 1, blocks.back()};
+    blocks.back() += bytes;
     return at;
   };
-  std::vector<size_t> at(p->slots.size(), 0);
+  std::vector<Place> at(p->slots.size(), Place{0, 0});
   for (size_t i = 0; i < p->slots.size(); ++i) {
     const Slot &s = p->slots[i];
     if (!s.owned) continue;
@@ -1780,26 +1799,28 @@ void plan_build(cc_plan *p, const cc_system *sys) {
     at[i] = room(bytes);
     p->workspace += bytes;
   }
-  double *ticket = nullptr;
   const struct {
     double **ptr;
     size_t n;
-  } arrays[] = {{&p->d_oo, size_t(p->o)},       {&p->d_vv, size_t(p->v)},       {&p->epart, size_t(2) * p->n_epart},
-                {&p->n2part, size_t(p->n_n2part)}, {&p->n1part, 2},             {&p->n3part, size_t(p->n_n3part)},
-                {&p->scalars, 4},               {&ticket, 1}};
-  size_t aat[8];
-  for (int k = 0; k < 8; ++k) aat[k] = room(sizeof(double) * arrays[k].n);
-  p->mem = dev_alloc(total);
-  char *base = static_cast<char *>(p->mem);
+  } arrays[] = {{&p->d_oo, size_t(p->o)},       {&p->d_vv, size_t(p->v)}, {&p->epart, size_t(2) * p->n_epart},
+                {&p->n2part, size_t(p->n_n2part)}, {&p->n1part, 3},       {&p->n3part, size_t(p->n_n3part)},
+                {&p->scalars, 4}};  // n1part: two sums, and the ticket
+  Place aat[7];
+  for (int k = 0; k < 7; ++k) aat[k] = room(sizeof(double) * arrays[k].n);
+  // the first table of the merged launches: two items a step at most
+  p->level_room = p->merge ? 2 * p->iter.size() * (sizeof(LevelItem) + sizeof(int)) : 0;
+  const Place tab_at = room(p->level_room);
+  for (size_t bytes : blocks) p->mem.push_back(dev_alloc(bytes));
+  auto address = [p](const Place &x) { return static_cast<char *>(p->mem[x.block]) + x.at; };
   for (size_t i = 0; i < p->slots.size(); ++i)
-    if (p->slots[i].owned) p->slots[i].ptr = base + at[i];
-  for (int k = 0; k < 8; ++k)
-    if (arrays[k].n) *arrays[k].ptr = reinterpret_cast<double *>(base + aat[k]);
+    if (p->slots[i].owned) p->slots[i].ptr = address(at[i]);
+  for (int k = 0; k < 7; ++k)
+    if (arrays[k].n) *arrays[k].ptr = reinterpret_cast<double *>(address(aat[k]));
+  if (p->merge) p->level_first = address(tab_at);
   hipStream_t s = p->ctx->stream;
   fock_diag(p->cplx, p->o, p->v, sys->f_oo, sys->f_vv, p->d_oo, p->d_vv, s);
-  fill_zero(p->n1part, 2, false, s);
-  fill_zero(ticket, 1, false, s);
-  p->ticket = reinterpret_cast<unsigned *>(ticket);
+  fill_zero(p->n1part, 3, false, s);
+  p->ticket = reinterpret_cast<unsigned *>(p->n1part + 2);
   if (p->packed) {
     auto upload = [&](std::vector<int> h, int **dst) {
       if (h.empty()) h.assign(2, 0);
@@ -1830,6 +1851,7 @@ void plan_build(cc_plan *p, const cc_system *sys) {
     upload(am, &p->pair_tab[3]);
   }
   for (Step &st : p->setup) exec(p, st, s);
+  plan_levels(p);  // beside the setup's kernels
   CC_HIP_CHECK(hipStreamSynchronize(s));
   for (Step &st : p->iter)
     if (st.kind == Step::GEMM) p->gemm_steps.push_back(&st);
@@ -1908,7 +1930,6 @@ void plan_build(cc_plan *p, const cc_system *sys) {
       st.blk_a = form(p->cplx ? 2 : 1, st.a, g.K);
       st.blk_b = form(p->cplx ? 3 : 1, st.b, g.K);
     }
-  plan_levels(p);
 }
 
 void plan_free(cc_plan *p) {
@@ -1916,8 +1937,8 @@ void plan_free(cc_plan *p) {
   p->events.clear();
   if (p->graph) (void)hipGraphExecDestroy(p->graph);
   p->graph = nullptr;
-  if (p->mem) (void)hipFree(p->mem);
-  p->mem = nullptr;
+  for (void *q : p->mem) (void)hipFree(q);
+  p->mem.clear();
   for (void *q : p->shadow)
     if (q) (void)hipFree(q);
   p->shadow.clear();

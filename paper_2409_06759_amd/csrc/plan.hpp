@@ -141,10 +141,13 @@ struct cc_plan {
   };
   std::vector<Level> levels;
   size_t level_tail = 0;          // steps from here on are run after the levels
-  void *level_tab = nullptr;      // items, then offsets: the last of level_tabs
+  void *level_tab = nullptr;      // items, then offsets: level_first, or the last of level_tabs
+  void *level_first = nullptr;    // in mem
+  size_t level_room = 0;
   size_t level_items = 0;
   std::vector<int> level_tiles;   // tile and split-K factor of every GEMM it was made for
-  std::vector<void *> level_tabs; // every table made, for graphs the caller captured
+  std::vector<void *> level_tabs; // every later table, kept for graphs the caller captured
+  std::vector<unsigned char> level_host;
   unsigned *ticket = nullptr;     // of the last launch; zero between runs
   int *pair_tab[4] = {nullptr, nullptr, nullptr, nullptr};  // device index-pair tables
   // triples (op lists that read t3 or accumulate Y3): bound per plan
@@ -159,7 +162,7 @@ struct cc_plan {
   std::map<int, int> version;             // writes seen so far while planning
   std::map<int, bool> touched;            // first write of an iteration uses beta = 0
   size_t workspace = 0;
-  void *mem = nullptr;                    // the owned slots and the arrays below
+  std::vector<void *> mem;                // the owned slots and the arrays below
   // scalar machinery (device)
   double *d_oo = nullptr, *d_vv = nullptr;
   double *epart = nullptr, *n2part = nullptr, *n1part = nullptr, *scalars = nullptr;
