@@ -445,7 +445,7 @@ __device__ __forceinline__ void r1_body(const R1Entry &E, void *smem) {
   if (threadIdx.x == 0) E.partial[0] = s;
 }
 
-// scalars[0] = ||R||, scalars[1..2] = E (re, im); fixed summation order.
+// Packed index pairs, gathered (mode 0), added back (1) or scattered (2).
 template <class T, class Res = SamePtr>
 __device__ __forceinline__ void pair_body(const PairEntry &E, int64_t bid, void *, Res rs = Res{}) {
   const T *__restrict__ src = static_cast<const T *>(rs(E.src));
@@ -614,6 +614,7 @@ __device__ __forceinline__ void t3_body(const T3Entry &E, int64_t bid, void *sme
   if (threadIdx.x == 0) E.partials[bid] = tot;
 }
 
+// scalars[0] = ||R||, scalars[1..2] = E (re, im); fixed summation order.
 __device__ __forceinline__ void fin_body(const FinEntry &E, void *smem) {
   double *sh = static_cast<double *>(smem);
   double a = 0.0, b = 0.0, c = 0.0;

@@ -303,10 +303,10 @@ const char *gemm_f64_tile_name(int id) { return (id >= 0 && id < kNumTiles) ? kT
 // when there are too few of them to hide it.  That time competes with the
 // operands' and outputs' HBM traffic and with the tiles' operand traffic from
 // the L2s; the shorter of the two is partly hidden.  Over those shapes the
-// choice is 2.5% (geometric mean) slower than the fastest configuration; the
-// rule it replaced (rounds of 256 workgroups x tile area, staged tiles first)
-// was 37% slower, on launches over 50 us: ladder 1024 x 25600 x 25600
-// 28.3 -> 20.0 ms, 2000^3 394 -> 295 us, 160000 x 400 x 400 1.97 -> 1.28 ms,
+// choice was 2.5% (geometric mean) slower than the fastest configuration when
+// fitted; the rule it replaced (rounds of 256 workgroups x tile area, staged tiles
+// first) was 37% slower, on launches over 50 us: ladder 1024 x 25600 x 25600
+// 28.3 -> 19.6 ms, 2000^3 394 -> 258 us, 160000 x 400 x 400 1.97 -> 1.28 ms,
 // 10 x 6400000 x 10 0.61 -> 0.46 ms.  The autotuner refines it by timing.
 // A launch that is cut into whole rounds and a K-split tail (gemm_tail_cut) counts as
 // such, and among choices within 5% the one with the least operand traffic through
@@ -315,8 +315,8 @@ const char *gemm_f64_tile_name(int id) { return (id >= 0 && id < kNumTiles) ? kT
 // HBM as 256 x 128 (20.8 against 19.6 ms).  Over 62 shapes of 2e9 flops and more the
 // choice is 4.0% slower than the fastest configuration, 4.9% without the two.
 // The 64x64 configuration was fitted to 4,000 timings of 160 small and middle
-// shapes; it is the fastest one from about 800^3 (34 -> 32 us) to 1300^3
-// (105 -> 95 us) and on long contractions (400 x 2000 x 10000 376 -> 317 us).
+// shapes; it is the fastest one at 1024^3 (64 x 128 50, 64 x 64 45 us) and 1280^3 (93,
+// 88 us), and on long contractions (400 x 2000 x 10000 309, 299 us).
 struct F64Model {
   int tile;       // kTiles index
   int resident;   // workgroups per CU

@@ -747,8 +747,10 @@ void dense(int prec, int64_t M, int64_t N, int64_t K, const double *A, int64_t s
 // Slices of the fused backward pass: those of the layer-by-layer gradient
 // GEMMs (their split-K factors, whole 16-row chunks), so that the partial sums
 // are the same.  The sums over rows with a vector go out several times per
-// dW2 slice; minibatches whose slice lengths do not fit each other that way
-// (2c above 65,536 and no multiple of it) run layer by layer.
+// dW2 slice; minibatches whose slice lengths do not fit each other that way run
+// layer by layer, at the times of those passes.  Up to 32,768 samples all fit,
+// above one size in sixteen (32769 to 34815 but for multiples of 128, and the
+// multiples of 128 from 63616 to the default of 65536).
 constexpr int64_t WS_ELEMS = 256 * int64_t(HID) * HID;
 bool fused_slices(int64_t R, GradSplits *g) {
   auto pick = [R](int64_t M, int64_t N, int *split, int64_t *kc) {
