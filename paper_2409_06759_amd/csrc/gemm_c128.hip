@@ -226,7 +226,7 @@ __global__ __launch_bounds__(WM *WN *kWave) void gemm_c128_dma_kernel(GemmDesc d
   // chunks, and whole ones (32-bit scalars, and running pointers advanced behind
   // the MFMAs, as in the real kernel: formed at the loads, the addresses cost
   // 1600 x 8000 x 8000 15.4 instead of 13.8 ms on 64 x 128, 400 x 2000 x 2001 360
-  // instead of 328 us on 64 x 64)
+  // instead of 313 us on 64 x 64)
   const int nk = __builtin_amdgcn_readfirstlane(int((K + BK - 1) / BK)), nf = __builtin_amdgcn_readfirstlane(int(K / BK));
 
   // load j of this wave (j = LOADS wave + u): block j >> 2 of the stage (A
@@ -301,7 +301,8 @@ __global__ __launch_bounds__(WM *WN *kWave) void gemm_c128_dma_kernel(GemmDesc d
         }
       }
       if (s <= 1) __builtin_amdgcn_sched_barrier(0);
-      if (s == 1) advance();
+      // (a branch in the 64 x 64 kernel: without it 1 to 8% slower; with one, 64 x 128 is 3%)
+      if (s == 1 && (NST == 3 || FM * FN == 1 || kt + NST - 1 < nk)) advance();
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
