@@ -420,7 +420,8 @@ int cc_plan_set_precision(cc_plan *plan, int prec);
 int cc_plan_set_correction(cc_plan *plan, int mode, int prec);
 /* Autotuner: times every instantiated GEMM tile configuration (of the
  * plan's current precision) for each distinct GEMM shape of the plan (reps launches each, on the plan's own
- * buffers, with t as the amplitude operand) and keeps the fastest.  Choices
+ * buffers, with t as the amplitude operand, after evaluating the intermediates at t: the time depends on
+ * the data) and keeps the fastest.  Choices
  * are cached per shape for the life of the process; if the environment
  * variable CC_AUTOTUNE_CACHE names a file, choices are also read from it at
  * the process's first autotune and new ones appended to it (lines

@@ -99,3 +99,23 @@ def test_choices_of_another_library(tmp_path):
     r = subprocess.run([sys.executable, "-c", FOREIGN.format(root=ROOT)], capture_output=True, text=True, timeout=100,
                        env={**os.environ, "CC_AUTOTUNE_CACHE": str(path)})
     assert r.returncode == 0 and "foreign choices ok" in r.stdout, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("prec", ["F64", "F32", "BF16X3"])
+def test_tuning_a_new_plan_only_reads_the_amplitudes(prec):
+    """The tiles are timed on the intermediates at t: t stays as it is, and the
+    residuals that follow, at t and at other amplitudes, are the untuned plan's
+    (same products in other tiles: rounding of the plan's type)."""
+    from paper_2409_06759_amd import engine as E
+    o, v = 6, 31
+    t1, t2 = _amps(o, v)
+    k1, k2 = t1.clone(), t2.clone()
+    rel = {"F64": 1e-12, "F32": 1e-4, "BF16X3": 1e-3}[prec]
+    with E.Context(0) as ctx:
+        d = E.DeviceSystem(make_system(o, v, 5))
+        with E.Plan(ctx, d, E.CCSD, prec=getattr(E, prec)) as p, E.Plan(ctx, d, E.CCSD, prec=getattr(E, prec)) as q:
+            p.autotune(t1, t2, reps=1)
+            assert torch.equal(t1, k1) and torch.equal(t2, k2)
+            for scale in (1.0, 0.5):
+                got, want = p.residual(scale * t1, scale * t2)[1], q.residual(scale * t1, scale * t2)[1]
+                assert float((got - want).abs().max()) <= rel * float(want.abs().max())
