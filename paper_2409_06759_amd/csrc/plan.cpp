@@ -2061,7 +2061,8 @@ void plan_autotune(cc_plan *p, int reps) {
   // zeros of new buffers the chip draws less power, and 64 x 128 tiles seemed 7%
   // faster than 256 x 128 at 1024 x 25600 x 25600 (18.2 against 19.5 ms) where they
   // are 2% slower on data (19.9, 19.55) and read six times as much from HBM.
-  // (Only the workspace is written; a list that writes amplitudes is left out.)
+  // (Only the workspace is written; a list that writes amplitudes is left out.  A
+  // solve that tunes itself and starts from t = 0 has zero amplitudes here still.)
   bool writes_amplitudes = false;
   for (const Step &st : p->iter) writes_amplitudes = writes_amplitudes || (st.c >= 0 && p->slots[st.c].external);
   if (p->delta_mode == 0 && !p->triples && !writes_amplitudes) {
