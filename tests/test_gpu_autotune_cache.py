@@ -119,3 +119,21 @@ def test_tuning_a_new_plan_only_reads_the_amplitudes(prec):
             for scale in (1.0, 0.5):
                 got, want = p.residual(scale * t1, scale * t2)[1], q.residual(scale * t1, scale * t2)[1]
                 assert float((got - want).abs().max()) <= rel * float(want.abs().max())
+
+
+@pytest.mark.parametrize("packed,prec", [(False, "F64"), (True, "F64"), (True, "BF16X3")])
+def test_tuning_at_unset_amplitudes_leaves_nothing_behind(packed, prec):
+    """A solve may tune before its amplitudes are formed: what the workspace
+    holds afterwards must not reach the iterations that follow."""
+    from paper_2409_06759_amd import engine as E
+    o, v = 7, 37
+    t1, t2 = _amps(o, v)
+    rel = {"F64": 1e-12, "BF16X3": 1e-3}[prec]
+    with E.Context(0) as ctx:
+        d = E.DeviceSystem(make_system(o, v, 5))
+        with E.Plan(ctx, d, E.CCSD, prec=getattr(E, prec), packed=packed) as p, \
+                E.Plan(ctx, d, E.CCSD, prec=getattr(E, prec), packed=packed) as q:
+            p.autotune(torch.full_like(t1, float("nan")), torch.full_like(t2, float("nan")), reps=1)
+            got, want = p.residual(t1, t2), q.residual(t1, t2)
+            for a, b in zip(got[:2], want[:2]):
+                assert float((a - b).abs().max()) <= rel * float(b.abs().max())
